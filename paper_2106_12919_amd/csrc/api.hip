@@ -161,6 +161,7 @@ struct SpeciesScratch {
   int* cursor = nullptr;
   int* nbr = nullptr;       // [27 * ntiles]: per tile, particles per neighbour tile (from the deposition)
   int* nbr_base = nullptr;  // [27 * ntiles]: per tile, first slot of its run in each neighbour tile
+  unsigned short* deal = nullptr;  // [n]: order of each tile's particles, from the deposition for the next gather
 };
 
 template <typename T>
@@ -216,8 +217,8 @@ struct Engine : EngineBase {
     if (sps.size() <= s) sps.resize(s + 1);
     SpeciesScratch<T>& x = sps[s];
     if (x.cap >= n) return hipSuccess;
-    void* old[17] = {x.cell, x.off[0], x.off[1], x.off[2], x.u[0], x.u[1], x.u[2], x.w, x.dst, x.perm,
-                     x.counts[0], x.counts[1], x.starts[0], x.starts[1], x.cursor, x.nbr, x.nbr_base};
+    void* old[18] = {x.cell, x.off[0], x.off[1], x.off[2], x.u[0], x.u[1], x.u[2], x.w, x.dst, x.perm,
+                     x.counts[0], x.counts[1], x.starts[0], x.starts[1], x.cursor, x.nbr, x.nbr_base, x.deal};
     for (void* q : old)
       if (q) (void)release_one(q);
     x = SpeciesScratch<T>{};
@@ -239,6 +240,7 @@ struct Engine : EngineBase {
     if ((e = alloc(&x.w, m)) != hipSuccess) return e;
     if ((e = alloc(&x.dst, m)) != hipSuccess) return e;
     if ((e = alloc(&x.perm, m)) != hipSuccess) return e;
+    if ((e = alloc(&x.deal, m)) != hipSuccess) return e;
     x.cap = n;
     return hipSuccess;
   }
@@ -1129,7 +1131,7 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
           permute_species<T>(cur, alt, x.dst, c->stream);
         else if (mobile)
           gather_push_tiled<T>(g, e.tiles, Enod, Bnod, cur, alt, nullptr, x.starts[L], true, x.cursor, x.nbr_base,
-                               c->stream);
+                               c->stream, x.deal);
       }
       const SpeciesView<T> dep = (first || mobile) ? alt : cur;  // immobile species stay put after the first step
       {
@@ -1137,7 +1139,7 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
         int* nextc = mobile ? x.counts[first ? 1 : L] : nullptr;
         deposit_tiled<T>(g, e.tiles, dep, nullptr, dep_starts, mobile, e.stage, c->d_bad, nextc,
                          mobile ? x.nbr : nullptr, e.work, sum.spill_rho(), sum.spill_j(), c->stream, sum.begin(),
-                         e.box_faces);
+                         e.box_faces, mobile ? x.deal : nullptr);
       }
       {
         StageScope sc(c, ST_REDUCE);

@@ -188,11 +188,13 @@ void neighbour_bases(const TileGeom& t, const int* old_starts, const int* nbr_co
 // particle's current cell, slots reserved per block from home_cursor (the new starts);
 // nbr_bases (optional, from neighbour_bases) holds, per home tile, the first slot of
 // its particles bound for each neighbour tile [27 * ntiles]; without it each block
-// counts its particles and reserves the runs with atomics on home_cursor.
+// counts its particles and reserves the runs with atomics on home_cursor.  ``deal`` (optional, from the
+// deposition that counted this grouping; cubic shapes): the order in which to visit each tile's particles.
 template <typename T>
 void gather_push_tiled(const GridGeom& g, const TileGeom& t, const T* const E[3], const T* const B[3],
                        const SpeciesView<T>& in, const SpeciesView<T>& out, const int* perm, const int* starts,
-                       bool write_sorted, int* home_cursor, const int* nbr_bases, hipStream_t s);
+                       bool write_sorted, int* home_cursor, const int* nbr_bases, hipStream_t s,
+                       const unsigned short* deal = nullptr);
 template <typename T>
 void permute_species(const SpeciesView<T>& in, const SpeciesView<T>& out, const int* dst, hipStream_t s);
 // Deposition of one species in two launches.  deposit_tiled accumulates rho (at the
@@ -209,11 +211,13 @@ void permute_species(const SpeciesView<T>& in, const SpeciesView<T>& out, const 
 // ``spill_flag`` (optional) is set to 1 whenever a particle goes to rho/J directly.  With
 // ``box_faces`` (ntiles ints, optional; used on grids of whole tiles) each tile stages only
 // the layers of its box that hold a nonzero value and records which outer faces it staged,
-// for a deposit_reduce with the same array in ReduceArgs::box_faces.
+// for a deposit_reduce with the same array in ReduceArgs::box_faces.  ``deal`` (optional, one per slot;
+// cubic shapes) receives the order in which each tile's particles were visited, chunk by chunk.
 template <typename T>
 void deposit_tiled(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& sp, const int* perm, const int* starts,
                    bool with_j, T* stage, int* bad, int* next_counts, int* nbr_counts, int* work, T* rho,
-                   T* const J[3], hipStream_t s, int* spill_flag = nullptr, int* box_faces = nullptr);
+                   T* const J[3], hipStream_t s, int* spill_flag = nullptr, int* box_faces = nullptr,
+                   unsigned short* deal = nullptr);
 // How deposit_reduce starts each node and what else it folds in.  By default it adds to the
 // nodal arrays.  With bit 0 (rho) or bit 1 (J) of acc_mask clear it overwrites them instead,
 // rho starting from ``base`` when given, else from zero.  When *flag != 0, the ``spill``

@@ -29,12 +29,6 @@ constexpr int kGatherBlock = (sizeof(T) == 4 && ORDER == 3) ? PIC_GATHER_BLOCK_F
 #ifndef PIC_DEPOSIT_BLOCK
 #define PIC_DEPOSIT_BLOCK 256
 #endif
-#ifndef PIC_DEPOSIT_BOUND_LOAD
-#define PIC_DEPOSIT_BOUND_LOAD 1
-#endif
-#ifndef PIC_DEPOSIT_CELL_KEY
-#define PIC_DEPOSIT_CELL_KEY 1
-#endif
 
 namespace pic {
 
@@ -548,6 +542,22 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_perm(G
   }
 }
 
+// Order of the particles inside a deposition chunk.  LDS atomics of a wave retire
+// without bank conflicts when the 32 lanes of each half wave address distinct words
+// modulo 32 (4-byte accumulators), or the 16 lanes of each quarter wave distinct
+// 8-byte words modulo 16 (measured on gfx950).  All atomics of a particle are at its
+// first support node plus a constant, so particles whose first nodes differ modulo
+// KG never conflict: they are dealt round-robin over the KG residues, row r of the
+// deal holding the r-th particle of every residue that has one.
+template <typename T>
+struct DepositOrder {
+  static constexpr int KG = sizeof(T) == 4 ? 32 : 16;
+  static constexpr int CH = sizeof(T) == 4 ? 1024 : 512;  // particles per chunk
+  static constexpr int RMAX = CH / 4;  // deal rows; a chunk with more keeps its stored order
+  static constexpr int U = CH / PIC_DEPOSIT_BLOCK;  // particles per thread and chunk, loaded together
+  static_assert(CH % PIC_DEPOSIT_BLOCK == 0, "a chunk is a whole number of particles per thread");
+};
+
 // Steady-state gather + push of pic_step.  ``in`` is grouped by home tile h (the
 // tile of the previous step's positions; slots [home[h], home[h+1])), so every
 // particle lies within one cell of its home tile and the LDS box of h covers it.
@@ -557,12 +567,22 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_perm(G
 // (the start of each tile in the new grouping, from the counts the previous
 // deposition took), then gathers, pushes and writes each particle to base + its
 // rank from a second LDS count.  Block ntiles carries invalid cells to the last bucket.
+//
+// The cubic gather was bound by its LDS reads: 64 nodes of 16 + 8 bytes per particle, each pair 9.4 clocks
+// per wave when the lanes' first nodes are distinct modulo 32, 20.6 in cell order and 26 in random order
+// (measured; LDS-active 71% of the beam wake's gather, 56% of that conflicts).  ``deal`` is the order in
+// which the previous deposition visited the same particles (dealt round-robin over those residues, per
+// chunk of DepositOrder<T>::CH); the gather takes it over, and as it writes in the order it visits, memory
+// stays nearly dealt and the deposition's own loads nearly contiguous.  64 x 64 x 128, 4 per cell, FP32:
+// 126 -> 98 us; 128 x 128 x 256, 2 per cell: 333 -> 311; FP64 192 x 192 x 384, 1 per cell: 1915 -> 1786.
+// Linear shapes (8 nodes) are bound by HBM and lose by it (FP32 +1%, FP64 +19% through 129 VGPRs): not used.
 template <typename T, int ORDER>
 __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_home(GridGeom g, TileGeom tg, Batch<const T*> F,
                                                                        SpeciesView<T> in, SpeciesView<T> out,
                                                                        const int* __restrict__ home, int* cursor,
-                                                                       const int* __restrict__ nbr_bases, T qdt2m,
-                                                                       T dtx, T dty, T dtz) {
+                                                                       const int* __restrict__ nbr_bases,
+                                                                       const unsigned short* __restrict__ deal,
+                                                                       T qdt2m, T dtx, T dty, T dtz) {
   extern __shared__ __align__(16) unsigned char smem[];
   T* box = reinterpret_cast<T*>(smem);
   __shared__ int cnt[27];
@@ -612,8 +632,16 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_home(G
   // loads in flight meanwhile.  They are issued after the slot is reserved: the rare
   // global reservation returns into the slot's register, and the wait for it would
   // otherwise also wait for the prefetch.
+  auto at = [&](int qq) {  // the particle at place qq of the dealt order
+    constexpr int CH = DepositOrder<T>::CH;
+    return (ORDER == 3 && deal) ? beg + ((qq - beg) & ~(CH - 1)) + deal[qq] : qq;
+  };
   Raw<T> nxt;
-  if (beg + (int)threadIdx.x < end) load_raw<T, true>(in, beg + threadIdx.x, nxt);
+  int pn = 0;  // the particle after the one in ``nxt``
+  if (beg + (int)threadIdx.x < end) {
+    load_raw<T, true>(in, at(beg + threadIdx.x), nxt);
+    pn = at(min(beg + (int)threadIdx.x + (int)blockDim.x, end - 1));
+  }
   for (int qq = beg + threadIdx.x; qq < end; qq += blockDim.x) {
     const Raw<T> r = nxt;
     int i, j, k;
@@ -631,7 +659,8 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_home(G
     } else {
       slot = nb >= 0 ? base[nb] + atomicAdd(&cnt[nb], 1) : atomicAdd(&cursor[tile_of(i, j, k, tg)], 1);
     }
-    load_raw<T, true>(in, min(qq + (int)blockDim.x, end - 1), nxt);
+    load_raw<T, true>(in, pn, nxt);
+    pn = at(min(qq + 2 * (int)blockDim.x, end - 1));
     T ox = r.o[0], oy = r.o[1], oz = r.o[2];
     T ux = r.u[0], uy = r.u[1], uz = r.u[2];
     const int lx = box_index(i, t0x, g.nx), ly = box_index(j, t0y, g.ny), lz = box_index(k, t0z, g.nz);
@@ -845,22 +874,6 @@ __device__ inline void unpack_xy(unsigned long long w, int& x, int& y) {
   y = (int)((long long)(w - (unsigned long long)(long long)x) >> 32);
 }
 
-// Order of the particles inside a deposition chunk.  LDS atomics of a wave retire
-// without bank conflicts when the 32 lanes of each half wave address distinct words
-// modulo 32 (4-byte accumulators), or the 16 lanes of each quarter wave distinct
-// 8-byte words modulo 16 (measured on gfx950).  All atomics of a particle are at its
-// first support node plus a constant, so particles whose first nodes differ modulo
-// KG never conflict: they are dealt round-robin over the KG residues, row r of the
-// deal holding the r-th particle of every residue that has one.
-template <typename T>
-struct DepositOrder {
-  static constexpr int KG = sizeof(typename Fixed<T>::acc_t) == 4 ? 32 : 16;
-  static constexpr int CH = sizeof(typename Fixed<T>::acc_t) == 4 ? 1024 : 512;  // particles per chunk
-  static constexpr int RMAX = CH / 4;  // deal rows; a chunk with more keeps its stored order
-  static constexpr int U = CH / PIC_DEPOSIT_BLOCK;  // particles per thread and chunk, loaded together
-  static_assert(CH % PIC_DEPOSIT_BLOCK == 0, "a chunk is a whole number of particles per thread");
-};
-
 // What the deposition needs of one particle: its cell and offsets at x, the velocity,
 // the cell and offsets at x - dt v / 2, and the box indices of the first support
 // node at both positions (-1 outside the box margin).
@@ -949,7 +962,8 @@ __device__ inline void block_exclusive_scan(int* a, int n, int* wtot) {
 // boxes on the grid.  (A particle outside the margin is added to the grid directly
 // with global atomics.)  With next_counts, the tiles of the particles' cells (the
 // next grouping) are counted: per tile in next_counts, per neighbour of this tile in
-// nbr_counts[27 * tile ...] (what the next gather of this tile's particles reserves).
+// nbr_counts[27 * tile ...] (what the next gather of this tile's particles reserves), and ``deal``
+// receives the order in which the tile's particles were visited (cubic shapes).
 // LDS of a deposition workgroup besides the box.
 template <typename T>
 struct DepositLds {
@@ -963,7 +977,6 @@ struct DepositLds {
   int next_tile;
   int cross;  // faces of the box holding a nonzero value (see deposit_tile)
   __align__(16) int hist[O::KG];
-  unsigned short kr[O::CH];
   unsigned short order[O::CH];
   unsigned rowmask[O::RMAX];
   int rowstart[O::RMAX];
@@ -975,7 +988,7 @@ __device__ inline void deposit_tile(int tile, const GridGeom& g, const TileGeom&
                                     const int* __restrict__ perm, const int* __restrict__ starts,
                                     const Batch<T*>& out, T* __restrict__ stage, T qdv, T hdtx, T hdty, T hdtz,
                                     int* bad, int* next_counts, int* nbr_counts, int* spill_flag, int* box_faces,
-                                    typename Fixed<T>::acc_t* box, DepositLds<T>& L) {
+                                    unsigned short* deal, typename Fixed<T>::acc_t* box, DepositLds<T>& L) {
   using S = Shape<T, ORDER>;
   using X = Box<S::NW>;
   using O = DepositOrder<T>;
@@ -990,7 +1003,6 @@ __device__ inline void deposit_tile(int tile, const GridGeom& g, const TileGeom&
   int* cnt = L.cnt;
   int* wtot = L.wtot;
   int* hist = L.hist;
-  unsigned short* kr = L.kr;
   unsigned short* order = L.order;
   unsigned* rowmask = L.rowmask;
   int* rowstart = L.rowstart;
@@ -1049,10 +1061,7 @@ __device__ inline void deposit_tile(int tile, const GridGeom& g, const TileGeom&
       Raw<T> r[O::U];
 #pragma unroll
       for (int u = 0; u < O::U; ++u) {
-        if (PIC_DEPOSIT_BOUND_LOAD)
-          load_bound<T, WJ>(sp, qi[u], r[u]);
-        else
-          load_raw<T, WJ>(sp, qi[u], r[u]);
+        load_bound<T, WJ>(sp, qi[u], r[u]);
       }
 #pragma unroll
       for (int u = 0; u < O::U; ++u)
@@ -1081,9 +1090,9 @@ __device__ inline void deposit_tile(int tile, const GridGeom& g, const TileGeom&
     // from the particle's cell alone (rho's first node; one int per particle instead of its whole
     // record, with momentum and weight for the bounds of a single-chunk tile): the first support
     // node of the current shifts from it only when the half step crosses a cell face, and the
-    // deal only orders the atomics, it does not change their sums.  PIC_DEPOSIT_CELL_KEY 0 keys
-    // by the current's first node instead.
-    if (PIC_DEPOSIT_CELL_KEY) {
+    // deal only orders the atomics, it does not change their sums.
+    int kr[O::U];  // (rank, residue) of this thread's particles, until the deal below
+    {
       const int e0 = threadIdx.x;
       int qi[O::U];
 #pragma unroll
@@ -1098,39 +1107,14 @@ __device__ inline void deposit_tile(int tile, const GridGeom& g, const TileGeom&
       }
 #pragma unroll
       for (int u = 0; u < O::U; ++u) {
-        const int e = e0 + u * PIC_DEPOSIT_BLOCK;
-        if (e < nc) {
+        kr[u] = 0;
+        if (e0 + u * PIC_DEPOSIT_BLOCK < nc) {
           int i, j, k, key = 0;
           if (decode_cell(c[u], g, nullptr, i, j, k)) {
             const int lx = box_index(i, t0x, g.nx), ly = box_index(j, t0y, g.ny), lz = box_index(k, t0z, g.nz);
             if (lx >= 0 && ly >= 0 && lz >= 0) key = X::at(lx, ly, lz) & (O::KG - 1);
           }
-          const int rk = atomicAdd(&hist[key], 1);
-          kr[e] = (unsigned short)(rk * O::KG + key);
-          if (single) bound_add<T, WJ>(r[u], sw, mw);
-        }
-      }
-    } else {
-      const int e0 = threadIdx.x;
-      int qi[O::U];
-#pragma unroll
-      for (int u = 0; u < O::U; ++u) qi[u] = cb + min(e0 + u * PIC_DEPOSIT_BLOCK, nc - 1);
-      through_perm(perm, qi);
-      Raw<T> r[O::U];
-#pragma unroll
-      for (int u = 0; u < O::U; ++u) load_raw<T, WJ>(sp, qi[u], r[u]);
-#pragma unroll
-      for (int u = 0; u < O::U; ++u) {
-        const int e = e0 + u * PIC_DEPOSIT_BLOCK;
-        if (e < nc) {
-          DepositPoint<T> d;
-          int key = 0;
-          if (locate<T, ORDER, WJ>(r[u], g, t0x, t0y, t0z, hdtx, hdty, hdtz, nullptr, d)) {
-            const int at = WJ ? d.at_j : d.at_rho;
-            key = at >= 0 ? (at & (O::KG - 1)) : 0;
-          }
-          const int rk = atomicAdd(&hist[key], 1);
-          kr[e] = (unsigned short)(rk * O::KG + key);
+          kr[u] = atomicAdd(&hist[key], 1) * O::KG + key;
           if (single) bound_add<T, WJ>(r[u], sw, mw);
         }
       }
@@ -1155,16 +1139,18 @@ __device__ inline void deposit_tile(int tile, const GridGeom& g, const TileGeom&
     }
     __syncthreads();
     block_exclusive_scan(rowstart, R, wtot);
-    for (int e = threadIdx.x; e < nc; e += blockDim.x) {
-      if (R == 0) {
-        order[e] = (unsigned short)e;
-      } else {
-        const int v = kr[e];
-        const int r = v / O::KG, key = v % O::KG;
-        order[rowstart[r] + __popc(rowmask[r] & ((1u << key) - 1u))] = (unsigned short)e;
+#pragma unroll
+    for (int u = 0; u < O::U; ++u) {
+      const int e = threadIdx.x + u * PIC_DEPOSIT_BLOCK;
+      if (e < nc) {
+        const int r = kr[u] / O::KG, key = kr[u] % O::KG;
+        const int pos = R == 0 ? e : rowstart[r] + __popc(rowmask[r] & ((1u << key) - 1u));
+        order[pos] = (unsigned short)e;
       }
     }
     __syncthreads();
+    if (ORDER == 3 && deal)  // the next gather visits this tile's particles in the same order
+      for (int e = threadIdx.x; e < nc; e += blockDim.x) deal[cb + e] = order[e];
     int sh[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) sh[c] = (c < ncomp) ? shs[c] : 0;
@@ -1305,7 +1291,7 @@ __global__ void __launch_bounds__(PIC_DEPOSIT_BLOCK, sizeof(T) == 4 ? (ORDER == 
     k_deposit_tiled(GridGeom g, TileGeom tg, SpeciesView<T> sp, const int* __restrict__ perm,
                     const int* __restrict__ starts, Batch<T*> out, T* __restrict__ stage, T qdv, T hdtx, T hdty,
                     T hdtz, int* bad, int* next_counts, int* nbr_counts, int* work, int* spill_flag,
-                    int* box_faces) {
+                    int* box_faces, unsigned short* deal) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ DepositLds<T> L;
   auto* box = reinterpret_cast<typename Fixed<T>::acc_t*>(smem);
@@ -1317,11 +1303,11 @@ __global__ void __launch_bounds__(PIC_DEPOSIT_BLOCK, sizeof(T) == 4 ? (ORDER == 
       __syncthreads();
       if (tile > tg.ntiles) break;
       deposit_tile<T, ORDER, WJ>(tile, g, tg, sp, perm, starts, out, stage, qdv, hdtx, hdty, hdtz, bad, next_counts,
-                                 nbr_counts, spill_flag, box_faces, box, L);
+                                 nbr_counts, spill_flag, box_faces, deal, box, L);
     }
   } else {
     deposit_tile<T, ORDER, WJ>(blockIdx.x, g, tg, sp, perm, starts, out, stage, qdv, hdtx, hdty, hdtz, bad,
-                               next_counts, nbr_counts, spill_flag, box_faces, box, L);
+                               next_counts, nbr_counts, spill_flag, box_faces, deal, box, L);
   }
 }
 
@@ -2372,7 +2358,8 @@ int deposit_stage_slot(int shape_order) { return shape_order == 1 ? StageRows<1>
 template <typename T>
 void gather_push_tiled(const GridGeom& g, const TileGeom& t, const T* const E[3], const T* const B[3],
                        const SpeciesView<T>& in, const SpeciesView<T>& out, const int* perm, const int* starts,
-                       bool write_sorted, int* home_cursor, const int* nbr_bases, hipStream_t s) {
+                       bool write_sorted, int* home_cursor, const int* nbr_bases, hipStream_t s,
+                       const unsigned short* deal) {
   if (in.n <= 0) return;
   Batch<const T*> F{};
   for (int d = 0; d < 3; ++d) {
@@ -2389,11 +2376,11 @@ void gather_push_tiled(const GridGeom& g, const TileGeom& t, const T* const E[3]
     if (g.shape_order == 1) {
       allow_lds((const void*)k_gather_push_home<T, 1>, lds);
       hipLaunchKernelGGL((k_gather_push_home<T, 1>), grid, block, lds, s, g, t, F, in, out, starts, home_cursor,
-                         nbr_bases, qdt2m, dtx, dty, dtz);
+                         nbr_bases, deal, qdt2m, dtx, dty, dtz);
     } else {
       allow_lds((const void*)k_gather_push_home<T, 3>, lds);
       hipLaunchKernelGGL((k_gather_push_home<T, 3>), grid, block, lds, s, g, t, F, in, out, starts, home_cursor,
-                         nbr_bases, qdt2m, dtx, dty, dtz);
+                         nbr_bases, deal, qdt2m, dtx, dty, dtz);
     }
   } else {
     const int ws = write_sorted ? 1 : 0;
@@ -2424,7 +2411,7 @@ int resident_blocks(const void* kernel, int block, size_t lds) {
 template <typename T, int ORDER, bool WJ>
 void launch_deposit(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& sp, const int* perm, const int* starts,
                     T* stage, int* bad, int* next_counts, int* nbr_counts, int* work, int* spill_flag,
-                    int* box_faces, const Batch<T*>& out, hipStream_t s) {
+                    int* box_faces, unsigned short* deal, const Batch<T*>& out, hipStream_t s) {
   const T qdv = (T)(sp.q / (g.dx * g.dy * g.dz));
   const T hx = (T)(0.5 * g.dt / g.dx), hy = (T)(0.5 * g.dt / g.dy), hz = (T)(0.5 * g.dt / g.dz);
   constexpr int B = Box<Shape<T, ORDER>::NW>::B;
@@ -2439,13 +2426,14 @@ void launch_deposit(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& 
     (void)hipMemsetAsync(work, 0, sizeof(int), s);
   }
   hipLaunchKernelGGL((k_deposit_tiled<T, ORDER, WJ>), dim3(nb), dim3(PIC_DEPOSIT_BLOCK), lds, s, g, t, sp, perm,
-                     starts, out, stage, qdv, hx, hy, hz, bad, next_counts, nbr_counts, work, spill_flag, box_faces);
+                     starts, out, stage, qdv, hx, hy, hz, bad, next_counts, nbr_counts, work, spill_flag, box_faces,
+                     deal);
 }
 
 template <typename T>
 void deposit_tiled(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& sp, const int* perm, const int* starts,
                    bool with_j, T* stage, int* bad, int* next_counts, int* nbr_counts, int* work, T* rho,
-                   T* const J[3], hipStream_t s, int* spill_flag, int* box_faces) {
+                   T* const J[3], hipStream_t s, int* spill_flag, int* box_faces, unsigned short* deal) {
   if (sp.n <= 0) return;
   // the face masks serve the whole-tile reduction only; the other one reads whole boxes
   if (!(g.nx % kTile == 0 && g.ny % kTile == 0 && g.nz % kTile == 0)) box_faces = nullptr;
@@ -2453,11 +2441,11 @@ void deposit_tiled(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& s
   out.p[0] = rho;
   for (int d = 0; d < 3; ++d) out.p[1 + d] = J ? J[d] : nullptr;
   if (g.shape_order == 1) {
-    if (with_j) launch_deposit<T, 1, true>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, out, s);
-    else launch_deposit<T, 1, false>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, out, s);
+    if (with_j) launch_deposit<T, 1, true>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, deal, out, s);
+    else launch_deposit<T, 1, false>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, deal, out, s);
   } else {
-    if (with_j) launch_deposit<T, 3, true>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, out, s);
-    else launch_deposit<T, 3, false>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, out, s);
+    if (with_j) launch_deposit<T, 3, true>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, deal, out, s);
+    else launch_deposit<T, 3, false>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, deal, out, s);
   }
 }
 
@@ -2662,12 +2650,13 @@ void deposit_yee(const GridGeom& g, const SpeciesView<T>& sp, bool with_j, T* rh
 #define PIC_INST(T)                                                                                              \
   template void permute_species<T>(const SpeciesView<T>&, const SpeciesView<T>&, const int*, hipStream_t);       \
   template void deposit_tiled<T>(const GridGeom&, const TileGeom&, const SpeciesView<T>&, const int*, const int*, \
-                                 bool, T*, int*, int*, int*, int*, T*, T* const*, hipStream_t, int*, int*);      \
+                                 bool, T*, int*, int*, int*, int*, T*, T* const*, hipStream_t, int*, int*,       \
+                                 unsigned short*);                                                               \
   template void deposit_reduce<T>(const GridGeom&, const TileGeom&, const int*, const T*, bool, T*, T* const*,   \
                                   hipStream_t, const ReduceArgs<T>&);                                            \
   template void gather_push_tiled<T>(const GridGeom&, const TileGeom&, const T* const*, const T* const*,         \
                                      const SpeciesView<T>&, const SpeciesView<T>&, const int*, const int*, bool,  \
-                                     int*, const int*, hipStream_t);                                              \
+                                     int*, const int*, hipStream_t, const unsigned short*);                       \
   template void particle_adjoint<T>(const GridGeom&, const TileGeom&, const SpeciesView<T>&, const Batch<T*>&,    \
                                     const int*, const int*, const T* const*, const T* const*, const Batch<T*>&,   \
                                     hipStream_t);                                                                 \
