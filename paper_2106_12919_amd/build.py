@@ -16,8 +16,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpic.so")
-SOURCES = ["api.hip", "fft.hip", "centering.hip", "psatd.hip", "particles.hip", "sort.hip", "diag.hip", "tables.cpp",
-           "probe.hip"]
+# "file:K" compiles the file as its unit K (-DPIC_FFT_UNIT=K); the longest compilations first.
+SOURCES = ["particles.hip"] + [f"fft_len.hip:{k}" for k in reversed(range(16))] + [
+    "api.hip", "fft.hip", "centering.hip", "psatd.hip", "sort.hip", "diag.hip", "tables.cpp", "probe.hip"]
 
 ARCH = "gfx950"
 FLAGS = [
@@ -37,8 +38,11 @@ def _hipcc():
 
 
 def _compile(src, build_dir=BUILD, extra=()):
-    obj = os.path.join(build_dir, os.path.splitext(src)[0] + ".o")
-    cmd = [_hipcc(), "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj] + FLAGS + list(extra)
+    name, _, unit = src.partition(":")
+    obj = os.path.join(build_dir, os.path.splitext(name)[0] + unit + ".o")
+    cmd = [_hipcc(), "-x", "hip", "-c", os.path.join(CSRC, name), "-o", obj] + FLAGS + list(extra)
+    if unit:
+        cmd.append(f"-DPIC_FFT_UNIT={unit}")
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     return src, obj, r.returncode, r.stdout
 

@@ -1056,7 +1056,7 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
   // transforms (J_nod -> spectra of J on the Yee grid; updated spectra -> E_nod, B_nod of the
   // next step).  The last step takes the separate passes, so that at return E_stag, B_stag,
   // J_stag and E_nod, B_nod hold what the documented cycle leaves.
-  const bool fused = !spectral && !nodal && !avg && e.fft.centering_fusable();
+  const bool fused = !spectral && !nodal && !avg;
   const LineCenter<T> lc_j = fused ? transform_centering<T>(c, false) : LineCenter<T>();
   const LineCenter<T> lc_eb = fused ? transform_centering<T>(c, true) : LineCenter<T>();
   for (int n = 0; n < nsteps; ++n) {

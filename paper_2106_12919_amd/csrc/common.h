@@ -50,50 +50,64 @@ struct FftPlan {
   int twcount;
 };
 
-// The plan of an axis of n = 2^a 3^b points: the radix-3 stages first, then radix 8 with
-// a 4 x 4 or a 4 or a 2 for the rest of the power of two (nstages = -1 for other n).  A
-// constant expression, so that kernels specialised for an axis length take the same stages
-// and twiddle offsets as the table the host builds from it.
-constexpr FftPlan plan_of(int n) {
+// Stages of an axis of n = 2^a 3^b points: the fewest radices out of 2, 3, 4, 6, 8, 9, 12 with
+// product n (every stage is a pass over LDS and a barrier), of those the smallest sum (registers,
+// twiddles).
+constexpr int kRadices[] = {2, 3, 4, 6, 8, 9, 12};
+constexpr int plan_cost(int n) {  // 1000 per stage plus the sum of the radices; < 0: none
+  if (n == 1) return 0;
+  int best = -1;
+  for (int r : kRadices)
+    if (n % r == 0) {
+      const int c = plan_cost(n / r);
+      if (c >= 0 && (best < 0 || c + 1000 + r < best)) best = c + 1000 + r;
+    }
+  return best;
+}
+
+// The plan of an axis (nstages = -1 for other n).  Along z a line is contiguous in LDS and the first
+// stage writes at a stride of its radix, which conflicts on the banks unless the radix is odd: there a
+// length with a factor 3 starts with a stage of radix 9 or 3, also at the cost of one stage more
+// (c2r of 768 points, FP32, 384 x 384 lines: 12 8 8 1.40 ms, 3 8 8 4 1.35; 384 points, FP64: 6 8 8
+// 300 us, 3 8 4 4 293).  On the strided axes lanes run over lines, which never conflict, and the radices go
+// odd first, then from large to small.  A constant expression, so that the kernels specialised for
+// an axis length take the same stages and twiddle offsets as the table the host builds from it.
+constexpr FftPlan plan_of(int n, bool z) {
   FftPlan p{};
   p.n = n;
-  int rest = n, n3 = 0, n2 = 0;
-  while (rest > 0 && rest % 3 == 0) { rest /= 3; ++n3; }
-  while (rest > 0 && rest % 2 == 0) { rest /= 2; ++n2; }
-  int r[64] = {};
-  int k = 0;
-  if (rest == 1) {
-    for (int i = 0; i < n3; ++i) r[k++] = 3;
-    int n8 = n2 / 3;
-    const int rem = n2 % 3;
-    if (rem == 1 && n8 > 0) {
-      n8 -= 1;
-      for (int i = 0; i < n8; ++i) r[k++] = 8;
-      r[k++] = 4;
-      r[k++] = 4;
-    } else {
-      for (int i = 0; i < n8; ++i) r[k++] = 8;
-      if (rem == 2) r[k++] = 4;
-      if (rem == 1) r[k++] = 2;
-    }
-  }
-  if (rest != 1 || k > kMaxStages) {
+  int cost = n > 0 ? plan_cost(n) : -1;
+  if (cost < 0 || cost / 1000 > kMaxStages - 1) {
     p.nstages = -1;
     return p;
   }
+  int left = n, k = 0, count[16] = {};
+  if (z && n % 3 == 0) {
+    const int f = n % 9 == 0 ? 9 : 3;
+    p.radix[k++] = f;
+    left /= f;
+  }
+  while (left > 1)
+    for (int r : kRadices)
+      if (left % r == 0 && plan_cost(left / r) >= 0 && plan_cost(left / r) + 1000 + r == plan_cost(left)) {
+        ++count[r];
+        left /= r;
+        break;
+      }
+  const int order[] = {9, 3, 12, 8, 6, 4, 2};
+  for (int r : order)
+    for (int c = 0; c < count[r]; ++c) p.radix[k++] = r;
   p.nstages = k;
   int ns = 1, off = 0;
   for (int s = 0; s < k; ++s) {
-    p.radix[s] = r[s];
     p.ns[s] = ns;
     p.twoff[s] = off;
-    off += ns * (r[s] - 1);
-    ns *= r[s];
+    off += ns * (p.radix[s] - 1);
+    ns *= p.radix[s];
   }
   p.twcount = off;
   return p;
 }
-inline FftPlan make_fft_plan(int n) { return plan_of(n); }
+inline FftPlan make_fft_plan(int n, bool z) { return plan_of(n, z); }
 // FP64 twiddles of a plan, 2*twcount doubles (re, im) of exp(-2 pi i k r/(ns R)).
 void fft_twiddles(const FftPlan& p, double* out);
 

@@ -24,17 +24,19 @@ struct LineCenter {
 };
 
 template <typename T>
+struct FftOps;  // launchers of one axis length (fft_kernels.h)
+
+template <typename T>
 struct Fft3D {
   int nx = 0, ny = 0, nz = 0, nzh = 0, pz = 0;
   FftPlan plan[3];
+  const FftOps<T>* ops[3] = {nullptr, nullptr, nullptr};
   cplx<T>* tw[3] = {nullptr, nullptr, nullptr};
   hipError_t init(int nx, int ny, int nz);   // builds plans, uploads twiddles
   void release();
   size_t spectrum_elems() const { return (size_t)nx * ny * pz; }
-  // Whether every axis length has transform kernels of its own (LineCenter needs them).
-  bool centering_fusable() const;
-  // count <= kMaxBatch arrays, real -> spectrum; lc (optional, centering_fusable() only):
-  // centering of the inputs folded into the passes
+  // count <= kMaxBatch arrays, real -> spectrum; lc (optional): centering of the inputs folded into
+  // the passes
   void forward(const Batch<const T*>& in, const Batch<cplx<T>*>& out, int count, hipStream_t s,
                const LineCenter<T>* lc = nullptr) const;
   // spectrum -> real; ``scratch`` receives the partially transformed spectra (``in`` is preserved);

@@ -1,0 +1,96 @@
+"""Parity with the oracle at the edges of the kernels' dispatch rules: every axis length's own transform
+kernels, and tiles holding more particles than one dealing chunk."""
+
+import numpy as np
+import pytest
+
+from gpu_common import EPS, banner, max_rel, np64, oracle_species, periodic_pos_err, put, rounded
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from oracle import step as ostep  # noqa: E402
+from paper_2106_12919_amd import inputs  # noqa: E402
+from paper_2106_12919_amd import lib as piclib  # noqa: E402
+
+LENGTHS = sorted(2 ** a * 3 ** b for a in range(1, 11) for b in range(7) if 8 <= 2 ** a * 3 ** b <= 1024)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_field_solve_at_every_axis_length(dtype, axis):
+    """Each accepted length on x, y and z (the z transform takes other stages than the strided ones)."""
+    for n in LENGTHS:
+        shape = tuple(n if a == axis else (8, 18, 12)[a] for a in range(3))
+        banner(f"psatd_push_fields dtype={dtype} shape={shape}")
+        p = ostep.Params(shape, (1.0, 1.0, 1.0), 0.5, 1, 8, 16)
+        ctx = piclib.Context(shape, (1.0, 1.0, 1.0), 0.5, 1, 8, 16, dtype)
+        f = piclib.Fields(shape, dtype)
+        src = rounded(inputs.random_grid(shape, seed=n, count=11), dtype)
+        put(f.E_stag, src[0:3])
+        put(f.B_stag, src[3:6])
+        put(f.J_stag, src[6:9])
+        put([f.rho_old, f.rho_new], src[9:11])
+        piclib.psatd_push_fields(ctx.ctx, f)
+        piclib.pic_sync(ctx.ctx)
+        E, B = ostep.push_fields(src[0:3], src[3:6], src[6:9], src[9], src[10], p)
+        # log2(N) eps per transform (Higham), two transforms around the 11-term update, margin 10
+        tol = 10 * 2 * np.log2(np.prod(shape)) * EPS[dtype] * 3
+        for d in range(3):
+            assert max_rel(np64(f.E_stag[d]), E[d]) <= tol, (shape, "E", d)
+            assert max_rel(np64(f.B_stag[d]), B[d]) <= tol, (shape, "B", d)
+        ctx.close()
+
+
+def steps_against_oracle(shape, ppc, order, center, dtype, nsteps, flags=0, seed=31):
+    """One call of ``nsteps`` cycles against as many oracle steps: fields, sources and every particle."""
+    wl = inputs.small(shape, ppc=ppc, shape_order=order, center_order=center, dtype=dtype, u_th=0.2,
+                      field_amp=0.02, seed=seed)
+    base = 2.0 ** np.floor(np.log2(wl.electrons.w[0]))
+    wl.electrons.w = base * (1.0 + np.arange(wl.electrons.n) * 2.0 ** -23)  # identities, exact in FP32
+    ctx = piclib.Context.for_workload(wl, flags=flags)
+    f = ctx.fields_from_workload(wl)
+    el = piclib.Species.from_host(wl.electrons, shape, dtype)
+    ions = piclib.Species.from_host(wl.ions, shape, dtype)
+    ctx.init_charge(f, el, ions)
+    p = ostep.Params(shape, wl.spacing, wl.dt, order, center, wl.psatd_order)
+    osp = oracle_species(el, shape, wl.spacing)
+    rho_static = ostep.deposit_rho([oracle_species(ions, shape, wl.spacing)], p)
+    state = {"E_stag": rounded(wl.E, dtype), "B_stag": rounded(wl.B, dtype),
+             "rho_old": ostep.deposit_rho([osp], p, rho_static)}
+    piclib.pic_step(ctx.ctx, f, [el], nsteps)
+    piclib.pic_sync(ctx.ctx)
+    for n in range(nsteps):
+        if n == nsteps - 1:
+            E_nod, B_nod = ostep.center_fields_s2n(state["E_stag"], state["B_stag"], p)
+        out = ostep.step(state, [osp], p, rho_static)
+    J_stag = ostep.center_current_n2s(out["J_nod"], p)
+    tol = 1e-10 if dtype == "f64" else 2e-4  # the tolerances of the other several-step parity tests
+    for d in range(3):
+        for got, ref in ((f.E_stag, state["E_stag"]), (f.B_stag, state["B_stag"]), (f.E_nod, E_nod),
+                         (f.B_nod, B_nod), (f.J_nod, out["J_nod"]), (f.J_stag, J_stag)):
+            assert max_rel(np64(got[d]), ref[d]) <= tol, d
+    assert max_rel(np64(f.rho_old), state["rho_old"]) <= tol
+    gi, oi = np.argsort(np64(el.w)), np.argsort(osp["w"])
+    tol_p = 1e-11 if dtype == "f64" else 4e-5
+    assert periodic_pos_err(el.positions(shape, wl.spacing)[gi], osp["pos"][oi], p.lengths) <= tol_p
+    assert np.max(np.abs(np.stack([np64(x) for x in el.u], axis=1)[gi] - osp["u"][oi])) <= tol_p
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("shape,ppc", [((16, 8, 16), 5), ((12, 18, 24), 3)])
+def test_several_chunks_per_tile(dtype, shape, ppc):
+    """Cubic tiles of more particles than one dealing chunk (1024 FP32, 512 FP64), whole and ragged tiles:
+    the gather follows the order the deposition published, chunk by chunk."""
+    banner(f"pic_step 4 steps, several chunks per tile dtype={dtype} shape={shape} ppc={ppc}")
+    steps_against_oracle(shape, ppc, 3, 8, dtype, 4)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("shape,order", [((24, 36, 54), 3), ((18, 32, 48), 1)])
+def test_centering_in_the_transforms_of_any_length(dtype, shape, order):
+    """Calls of several steps centre inside the transforms on every grid; here axes with factors of 9."""
+    banner(f"pic_step 3 steps, centering in the transforms dtype={dtype} shape={shape} order={order}")
+    steps_against_oracle(shape, 1, order, 8, dtype, 3)
