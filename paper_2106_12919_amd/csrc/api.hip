@@ -13,9 +13,8 @@
 
 using namespace pic;
 
-// Scratch of pic_deposit_noalloc: the per-call tile sort of each species (the slot of every
-// particle and its inverse, two int32 per particle) for callers that cannot allocate device
-// memory.  A file-scope device array: each GPU the library runs on holds its own copy until the
+// Scratch of pic_deposit_noalloc: the per-call tile sort of each species (at most two int32 per
+// particle) for callers that cannot allocate device memory.  A file-scope device array: each GPU the library runs on holds its own copy until the
 // process ends, and every call on that GPU shares it.  Host code reaches it only through the
 // per-device address hipGetSymbolAddress returns (scratch_address below), never by its name.
 constexpr size_t kNoAllocScratchBytes = size_t(32) << 20;
@@ -153,7 +152,6 @@ struct SpeciesScratch {
   T* off[3] = {nullptr, nullptr, nullptr};
   T* u[3] = {nullptr, nullptr, nullptr};
   T* w = nullptr;
-  int* dst = nullptr;
   int* perm = nullptr;
   // tile groupings of pic_step: counts[ntiles + 1], starts[ntiles + 2] (two, alternating)
   int* counts[2] = {nullptr, nullptr};
@@ -217,7 +215,7 @@ struct Engine : EngineBase {
     if (sps.size() <= s) sps.resize(s + 1);
     SpeciesScratch<T>& x = sps[s];
     if (x.cap >= n) return hipSuccess;
-    void* old[18] = {x.cell, x.off[0], x.off[1], x.off[2], x.u[0], x.u[1], x.u[2], x.w, x.dst, x.perm,
+    void* old[17] = {x.cell, x.off[0], x.off[1], x.off[2], x.u[0], x.u[1], x.u[2], x.w, x.perm,
                      x.counts[0], x.counts[1], x.starts[0], x.starts[1], x.cursor, x.nbr, x.nbr_base, x.deal};
     for (void* q : old)
       if (q) (void)release_one(q);
@@ -227,6 +225,7 @@ struct Engine : EngineBase {
     const size_t nt = (size_t)tiles.ntiles;
     for (int b = 0; b < 2; ++b) {
       if ((e = alloc(&x.counts[b], nt + 1)) != hipSuccess) return e;
+      if ((e = hipMemset(x.counts[b], 0, sizeof(int) * (nt + 1))) != hipSuccess) return e;
       if ((e = alloc(&x.starts[b], nt + 2)) != hipSuccess) return e;
     }
     if ((e = alloc(&x.cursor, nt + 1)) != hipSuccess) return e;
@@ -238,9 +237,9 @@ struct Engine : EngineBase {
       if ((e = alloc(&x.u[d], m)) != hipSuccess) return e;
     }
     if ((e = alloc(&x.w, m)) != hipSuccess) return e;
-    if ((e = alloc(&x.dst, m)) != hipSuccess) return e;
     if ((e = alloc(&x.perm, m)) != hipSuccess) return e;
     if ((e = alloc(&x.deal, m)) != hipSuccess) return e;
+    if ((e = hipStreamSynchronize(nullptr)) != hipSuccess) return e;  // the cleared counts, before any stream's use
     x.cap = n;
     return hipSuccess;
   }
@@ -399,11 +398,13 @@ hipError_t build_engine(const pic_params& p, Engine<T>& e) {
   if ((err = e.alloc(&e.t_starts, (size_t)e.tiles.ntiles + 2)) != hipSuccess) return err;
   if ((err = e.alloc(&e.t_cursor, (size_t)e.tiles.ntiles + 1)) != hipSuccess) return err;
   if ((err = e.alloc(&e.work, 1)) != hipSuccess) return err;
+  if ((err = hipMemset(e.work, 0, sizeof(int))) != hipSuccess) return err;
+  if ((err = hipMemset(e.t_counts, 0, sizeof(int) * ((size_t)e.tiles.ntiles + 1))) != hipSuccess) return err;
   // the row layout of deposit_tiled (B x B x 16 per component) holds the node-major boxes
   // (B^3) of the staggered cycle's deposition too
   const size_t slot = (size_t)deposit_stage_slot(p.shape_order);
   if ((err = e.alloc(&e.stage, (size_t)e.tiles.ntiles * 4 * slot)) != hipSuccess) return err;
-  return hipSuccess;
+  return hipStreamSynchronize(nullptr);  // everything cleared above, before any stream's use
 }
 
 pic_status validate_params(const pic_params* p, std::string& msg) {
@@ -611,6 +612,7 @@ struct SourceSum {
     ra.box_faces = e.box_faces;
     ra.rows = 1;  // deposit_tiled's staging layout
     ra.flag = flag;
+    ra.work = e.work;
     ra.next_flag = e.spill_flag + ((e.dep_k + 1u) & 1u);
     ++e.dep_k;
     rho_done = true;
@@ -663,8 +665,7 @@ pic_status deposit_yee_all(pic_ctx c, const pic_species* sp, int nsp, pic_fields
       continue;
     }
     SpeciesScratch<T>& x = e.sps[s];
-    tile_sort(g, e.tiles, v.cell, v.n, x.counts[0], x.starts[0], x.cursor, x.dst, c->d_bad, c->stream);
-    invert_perm(x.dst, x.perm, v.n, c->stream);
+    tile_sort(g, e.tiles, v.cell, v.n, x.counts[0], x.starts[0], x.cursor, x.perm, c->d_bad, c->stream);
     deposit_yee_tiled<T>(g, e.tiles, v, x.perm, x.starts[0], wj, e.stage, static_cast<T*>(f->rho_new), J, c->stream);
   }
   return PIC_OK;
@@ -687,17 +688,15 @@ pic_status do_deposit(pic_ctx c, const pic_species* sp, int nsp, pic_fields* f, 
   const GridGeom g = geom(c->p);
   for (int s = 0; s < nsp; ++s) {
     if (sp[s].n == 0) continue;
-    int *dst = sort_idx, *perm = sort_idx ? sort_idx + sp[s].n : nullptr;
+    int* perm = sort_idx;
     if (!sort_idx) {
       hipError_t he = e.ensure_species((size_t)s, sp[s].n);
       if (he != hipSuccess) return c->fail(PIC_ENOMEM, std::string("pic_deposit: ") + hipGetErrorString(he));
-      dst = e.sps[s].dst;
       perm = e.sps[s].perm;
     }
     const SpeciesView<T> v = view<T>(sp[s]);
     // visit the caller's particles in tile order through a permutation (caller order untouched)
-    tile_sort(g, e.tiles, v.cell, v.n, e.t_counts, e.t_starts, e.t_cursor, dst, c->d_bad, c->stream);
-    invert_perm(dst, perm, v.n, c->stream);
+    tile_sort(g, e.tiles, v.cell, v.n, e.t_counts, e.t_starts, e.t_cursor, perm, c->d_bad, c->stream);
     const bool mobile = std::isfinite(sp[s].m);
     int* flag = sum.begin();
     deposit_tiled<T>(g, e.tiles, v, perm, e.t_starts, with_j && mobile, e.stage, c->d_bad, nullptr, nullptr, e.work,
@@ -738,8 +737,7 @@ pic_status do_gather_push(pic_ctx c, const pic_fields* f, pic_species* sp, int n
       SpeciesScratch<T>& x = e.sps[s];
       const SpeciesView<T> v = view<T>(sp[s]);
       // tile order through a permutation; every particle is updated in place
-      tile_sort(g, e.tiles, v.cell, v.n, e.t_counts, e.t_starts, e.t_cursor, x.dst, c->d_bad, c->stream);
-      invert_perm(x.dst, x.perm, v.n, c->stream);
+      tile_sort(g, e.tiles, v.cell, v.n, e.t_counts, e.t_starts, e.t_cursor, x.perm, c->d_bad, c->stream);
       gather_push_tiled<T>(g, e.tiles, E, B, v, v, x.perm, e.t_starts, false, nullptr, nullptr, c->stream);
     }
   return c->check("pic_gather_push");
@@ -760,25 +758,27 @@ SpeciesView<T> scratch_view(const SpeciesScratch<T>& x, const pic_species& like)
 template <typename T>
 void copy_species(const SpeciesView<T>& from, const SpeciesView<T>& to, hipStream_t st) {
   const size_t n = (size_t)from.n;
-  (void)hipMemcpyAsync(to.cell, from.cell, n * sizeof(int32_t), hipMemcpyDeviceToDevice, st);
+  CopyList c;
+  c.add(to.cell, from.cell, n * sizeof(int32_t));
   for (int d = 0; d < 3; ++d) {
-    (void)hipMemcpyAsync(to.off[d], from.off[d], n * sizeof(T), hipMemcpyDeviceToDevice, st);
-    (void)hipMemcpyAsync(to.u[d], from.u[d], n * sizeof(T), hipMemcpyDeviceToDevice, st);
+    c.add(to.off[d], from.off[d], n * sizeof(T));
+    c.add(to.u[d], from.u[d], n * sizeof(T));
   }
-  if (from.w) (void)hipMemcpyAsync(to.w, from.w, n * sizeof(T), hipMemcpyDeviceToDevice, st);
+  if (from.w) c.add(to.w, from.w, n * sizeof(T));
+  copy_arrays(c, st);
 }
 
 // forward transforms of the state (E, B) and/or sources (J, rho_old, rho_new)
 template <typename T>
 void forward_batch(pic_ctx c, Engine<T>& e, const T* const* src, cplx<T>* const* dst, int count,
-                   const LineCenter<T>* lc = nullptr) {
+                   const LineCenter<T>* lc = nullptr, bool x_pass = true) {
   Batch<const T*> in{};
   Batch<cplx<T>*> out{};
   for (int i = 0; i < count; ++i) {
     in.p[i] = src[i];
     out.p[i] = dst[i];
   }
-  e.fft.forward(in, out, count, c->stream, lc);
+  e.fft.forward(in, out, count, c->stream, lc, x_pass);
 }
 
 // The centering of the real-space cycle as LineCenter of the transforms: J nodes -> Yee (J^d
@@ -797,15 +797,54 @@ LineCenter<T> transform_centering(pic_ctx c, bool to_nodes) {
   return lc;
 }
 
+// The x pass of the sources' transforms, the update and the inverse x pass in one kernel: the standard
+// update (staggered or nodal) of axes up to 768 points.  The options with other tables or more outputs keep
+// the separate passes.
+template <typename T>
+bool solves_along_x(pic_ctx c, const Engine<T>& e) {
+  return e.fft.can_solve_x() && !e.tab.G[0] && !e.tab.Av[0] && !e.tab.cc &&
+         !(c->p.flags & PIC_SPECTRAL_CENTERING);
+}
+
+// That kernel, into the scratch spectra; step: pic_step's resident spectra, else psatd_push_fields' eleven.
+template <typename T>
+void solve_along_x(pic_ctx c, Engine<T>& e, int rho_old_slot, bool step, const LineCenter<T>* j_center,
+                   const LineCenter<T>* eb_center) {
+  SolveX<T> a{};
+  for (int d = 0; d < 3; ++d) {
+    a.src[d] = a.state[d] = e.Eh[d];
+    a.src[3 + d] = a.state[3 + d] = e.Bh[d];
+    a.src[6 + d] = e.Jh[d];
+    a.Dp[d] = e.tab.Dp[d];
+    a.Dm[d] = e.tab.Dm[d];
+  }
+  a.src[9] = a.rho_out = e.rh[1 - rho_old_slot];
+  a.src[10] = e.rh[rho_old_slot];
+  for (int i = 0; i < 6; ++i) a.out[i] = e.scratch[i];
+  a.C = e.tab.C;
+  a.Sw = e.tab.Sw;
+  a.X1 = e.tab.X1;
+  a.X2 = e.tab.X2;
+  a.X3 = e.tab.X3;
+  a.ny = c->p.ny;
+  a.nzh = e.fft.nzh;
+  a.pz = e.fft.pz;
+  e.fft.solve_x(a, step, j_center, eb_center, c->stream);
+}
+
 // The per-mode update, then the inverse transforms: of the staggered state into E_stag,
 // B_stag, or (spectral centering) of the nodal spectra the update also wrote, in place in
 // the scratch spectra, into E_nod, B_nod.
 template <typename T>
 void update_and_inverse(pic_ctx c, Engine<T>& e, pic_fields* f, int rho_old_slot, bool spectral = false,
-                        bool state_out = true, const LineCenter<T>* to_nodes = nullptr) {
+                        bool state_out = true, const LineCenter<T>* to_nodes = nullptr, int along_x = 0,
+                        const LineCenter<T>* j_center = nullptr) {
   const pic_params& p = c->p;
   const bool avg = averaged(p);
-  {
+  if (along_x) {  // (1: pic_step, 2: psatd_push_fields)
+    StageScope sc(c, ST_UPDATE);
+    solve_along_x<T>(c, e, rho_old_slot, along_x == 1, j_center, to_nodes);
+  } else {
     StageScope sc(c, ST_UPDATE);
     psatd_update<T>(e.tab, e.Eh, e.Bh, e.Jh, e.rh[rho_old_slot], e.rh[1 - rho_old_slot], p.nx, p.ny, e.fft.nzh,
                     e.fft.pz, spectral ? e.scratch : (avg ? e.Ah : nullptr), c->stream);
@@ -836,7 +875,7 @@ void update_and_inverse(pic_ctx c, Engine<T>& e, pic_fields* f, int rho_old_slot
     out.p[3 + d] = static_cast<T*>(nod ? f->B_nod[d] : f->B_stag[d]);
   }
   for (int i = 0; i < 6; ++i) scr.p[i] = e.scratch[i];
-  e.fft.inverse(in, scr, out, 6, 1.0 / (double)ncells(p), c->stream, to_nodes);
+  e.fft.inverse(in, scr, out, 6, 1.0 / (double)ncells(p), c->stream, to_nodes, !along_x);
 }
 
 // The staggered state E_stag, B_stag from the resident spectra (end of a spectral-
@@ -860,6 +899,7 @@ void state_inverse(pic_ctx c, Engine<T>& e, pic_fields* f) {
 template <typename T>
 pic_status do_push_fields(pic_ctx c, pic_fields* f) {
   Engine<T>& e = static_cast<Engine<T>&>(*c->eng);
+  const bool along_x = solves_along_x(c, e);
   {
     StageScope sc(c, ST_FFT_FWD);
     const T* src[11];
@@ -876,9 +916,9 @@ pic_status do_push_fields(pic_ctx c, pic_fields* f) {
     dst[9] = e.rh[0];
     src[10] = static_cast<const T*>(f->rho_new);
     dst[10] = e.rh[1];
-    forward_batch<T>(c, e, src, dst, 11);
+    forward_batch<T>(c, e, src, dst, 11, nullptr, !along_x);
   }
-  update_and_inverse<T>(c, e, f, 0);
+  update_and_inverse<T>(c, e, f, 0, false, true, nullptr, along_x ? 2 : 0);
   return c->check("psatd_push_fields");
 }
 
@@ -966,6 +1006,7 @@ pic_status do_step_yee(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int n
     if (he != hipSuccess) return c->fail(PIC_ENOMEM, std::string("pic_step: ") + hipGetErrorString(he));
   }
   const size_t N = ncells(p);
+  const bool along_x = solves_along_x(c, e);
   for (int n = 0; n < nsteps; ++n) {
     {
       StageScope sc(c, ST_CLEAR);
@@ -982,8 +1023,7 @@ pic_status do_step_yee(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int n
       const SpeciesView<T> v = view<T>(sp[q]);
       {
         StageScope sc(c, ST_SORT);  // one grouping (cells at n) serves the gather and the deposition
-        tile_sort(g, e.tiles, v.cell, v.n, x.counts[0], x.starts[0], x.cursor, x.dst, c->d_bad, c->stream);
-        invert_perm(x.dst, x.perm, v.n, c->stream);
+        tile_sort(g, e.tiles, v.cell, v.n, x.counts[0], x.starts[0], x.cursor, x.perm, c->d_bad, c->stream);
       }
       {
         StageScope sc(c, ST_PUSH);
@@ -1000,9 +1040,9 @@ pic_status do_step_yee(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int n
       const T* src[4] = {static_cast<const T*>(f->J_stag[0]), static_cast<const T*>(f->J_stag[1]),
                          static_cast<const T*>(f->J_stag[2]), static_cast<const T*>(f->rho_new)};
       cplx<T>* dst[4] = {e.Jh[0], e.Jh[1], e.Jh[2], e.rh[1 - slot]};
-      forward_batch<T>(c, e, src, dst, 4);
+      forward_batch<T>(c, e, src, dst, 4, nullptr, !along_x);
     }
-    update_and_inverse<T>(c, e, f, slot);
+    update_and_inverse<T>(c, e, f, slot, false, true, nullptr, along_x ? 1 : 0);
     slot = 1 - slot;
     if ((st = c->check("pic_step")) != PIC_OK) return st;
   }
@@ -1059,6 +1099,7 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
   const bool fused = !spectral && !nodal && !avg;
   const LineCenter<T> lc_j = fused ? transform_centering<T>(c, false) : LineCenter<T>();
   const LineCenter<T> lc_eb = fused ? transform_centering<T>(c, true) : LineCenter<T>();
+  const bool along_x = solves_along_x(c, e);
   for (int n = 0; n < nsteps; ++n) {
     const bool mid = fused && n + 1 < nsteps;  // this step's transforms centre
     const bool nod_ready = fused && n > 0;     // E_nod, B_nod from the previous step's inverse
@@ -1082,8 +1123,7 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
         const bool mobile = std::isfinite(sp[q].m);
         {
           StageScope sc(c, ST_SORT);
-          tile_sort(g, e.tiles, v.cell, v.n, x.counts[0], x.starts[0], x.cursor, x.dst, c->d_bad, c->stream);
-          invert_perm(x.dst, x.perm, v.n, c->stream);
+          tile_sort(g, e.tiles, v.cell, v.n, x.counts[0], x.starts[0], x.cursor, x.perm, c->d_bad, c->stream);
         }
         if (mobile) {
           StageScope sc(c, ST_PUSH);
@@ -1105,7 +1145,6 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
       const SpeciesView<T> cur = in_scratch[q] ? scratch_view<T>(x, sp[q]) : view<T>(sp[q]);
       const SpeciesView<T> alt = in_scratch[q] ? view<T>(sp[q]) : scratch_view<T>(x, sp[q]);
       const bool mobile = std::isfinite(sp[q].m);
-      const size_t nt = (size_t)e.tiles.ntiles;
       // Grouping: on the first step a full counting sort of the caller's order; afterwards
       // the deposition of the previous step has counted the tiles of the current cells.
       const int L = layout[q];
@@ -1113,13 +1152,11 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
       {
         StageScope sc(c, ST_SORT);
         if (first) {
-          tile_sort(g, e.tiles, cur.cell, cur.n, x.counts[0], x.starts[0], x.cursor, x.dst, c->d_bad, c->stream);
-          invert_perm(x.dst, x.perm, cur.n, c->stream);
+          tile_sort(g, e.tiles, cur.cell, cur.n, x.counts[0], x.starts[0], x.cursor, x.perm, c->d_bad, c->stream);
         } else if (mobile) {
           scan_counts(e.tiles, x.counts[1 - L], x.starts[1 - L], x.cursor, c->stream);
           neighbour_bases(e.tiles, x.starts[L], x.nbr, x.starts[1 - L], x.nbr_base, x.cursor, c->stream);
         }
-        if (mobile) (void)hipMemsetAsync(x.counts[first ? 1 : L], 0, sizeof(int) * (nt + 1), c->stream);
       }
       const int* dep_starts = first ? x.starts[0] : (mobile ? x.starts[1 - L] : x.starts[L]);
       {
@@ -1128,7 +1165,7 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
           gather_push_tiled<T>(g, e.tiles, Enod, Bnod, cur, alt, x.perm, x.starts[0], true, nullptr, nullptr,
                                c->stream);
         else if (first)
-          permute_species<T>(cur, alt, x.dst, c->stream);
+          permute_species<T>(cur, alt, x.perm, c->stream);
         else if (mobile)
           gather_push_tiled<T>(g, e.tiles, Enod, Bnod, cur, alt, nullptr, x.starts[L], true, x.cursor, x.nbr_base,
                                c->stream, x.deal);
@@ -1136,10 +1173,12 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
       const SpeciesView<T> dep = (first || mobile) ? alt : cur;  // immobile species stay put after the first step
       {
         StageScope sc(c, ST_DEPOSIT);
-        int* nextc = mobile ? x.counts[first ? 1 : L] : nullptr;
+        // the next step's grouping (its counts are zero: every scan leaves them so, and the call's
+        // last step counts nothing)
+        int* nextc = mobile && n + 1 < nsteps ? x.counts[first ? 1 : L] : nullptr;
         deposit_tiled<T>(g, e.tiles, dep, nullptr, dep_starts, mobile, e.stage, c->d_bad, nextc,
-                         mobile ? x.nbr : nullptr, e.work, sum.spill_rho(), sum.spill_j(), c->stream, sum.begin(),
-                         e.box_faces, mobile ? x.deal : nullptr);
+                         nextc ? x.nbr : nullptr, e.work, sum.spill_rho(), sum.spill_j(), c->stream, sum.begin(),
+                         e.box_faces, nextc ? x.deal : nullptr);
       }
       {
         StageScope sc(c, ST_REDUCE);
@@ -1166,9 +1205,10 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
       const T* src[4] = {static_cast<const T*>(J[0]), static_cast<const T*>(J[1]), static_cast<const T*>(J[2]),
                          static_cast<const T*>(f->rho_new)};
       cplx<T>* dst[4] = {e.Jh[0], e.Jh[1], e.Jh[2], e.rh[1 - slot]};
-      forward_batch<T>(c, e, src, dst, 4, mid ? &lc_j : nullptr);
+      forward_batch<T>(c, e, src, dst, 4, mid ? &lc_j : nullptr, !along_x);
     }
-    update_and_inverse<T>(c, e, f, slot, spectral, !avg, mid ? &lc_eb : nullptr);
+    update_and_inverse<T>(c, e, f, slot, spectral, !avg, mid ? &lc_eb : nullptr, along_x ? 1 : 0,
+                          mid ? &lc_j : nullptr);
     slot = 1 - slot;
     if ((st = c->check("pic_step")) != PIC_OK) return st;
   }
@@ -1248,8 +1288,7 @@ pic_status do_step_adjoint(pic_ctx c, pic_fields* f, const pic_species* sp, int 
     const SpeciesView<T> v = view<T>(sp[q]);
     {
       StageScope sc(c, ST_SORT);
-      tile_sort(g, e.tiles, v.cell, v.n, x.counts[0], x.starts[0], x.cursor, x.dst, c->d_bad, c->stream);
-      invert_perm(x.dst, x.perm, v.n, c->stream);
+      tile_sort(g, e.tiles, v.cell, v.n, x.counts[0], x.starts[0], x.cursor, x.perm, c->d_bad, c->stream);
     }
     Batch<T*> lam{}, lamF{};
     for (int d = 0; d < 3; ++d) {

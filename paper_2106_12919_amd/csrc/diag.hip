@@ -1,5 +1,7 @@
 // Grid reductions accumulated in FP64 (field energy of Sec. 2 item iii, total
 // charge, the Gauss's-law and continuity residuals of the spectra) and element-wise helpers.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace pic {
@@ -97,6 +99,17 @@ __global__ void __launch_bounds__(256) k_zero_arrays(Batch<T*> arrs, long long n
     d[i] = (T)0;
 }
 
+__global__ void __launch_bounds__(256) k_copy_arrays(CopyList c) {
+  const int a = blockIdx.y;
+  const size_t n16 = c.bytes[a] / 16, step = (size_t)gridDim.x * blockDim.x;
+  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int4* __restrict__ s = static_cast<const int4*>(c.src[a]);
+  int4* __restrict__ d = static_cast<int4*>(c.dst[a]);
+  for (size_t i = t; i < n16; i += step) d[i] = s[i];
+  const size_t words = c.bytes[a] / 4;  // the words past the last 16 bytes
+  if (t < words - 4 * n16) reinterpret_cast<int*>(d)[4 * n16 + t] = reinterpret_cast<const int*>(s)[4 * n16 + t];
+}
+
 }  // namespace
 
 template <typename T>
@@ -117,6 +130,14 @@ void div_residual(const PsatdTables<T>& t, const cplx<T>* const V[3], const cplx
   hipLaunchKernelGGL((k_div_residual<T>), dim3(1024), dim3(256), 0, s, S, t.Dm[0], t.Dm[1], t.Dm[2], ca, cb, nx, ny,
                      nzh, pz, nz, acc);
 }
+void copy_arrays(const CopyList& c, hipStream_t s) {
+  if (c.count == 0) return;
+  size_t most = 0;
+  for (int i = 0; i < c.count; ++i) most = std::max(most, c.bytes[i]);
+  const unsigned blocks = (unsigned)std::min<size_t>((most / 16 + 255) / 256 + 1, 4096);
+  hipLaunchKernelGGL(k_copy_arrays, dim3(blocks, c.count), dim3(256), 0, s, c);
+}
+
 template <typename T>
 void zero_arrays(const Batch<T*>& arrs, int count, int64_t n, hipStream_t s) {
   if (count <= 0 || n <= 0) return;

@@ -167,14 +167,13 @@ int deposit_box(int shape_order);
 // nodes z = 4g .. 4g+3 at positions 4h .. 4h+3 of every box that covers them, so that the
 // reduction reads four nodes of a box as one aligned vector.
 int deposit_stage_slot(int shape_order);
-// Counting sort by tile of the particles' current cells: counts[ntiles+1],
-// starts[ntiles+2], cursor[ntiles+1] (scratch), dst[n] = each particle's slot in
+// Counting sort by tile of the particles' current cells: counts[ntiles+1] (zero on entry and again on
+// return), starts[ntiles+2], cursor[ntiles+1] (scratch), perm[n] = the particle of each slot in
 // tile order (tiles in order, then particles with invalid cells, counted in *bad).
 void tile_sort(const GridGeom& g, const TileGeom& t, const int32_t* cell, int64_t n, int* counts, int* starts,
-               int* cursor, int* dst, int* bad, hipStream_t s);
-void invert_perm(const int* dst, int* perm, int64_t n, hipStream_t s);
-// Exclusive scan of counts[ntiles + 1] into starts[ntiles + 2] and cursor[ntiles + 1].
-void scan_counts(const TileGeom& t, const int* counts, int* starts, int* cursor, hipStream_t s);
+               int* cursor, int* perm, int* bad, hipStream_t s);
+// Exclusive scan of counts[ntiles + 1] into starts[ntiles + 2] and cursor[ntiles + 1]; leaves the counts zero.
+void scan_counts(const TileGeom& t, int* counts, int* starts, int* cursor, hipStream_t s);
 // Slot runs of the regrouping: from the per-(source tile, neighbour) counts a deposition
 // published (nbr_counts, source grouping old_starts) and the new grouping's starts,
 // bases[27 S + nb] = first slot of source S's particles bound for neighbour nb, and
@@ -198,7 +197,7 @@ void gather_push_tiled(const GridGeom& g, const TileGeom& t, const T* const E[3]
                        bool write_sorted, int* home_cursor, const int* nbr_bases, hipStream_t s,
                        const unsigned short* deal = nullptr);
 template <typename T>
-void permute_species(const SpeciesView<T>& in, const SpeciesView<T>& out, const int* dst, hipStream_t s);
+void permute_species(const SpeciesView<T>& in, const SpeciesView<T>& out, const int* perm, hipStream_t s);
 // Deposition of one species in two launches.  deposit_tiled accumulates rho (at the
 // particles' positions) and, when with_j, J (at x - dt v/2) tile by tile (tile t owns
 // sorted slots [starts[t], starts[t+1]); slot q holds particle perm[q], perm == nullptr:
@@ -209,7 +208,8 @@ void permute_species(const SpeciesView<T>& in, const SpeciesView<T>& out, const 
 // (the grouping of the next step), into next_counts[ntiles + 1] (invalid cells last),
 // and, when nbr_counts != nullptr, per tile t of this grouping and neighbour nb of t
 // (0..26, the tile offsets in {-1,0,1}^3 in x-major order) into nbr_counts[27 t + nb].
-// ``work`` is one int of device scratch (the tile counter of the persistent launch).
+// ``work`` is one int of device scratch (the tile counter of the persistent launch), zero on entry;
+// deposit_reduce zeroes it again (ReduceArgs::work).
 // ``spill_flag`` (optional) is set to 1 whenever a particle goes to rho/J directly.  With
 // ``box_faces`` (ntiles ints, optional; used on grids of whole tiles) each tile stages only
 // the layers of its box that hold a nonzero value and records which outer faces it staged,
@@ -232,10 +232,15 @@ struct ReduceArgs {
   T* spill[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   const int* flag = nullptr;
   int* next_flag = nullptr;
+  int* work = nullptr;  // the deposition's tile counter, zeroed for the next one (optional)
   const int* box_faces = nullptr;  // per tile, the outer faces its deposition staged (null: all)
   // Staging layout: 0 = node-major boxes (B^3 per component); 1 = the zero-padded rows that
   // deposit_tiled writes (deposit_stage_slot elements per component).
   int rows = 0;
+  __device__ void reset() const {  // by one thread of the launch
+    if (next_flag) *next_flag = 0;
+    if (work) *work = 0;
+  }
   __device__ T start(int q, const T* o, size_t idx) const {
     if (acc_mask & (q == 0 ? 1 : 2)) return o[idx];
     return (q == 0 && base) ? base[idx] : (T)0;
@@ -295,6 +300,19 @@ template <typename T>
 void sum_plain(const T* arr, int64_t n, double* acc, hipStream_t s);
 template <typename T>
 void add_into(T* dst, const T* src, int64_t n, hipStream_t s);
+// Copies of up to kMaxBatch arrays (16-byte aligned, sizes multiples of 4 bytes) in one launch.
+struct CopyList {
+  const void* src[kMaxBatch];
+  void* dst[kMaxBatch];
+  size_t bytes[kMaxBatch];
+  int count = 0;
+  void add(void* d, const void* s, size_t n) {
+    src[count] = s;
+    dst[count] = d;
+    bytes[count++] = n;
+  }
+};
+void copy_arrays(const CopyList& c, hipStream_t s);
 // Zeroes count (<= 8) arrays of n elements in one launch.
 template <typename T>
 void zero_arrays(const Batch<T*>& arrs, int count, int64_t n, hipStream_t s);

@@ -756,16 +756,9 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_home(G
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256) k_permute(SpeciesView<T> in, SpeciesView<T> out, const int* __restrict__ dst) {
-  const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= in.n) return;
-  const long long q = dst[p];
-  out.cell[q] = in.cell[p];
-  for (int d = 0; d < 3; ++d) {
-    out.off[d][q] = in.off[d][p];
-    out.u[d][q] = in.u[d][p];
-  }
-  if (in.w) out.w[q] = in.w[p];
+__global__ void __launch_bounds__(256) k_permute(SpeciesView<T> in, SpeciesView<T> out, const int* __restrict__ perm) {
+  const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q < in.n) copy_particle(in, perm[q], out, q);
 }
 
 template <typename T>
@@ -1426,7 +1419,7 @@ __global__ void __launch_bounds__(256) k_deposit_reduce_whole(GridGeom g, TileGe
   using X = Box<Shape<T, ORDER>::NW>;
   // per candidate tile of the row, by tz: 0 if empty, else 1 + 2 x its face mask
   __shared__ unsigned char occ[4][kMaxTilesZ];
-  if (ra.next_flag && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) *ra.next_flag = 0;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) ra.reset();
   // grid (z blocks, ny, nx) flattened and renumbered XCD-major: rows next to each other
   // read the same staging lines
   const int nzb = gridDim.x;
@@ -1504,7 +1497,7 @@ __global__ void __launch_bounds__(256) k_deposit_reduce_rows(GridGeom g, TileGeo
   using RL = StageRows<ORDER>;
   static_assert(kTile == 8, "two groups of four nodes per tile along z");
   __shared__ unsigned char occ[4][kMaxTilesZ];
-  if (ra.next_flag && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) *ra.next_flag = 0;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) ra.reset();
   const int nzb = gridDim.x;
   const int L = xcd_major(blockIdx.x + nzb * (blockIdx.y + gridDim.y * blockIdx.z), nzb * gridDim.y * gridDim.z);
   const int z0 = 4 * ((L % nzb) * blockDim.x + threadIdx.x);
@@ -1587,7 +1580,7 @@ __global__ void __launch_bounds__(256) k_deposit_reduce(GridGeom g, TileGeom tg,
                                                         ReduceArgs<T> ra) {
   using S = Shape<T, ORDER>;
   using X = Box<S::NW>;
-  if (ra.next_flag && blockIdx.x == 0 && threadIdx.x == 0) *ra.next_flag = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) ra.reset();
   const bool spilled = ra.flag && *ra.flag;
   const long long N = (long long)g.nx * g.ny * g.nz;
   for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < N;
@@ -2423,9 +2416,9 @@ __global__ void __launch_bounds__(256) k_deposit_yee_tiled(GridGeom g, TileGeom 
 }  // namespace
 
 template <typename T>
-void permute_species(const SpeciesView<T>& in, const SpeciesView<T>& out, const int* dst, hipStream_t s) {
+void permute_species(const SpeciesView<T>& in, const SpeciesView<T>& out, const int* perm, hipStream_t s) {
   if (in.n <= 0) return;
-  hipLaunchKernelGGL((k_permute<T>), dim3((unsigned)((in.n + 255) / 256)), dim3(256), 0, s, in, out, dst);
+  hipLaunchKernelGGL((k_permute<T>), dim3((unsigned)((in.n + 255) / 256)), dim3(256), 0, s, in, out, perm);
 }
 
 // Raises a kernel's dynamic-LDS limit above the 64 KiB default when a launch needs it
@@ -2507,7 +2500,6 @@ void launch_deposit(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& 
     static int resident = 0;  // per instantiation; the device's occupancy does not change
     if (resident == 0) resident = resident_blocks(k, PIC_DEPOSIT_BLOCK, lds);
     nb = std::min(nb, resident);
-    (void)hipMemsetAsync(work, 0, sizeof(int), s);
   }
   hipLaunchKernelGGL((k_deposit_tiled<T, ORDER, WJ>), dim3(nb), dim3(PIC_DEPOSIT_BLOCK), lds, s, g, t, sp, perm,
                      starts, out, stage, qdv, hx, hy, hz, bad, next_counts, nbr_counts, work, spill_flag, box_faces,

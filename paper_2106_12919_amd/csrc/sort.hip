@@ -4,10 +4,7 @@
 // with an out-of-range cell index go to one extra bucket after the last tile so
 // the sorted order has no holes (they are counted and never deposited).  Three
 // launches: count per tile, exclusive scan of the counts, rank (each particle's
-// slot in tile order).  Particles that share a tile within a wavefront are
-// combined before touching the tile counter, so a wave issues one atomic per
-// distinct tile: with particles already grouped by tile (the previous step's
-// order) that is one or two atomics per wave instead of 64.
+// slot in tile order, kept as the permutation slot -> particle).
 #include "kernels.h"
 
 namespace pic {
@@ -25,145 +22,162 @@ __device__ inline int tile_key(int c, const GridGeom& g, const TileGeom& t) {
   return ((i / kTile) * t.nty + j / kTile) * t.ntz + k / kTile;
 }
 
-// Adds one per valid lane to counters[key]; returns each lane's previous-value
-// slot (counter value before the lane's increment, lanes of one key in lane order).
-// The lanes are first grouped by key (ballots only); then the first lane of every group
-// issues the group's atomic, all groups' atomics in the same instruction, so a wave waits
-// for one atomic round trip however many distinct keys it holds.
-__device__ inline int wave_aggregated_add(int* counters, int key, bool valid) {
+// A workgroup counts its BLOCK * kSortPer particles per tile in an LDS table and touches each global
+// counter once per tile it holds.  Up to kSortBuckets buckets (128 KiB of LDS) the table is indexed by
+// the tile; beyond, by a hash with linear probing (HASH): particles are nearly grouped by tile (the
+// previous call's order), so a workgroup holds few distinct tiles.  A key that finds no place in the
+// table goes to the global counter by itself.  32769 buckets, 134 M particles of the 256^3 thermal
+// plasma: count and rank 334 + 453 us, against 701 + 1325 (and 308 to invert the slots) with one global
+// atomic per wave and tile.  At 1025 and 6157 buckets the hash was slower than the indexed table (33 against
+// 26 us for 2.1 M grouped particles, 407 against 341 for 9 M scattered ones).
+constexpr int kSortPer = 8;
+constexpr int kSortBuckets = 32768;
+constexpr int kSortTable = 1024;  // entries of the hashed table
+constexpr int kSortProbes = 16;
+
+template <bool HASH>
+__device__ inline int table_place(volatile int* keys, int key) {
+  if (!HASH) return key;
+  const unsigned h = ((unsigned)key * 2654435761u) >> 22;  // 10 bits: kSortTable entries
+  for (int p = 0; p < kSortProbes; ++p) {
+    const int e = (int)((h + p) & (kSortTable - 1));
+    int k = keys[e];
+    if (k < 0) k = atomicCAS(const_cast<int*>(keys) + e, -1, key);
+    if (k < 0 || k == key) return e;
+  }
+  return -1;
+}
+
+// Adds one per valid lane to the table entry of its key (global[key] when the table has no place):
+// place = the entry or -1, returns the lane's rank in it (the global slot when place < 0; ranks only
+// when RANK).  The first few distinct keys of a wave are added by one lane each for all lanes of the
+// key (grouped particles: one or two keys per wave); lanes left after that (scattered particles) add
+// for themselves.
+template <bool HASH, bool RANK>
+__device__ inline int table_add(int* keys, int* cnt, int* global, int key, bool valid, int& place) {
+  constexpr int kGrouped = 3;
   unsigned long long active = __ballot(valid);
   const int lane = __lane_id();
-  int leader_of = lane, rank = 0, group = 0;
-  while (active) {
+  int leader_of = lane, rank = 0, group = valid ? 1 : 0;
+  for (int q = 0; q < kGrouped && active; ++q) {
     const int leader = __ffsll((unsigned long long)active) - 1;
     const int lkey = __shfl(key, leader);
     const unsigned long long same = __ballot(valid && key == lkey) & active;
     if ((same >> lane) & 1ull) {
       leader_of = leader;
       rank = __popcll(same & ((1ull << lane) - 1ull));
+      group = lane == leader ? __popcll(same) : 0;
     }
-    if (lane == leader) group = __popcll(same);
     active &= ~same;
   }
   int base = 0;
-  if (valid && lane == leader_of) base = atomicAdd(&counters[key], group);
+  place = -1;
+  if (group > 0) {
+    place = table_place<HASH>(keys, key);
+    base = atomicAdd(place >= 0 ? &cnt[place] : &global[key], group);
+  }
+  if (!RANK) return 0;
   base = __shfl(base, leader_of);
-  return valid ? base + rank : -1;
+  place = __shfl(place, leader_of);
+  return base + rank;
 }
 
-// The same count without the slots: the atomics' results are not waited for.
-__device__ inline void wave_aggregated_count(int* counters, int key, bool valid) {
-  unsigned long long active = __ballot(valid);
-  const int lane = __lane_id();
-  int group = 0;
-  while (active) {
-    const int leader = __ffsll((unsigned long long)active) - 1;
-    const int lkey = __shfl(key, leader);
-    const unsigned long long same = __ballot(valid && key == lkey) & active;
-    if (lane == leader) group = __popcll(same);
-    active &= ~same;
+template <bool HASH, int BLOCK>
+__device__ inline void table_clear(int* keys, int* cnt, int nbk) {
+  for (int e = threadIdx.x; e < (HASH ? kSortTable : nbk); e += BLOCK) {
+    cnt[e] = 0;
+    if (HASH) keys[e] = -1;
   }
-  if (group > 0) atomicAdd(&counters[key], group);
-}
-
-__global__ void __launch_bounds__(256) k_tile_count(GridGeom g, TileGeom t, const int32_t* __restrict__ cell, long long n,
-                                                    int* counts) {
-  const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int key = (p < n) ? tile_key(cell[p], g, t) : 0;
-  wave_aggregated_count(counts, key, p < n);
-}
-
-__global__ void __launch_bounds__(256) k_tile_rank(GridGeom g, TileGeom t, const int32_t* __restrict__ cell, long long n,
-                                                   int* cursor, int* dst, int* bad) {
-  const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int key = (p < n) ? tile_key(cell[p], g, t) : 0;
-  const int slot = wave_aggregated_add(cursor, key, p < n);
-  if (p < n) {
-    if (key == t.ntiles && bad) atomicAdd(bad, 1);
-    dst[p] = slot;
-  }
-}
-
-// The same two passes with a per-workgroup histogram in LDS (grids of at most
-// kSortMaxBuckets - 1 tiles): each workgroup counts its kSortBlock * kSortPer particles
-// per tile in LDS and touches each global counter once per tile it holds, so a counter
-// sees a few atomics per step instead of one per wave (atomics on one address serialise).
-// For the ranks, a workgroup reserves one run per tile on ``cursor`` and places its
-// particles in the run by their LDS ranks.
-constexpr int kSortBlock = 1024, kSortPer = 8;
-constexpr int kSortMaxBuckets = 32768;  // 128 KiB of LDS counters
-
-__global__ void __launch_bounds__(kSortBlock) k_tile_count_lds(GridGeom g, TileGeom t, const int32_t* __restrict__ cell,
-                                                               long long n, int* counts) {
-  extern __shared__ int hist[];
-  const int nbk = t.ntiles + 1;
-  for (int e = threadIdx.x; e < nbk; e += blockDim.x) hist[e] = 0;
   __syncthreads();
-  const long long p0 = (long long)blockIdx.x * kSortBlock * kSortPer + threadIdx.x;
+}
+
+// Dynamic LDS of both: the counts (the table's entries, or one per bucket), then with HASH the keys.
+template <bool HASH, int BLOCK>
+__global__ void __launch_bounds__(BLOCK) k_tile_count(GridGeom g, TileGeom t, const int32_t* __restrict__ cell,
+                                                           long long n, int* counts) {
+  extern __shared__ int cnt[];
+  int* const keys = cnt + kSortTable;
+  const int nbk = t.ntiles + 1;
+  table_clear<HASH, BLOCK>(keys, cnt, nbk);
+  const long long p0 = (long long)blockIdx.x * BLOCK * kSortPer + threadIdx.x;
 #pragma unroll
   for (int u = 0; u < kSortPer; ++u) {
-    const long long p = p0 + (long long)u * kSortBlock;
+    const long long p = p0 + (long long)u * BLOCK;
     const int key = (p < n) ? tile_key(cell[p], g, t) : 0;
-    wave_aggregated_count(hist, key, p < n);
+    int place;
+    (void)table_add<HASH, false>(keys, cnt, counts, key, p < n, place);
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < nbk; e += blockDim.x) {
-    const int c = hist[e];
-    if (c) atomicAdd(&counts[e], c);
+  for (int e = threadIdx.x; e < (HASH ? kSortTable : nbk); e += BLOCK) {
+    const int c = cnt[e];
+    if (c) atomicAdd(&counts[HASH ? keys[e] : e], c);
   }
 }
 
-__global__ void __launch_bounds__(kSortBlock) k_tile_rank_lds(GridGeom g, TileGeom t, const int32_t* __restrict__ cell,
-                                                              long long n, int* cursor, int* dst, int* bad) {
-  extern __shared__ int hist[];
+// Each workgroup reserves one run per tile on ``cursor`` and places its particles in it by rank.
+template <bool HASH, int BLOCK>
+__global__ void __launch_bounds__(BLOCK) k_tile_rank(GridGeom g, TileGeom t, const int32_t* __restrict__ cell,
+                                                          long long n, int* cursor, int* perm, int* bad) {
+  extern __shared__ int cnt[];
+  int* const keys = cnt + kSortTable;
   const int nbk = t.ntiles + 1;
-  for (int e = threadIdx.x; e < nbk; e += blockDim.x) hist[e] = 0;
-  __syncthreads();
-  const long long p0 = (long long)blockIdx.x * kSortBlock * kSortPer + threadIdx.x;
-  int key[kSortPer], rank[kSortPer];
+  table_clear<HASH, BLOCK>(keys, cnt, nbk);
+  const long long p0 = (long long)blockIdx.x * BLOCK * kSortPer + threadIdx.x;
+  int place[kSortPer], rank[kSortPer];
 #pragma unroll
   for (int u = 0; u < kSortPer; ++u) {
-    const long long p = p0 + (long long)u * kSortBlock;
-    key[u] = (p < n) ? tile_key(cell[p], g, t) : 0;
-    rank[u] = wave_aggregated_add(hist, key[u], p < n);
+    const long long p = p0 + (long long)u * BLOCK;
+    const int key = (p < n) ? tile_key(cell[p], g, t) : 0;
+    rank[u] = table_add<HASH, true>(keys, cnt, cursor, key, p < n, place[u]);
+    if (p < n && key == t.ntiles && bad) atomicAdd(bad, 1);
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < nbk; e += blockDim.x) {
-    const int c = hist[e];
-    if (c) hist[e] = atomicAdd(&cursor[e], c);  // this workgroup's run of tile e
+  for (int e = threadIdx.x; e < (HASH ? kSortTable : nbk); e += BLOCK) {
+    const int c = cnt[e];
+    if (c) cnt[e] = atomicAdd(&cursor[HASH ? keys[e] : e], c);  // this workgroup's run of the tile
   }
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < kSortPer; ++u) {
-    const long long p = p0 + (long long)u * kSortBlock;
-    if (p < n) {
-      if (key[u] == t.ntiles && bad) atomicAdd(bad, 1);
-      dst[p] = hist[key[u]] + rank[u];
-    }
+    const long long p = p0 + (long long)u * BLOCK;
+    if (p < n) perm[(place[u] >= 0 ? cnt[place[u]] : 0) + rank[u]] = (int)p;
   }
 }
 
 // Exclusive scan of counts[0..m) into starts[0..m] (starts[m] = the total) and cursor[0..m)
-// by blocks of 1024 threads, in chunks of 1024 x 8 entries: thread t takes the 8 adjacent
-// entries at the chunk's base + 8 t (the block's loads and stores cover contiguous memory),
-// and the block scans the thread sums (a scan within each wave, then over the 16 wave totals).
+// by blocks of 1024 threads, in chunks of 1024 x PER entries: thread t takes the PER adjacent
+// entries at the chunk's base + PER t as 16-byte vectors, and the block scans the thread sums (a scan
+// within each wave, then over the 16 wave totals).  A scan leaves the counts at zero, for the next
+// count into them.
 constexpr int kScanPer = 8;
 constexpr int kScanChunk = 1024 * kScanPer;
 constexpr int kScanWaves = 1024 / 64;
 
-// One chunk from ``carry`` (the sum of everything before it); returns the chunk's total.
+// One chunk from ``carry`` (the sum of everything before it); returns the sum up to its end.
 // Every thread of the block calls it.
-__device__ inline int scan_chunk(const int* __restrict__ counts, int* starts, int* cursor, int m, int base, int carry,
-                                 int* wsum) {
+template <int PER>
+__device__ inline int scan_chunk(int* counts, int* starts, int* cursor, int m, int base, int carry, int* wsum) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int i0 = base + tid * kScanPer;
-  int v[kScanPer];
+  const int i0 = base + tid * PER;
+  int v[PER];
+  const bool whole = i0 + PER <= m;
+  if (whole) {
+#pragma unroll
+    for (int k = 0; k < PER; k += 4) {
+      const int4 q = *reinterpret_cast<const int4*>(counts + i0 + k);
+      v[k] = q.x; v[k + 1] = q.y; v[k + 2] = q.z; v[k + 3] = q.w;
+      *reinterpret_cast<int4*>(counts + i0 + k) = make_int4(0, 0, 0, 0);
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      v[k] = (i0 + k < m) ? counts[i0 + k] : 0;
+      if (i0 + k < m) counts[i0 + k] = 0;
+    }
+  }
   int s = 0;
 #pragma unroll
-  for (int k = 0; k < kScanPer; ++k) {
-    v[k] = (i0 + k < m) ? counts[i0 + k] : 0;
-    s += v[k];
-  }
+  for (int k = 0; k < PER; ++k) s += v[k];
   int x = s;  // inclusive scan of the thread sums within the wave
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
@@ -172,54 +186,42 @@ __device__ inline int scan_chunk(const int* __restrict__ counts, int* starts, in
   }
   if (lane == 63) wsum[wave] = x;
   __syncthreads();
-  if (wave == 0) {  // inclusive scan of the wave totals
-    int w = lane < kScanWaves ? wsum[lane] : 0;
+  int run = carry + x - s, total = carry;
 #pragma unroll
-    for (int o = 1; o < kScanWaves; o <<= 1) {
-      const int y = __shfl_up(w, o, 64);
-      if (lane >= o) w += y;
-    }
-    if (lane < kScanWaves) wsum[lane] = w;
+  for (int w = 0; w < kScanWaves; ++w) {
+    run += w < wave ? wsum[w] : 0;
+    total += wsum[w];
   }
-  __syncthreads();
-  int run = carry + (wave > 0 ? wsum[wave - 1] : 0) + x - s;
 #pragma unroll
-  for (int k = 0; k < kScanPer; ++k) {
-    if (i0 + k < m) {
-      starts[i0 + k] = run;
-      cursor[i0 + k] = run;
-      run += v[k];
-    }
+  for (int k = 0; k < PER; ++k) {
+    const int c = v[k];
+    v[k] = run;
+    run += c;
   }
-  const int total = wsum[kScanWaves - 1];
-  __syncthreads();  // wsum is rewritten by the next chunk
+  if (whole) {
+#pragma unroll
+    for (int k = 0; k < PER; k += 4) {
+      const int4 q = make_int4(v[k], v[k + 1], v[k + 2], v[k + 3]);
+      *reinterpret_cast<int4*>(starts + i0 + k) = q;
+      *reinterpret_cast<int4*>(cursor + i0 + k) = q;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (i0 + k < m) {
+        starts[i0 + k] = v[k];
+        cursor[i0 + k] = v[k];
+      }
+  }
   return total;
 }
 
-// Up to two chunks (m <= 2 kScanChunk), one block: thread t scans its own run of at most 16
-// adjacent entries serially, the block scans the run totals (one launch beats three there).
-__global__ void __launch_bounds__(1024) k_scan(const int* __restrict__ counts, int* starts, int* cursor, int m) {
-  __shared__ int part[1024];
-  const int tid = threadIdx.x;
-  const int chunk = (m + blockDim.x - 1) / blockDim.x;
-  const int lo = min(m, tid * chunk), hi = min(m, lo + chunk);
-  int s = 0;
-  for (int i = lo; i < hi; ++i) s += counts[i];
-  part[tid] = s;
-  __syncthreads();
-  for (int off = 1; off < (int)blockDim.x; off <<= 1) {
-    const int v = (tid >= off) ? part[tid - off] : 0;
-    __syncthreads();
-    part[tid] += v;
-    __syncthreads();
-  }
-  int run = part[tid] - s;  // exclusive prefix of this run
-  for (int i = lo; i < hi; ++i) {
-    starts[i] = run;
-    cursor[i] = run;
-    run += counts[i];
-  }
-  if (tid == blockDim.x - 1) starts[m] = part[tid];
+// m <= 1024 x PER, one block (one launch beats three there).
+template <int PER>
+__global__ void __launch_bounds__(1024) k_scan(int* counts, int* starts, int* cursor, int m) {
+  __shared__ int wsum[kScanWaves];
+  const int total = scan_chunk<PER>(counts, starts, cursor, m, 0, 0, wsum);
+  if (threadIdx.x == 0) starts[m] = total;
 }
 
 // Large m, first of three launches: sums[b] = the total of chunk b.
@@ -262,20 +264,11 @@ __global__ void __launch_bounds__(1024) k_scan_offsets(int* sums, int nb, int* t
   if (tid == 1023) *total = before + x;
 }
 
-// One block over every chunk in turn (the fallback without scratch).
-__global__ void __launch_bounds__(1024) k_scan_apply_serial(const int* __restrict__ counts, int* starts, int* cursor,
-                                                            int m) {
-  __shared__ int wsum[kScanWaves];
-  int carry = 0;
-  for (int base = 0; base < m; base += kScanChunk) carry += scan_chunk(counts, starts, cursor, m, base, carry, wsum);
-  if (threadIdx.x == 0) starts[m] = carry;
-}
-
 // Third launch: block b scans chunk b from its offset.
-__global__ void __launch_bounds__(1024) k_scan_apply(const int* __restrict__ counts, int* starts, int* cursor, int m,
+__global__ void __launch_bounds__(1024) k_scan_apply(int* counts, int* starts, int* cursor, int m,
                                                      const int* __restrict__ offsets) {
   __shared__ int wsum[kScanWaves];
-  (void)scan_chunk(counts, starts, cursor, m, blockIdx.x * kScanChunk, offsets[blockIdx.x], wsum);
+  (void)scan_chunk<kScanPer>(counts, starts, cursor, m, blockIdx.x * kScanChunk, offsets[blockIdx.x], wsum);
 }
 
 // For every destination tile D of the new grouping: the slot runs of the particles that
@@ -320,11 +313,6 @@ __global__ void __launch_bounds__(256) k_neighbour_bases(TileGeom t, const int* 
   if (o == 31) cursor[D] = run0 + x;
 }
 
-__global__ void __launch_bounds__(256) k_invert(const int* __restrict__ dst, int* perm, long long n) {
-  const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < n) perm[dst[p]] = (int)p;
-}
-
 }  // namespace
 
 FastDiv make_fastdiv(uint32_t d) {
@@ -349,62 +337,52 @@ TileGeom make_tiles(const GridGeom& g) {
   return t;
 }
 
-// The exclusive scan of the ntiles + 1 bucket counts: one block for up to two chunks, else
-// the three-launch form through t.scan_tmp (up to 1024 chunks: every grid pic_init accepts).
-void scan_buckets(const TileGeom& t, const int* counts, int* starts, int* cursor, hipStream_t s) {
+// The exclusive scan of the ntiles + 1 bucket counts: one block up to 16384 entries, else
+// the three-launch form through t.scan_tmp (at most 257 chunks on a 1024^3 grid).
+void scan_counts(const TileGeom& t, int* counts, int* starts, int* cursor, hipStream_t s) {
   const int m = t.ntiles + 1;
   const int nb = (m + kScanChunk - 1) / kScanChunk;
   if (nb <= 2) {
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, counts, starts, cursor, m);
+    if (m <= 4096) hipLaunchKernelGGL(k_scan<4>, dim3(1), dim3(1024), 0, s, counts, starts, cursor, m);
+    else hipLaunchKernelGGL(k_scan<16>, dim3(1), dim3(1024), 0, s, counts, starts, cursor, m);
     return;
   }
-  if (nb > 1024 || !t.scan_tmp) {  // not reached through pic_init: a chunk per block in turn would be needed
-    hipLaunchKernelGGL(k_scan_apply_serial, dim3(1), dim3(1024), 0, s, counts, starts, cursor, m);
-    return;
-  }
-  hipLaunchKernelGGL(k_scan_sums, dim3(nb), dim3(1024), 0, s, counts, m, t.scan_tmp);
+  hipLaunchKernelGGL(k_scan_sums, dim3(nb), dim3(1024), 0, s, (const int*)counts, m, t.scan_tmp);
   hipLaunchKernelGGL(k_scan_offsets, dim3(1), dim3(1024), 0, s, t.scan_tmp, nb, starts + m);
-  hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(1024), 0, s, counts, starts, cursor, m,
-                     (const int*)t.scan_tmp);
+  hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(1024), 0, s, counts, starts, cursor, m, (const int*)t.scan_tmp);
 }
+
+namespace {
+
+template <bool HASH, int BLOCK>
+void sort_with(const GridGeom& g, const TileGeom& t, const int32_t* cell, int64_t n, int* counts, int* starts,
+               int* cursor, int* perm, int* bad, hipStream_t s) {
+  const dim3 grid((unsigned)((n + BLOCK * kSortPer - 1) / (BLOCK * kSortPer))), block(BLOCK);
+  const size_t lds = sizeof(int) * (size_t)(HASH ? 2 * kSortTable : t.ntiles + 1);
+  allow_lds((const void*)k_tile_count<HASH, BLOCK>, lds);
+  allow_lds((const void*)k_tile_rank<HASH, BLOCK>, lds);
+  if (n > 0)
+    hipLaunchKernelGGL((k_tile_count<HASH, BLOCK>), grid, block, lds, s, g, t, cell, (long long)n, counts);
+  scan_counts(t, counts, starts, cursor, s);
+  if (n > 0)
+    hipLaunchKernelGGL((k_tile_rank<HASH, BLOCK>), grid, block, lds, s, g, t, cell, (long long)n, cursor, perm, bad);
+}
+
+}  // namespace
 
 void tile_sort(const GridGeom& g, const TileGeom& t, const int32_t* cell, int64_t n, int* counts, int* starts,
-               int* cursor, int* dst, int* bad, hipStream_t s) {
-  // buckets 0..ntiles-1 are tiles, bucket ntiles collects invalid cells
-  (void)hipMemsetAsync(counts, 0, sizeof(int) * (t.ntiles + 1), s);
-  if (t.ntiles + 1 <= kSortMaxBuckets) {
-    const size_t lds = sizeof(int) * (size_t)(t.ntiles + 1);
-    const unsigned nbl = (unsigned)((n + kSortBlock * kSortPer - 1) / (kSortBlock * kSortPer));
-    if (lds > 64 * 1024) {
-      (void)hipFuncSetAttribute((const void*)k_tile_count_lds, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      (void)hipFuncSetAttribute((const void*)k_tile_rank_lds, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    }
-    if (n > 0)
-      hipLaunchKernelGGL(k_tile_count_lds, dim3(nbl), dim3(kSortBlock), lds, s, g, t, cell, (long long)n, counts);
-    scan_buckets(t, counts, starts, cursor, s);
-    if (n > 0)
-      hipLaunchKernelGGL(k_tile_rank_lds, dim3(nbl), dim3(kSortBlock), lds, s, g, t, cell, (long long)n, cursor, dst,
-                         bad);
-    return;
-  }
-  const unsigned nb = (unsigned)((n + 255) / 256);
-  if (n > 0) hipLaunchKernelGGL(k_tile_count, dim3(nb), dim3(256), 0, s, g, t, cell, (long long)n, counts);
-  scan_buckets(t, counts, starts, cursor, s);
-  if (n > 0) hipLaunchKernelGGL(k_tile_rank, dim3(nb), dim3(256), 0, s, g, t, cell, (long long)n, cursor, dst, bad);
-}
-
-void scan_counts(const TileGeom& t, const int* counts, int* starts, int* cursor, hipStream_t s) {
-  scan_buckets(t, counts, starts, cursor, s);
+               int* cursor, int* perm, int* bad, hipStream_t s) {
+  // buckets 0..ntiles-1 are tiles, bucket ntiles collects invalid cells; small tables (and the hashed
+  // one) take small workgroups, large ones as many particles per table as a workgroup can hold
+  if (t.ntiles + 1 > kSortBuckets) sort_with<true, 256>(g, t, cell, n, counts, starts, cursor, perm, bad, s);
+  else if (t.ntiles + 1 > 1024) sort_with<false, 1024>(g, t, cell, n, counts, starts, cursor, perm, bad, s);
+  else sort_with<false, 256>(g, t, cell, n, counts, starts, cursor, perm, bad, s);
 }
 
 void neighbour_bases(const TileGeom& t, const int* old_starts, const int* nbr_counts, const int* new_starts,
                      int* bases, int* cursor, hipStream_t s) {
   hipLaunchKernelGGL(k_neighbour_bases, dim3((unsigned)((t.ntiles + 7) / 8)), dim3(256), 0, s, t, old_starts,
                      nbr_counts, new_starts, bases, cursor);
-}
-
-void invert_perm(const int* dst, int* perm, int64_t n, hipStream_t s) {
-  if (n > 0) hipLaunchKernelGGL(k_invert, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dst, perm, (long long)n);
 }
 
 }  // namespace pic

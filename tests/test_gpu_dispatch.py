@@ -94,3 +94,38 @@ def test_centering_in_the_transforms_of_any_length(dtype, shape, order):
     """Calls of several steps centre inside the transforms on every grid; here axes with factors of 9."""
     banner(f"pic_step 3 steps, centering in the transforms dtype={dtype} shape={shape} order={order}")
     steps_against_oracle(shape, 1, order, 8, dtype, 3)
+
+
+@pytest.mark.parametrize("order", ["grouped", "scattered"])
+@pytest.mark.parametrize("shape", [(16, 16, 24), (72, 72, 128), (192, 324, 256), (256, 256, 288)])
+def test_tile_sort_tables(shape, order):
+    """The counting sort's tables: few buckets (small workgroups), more than 1024, the most the indexed table
+    holds, and the hashed table (more than 32768 buckets), with grouped and with scattered particles, some of
+    them outside the grid.  Every valid particle deposits its charge once, wherever it lies in the arrays."""
+    banner(f"pic_deposit over the sort's tables shape={shape} order={order}")
+    N, n = int(np.prod(shape)), 70000
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9)
+    cell = torch.randint(0, N, (n,), generator=gen, device="cuda", dtype=torch.int32)
+    if order == "grouped":
+        cell = cell.sort().values
+    bad = torch.arange(0, n, 997, device="cuda")
+    cell[bad] = -1
+    half = torch.full((n,), 0.5, device="cuda", dtype=torch.float64)
+    ctx = piclib.Context(shape, (1.0, 1.0, 1.0), 0.5, 1, 4, 16, "f64")
+    f = piclib.Fields(shape, "f64")
+    sp = piclib.Species(cell, [half] * 3, [torch.zeros_like(half)] * 3, None, 1.0, 1.0, w_const=8.0)
+    for _ in range(2):  # the second call counts into what the first left
+        piclib.pic_deposit(ctx.ctx, [sp], f, piclib.PIC_DEP_RHO_ONLY)
+    # an offset of 1/2 gives every one of the eight nodes of the cell the charge 8 / 8 = 1
+    c = cell[cell >= 0].long()
+    i, j, k = c // (shape[1] * shape[2]), (c // shape[2]) % shape[1], c % shape[2]
+    ref = torch.zeros(N, device="cuda", dtype=torch.float64)
+    one = torch.ones(c.numel(), device="cuda", dtype=torch.float64)
+    for a in range(8):
+        q = (((i + a // 4) % shape[0]) * shape[1] + (j + a // 2 % 2) % shape[1]) * shape[2] + (k + a % 2) % shape[2]
+        ref.index_add_(0, q, one)
+    assert torch.equal(f.rho_new.reshape(-1), ref)
+    with pytest.raises(RuntimeError, match="out-of-range"):
+        piclib.pic_sync(ctx.ctx)
+    ctx.close()
