@@ -771,14 +771,14 @@ void copy_species(const SpeciesView<T>& from, const SpeciesView<T>& to, hipStrea
 // forward transforms of the state (E, B) and/or sources (J, rho_old, rho_new)
 template <typename T>
 void forward_batch(pic_ctx c, Engine<T>& e, const T* const* src, cplx<T>* const* dst, int count,
-                   const LineCenter<T>* lc = nullptr, bool x_pass = true) {
+                   const LineCenter<T>* lc = nullptr) {
   Batch<const T*> in{};
   Batch<cplx<T>*> out{};
   for (int i = 0; i < count; ++i) {
     in.p[i] = src[i];
     out.p[i] = dst[i];
   }
-  e.fft.forward(in, out, count, c->stream, lc, x_pass);
+  e.fft.forward(in, out, count, c->stream, lc);
 }
 
 // The centering of the real-space cycle as LineCenter of the transforms: J nodes -> Yee (J^d
@@ -797,54 +797,15 @@ LineCenter<T> transform_centering(pic_ctx c, bool to_nodes) {
   return lc;
 }
 
-// The x pass of the sources' transforms, the update and the inverse x pass in one kernel: the standard
-// update (staggered or nodal) of axes up to 768 points.  The options with other tables or more outputs keep
-// the separate passes.
-template <typename T>
-bool solves_along_x(pic_ctx c, const Engine<T>& e) {
-  return e.fft.can_solve_x() && !e.tab.G[0] && !e.tab.Av[0] && !e.tab.cc &&
-         !(c->p.flags & PIC_SPECTRAL_CENTERING);
-}
-
-// That kernel, into the scratch spectra; step: pic_step's resident spectra, else psatd_push_fields' eleven.
-template <typename T>
-void solve_along_x(pic_ctx c, Engine<T>& e, int rho_old_slot, bool step, const LineCenter<T>* j_center,
-                   const LineCenter<T>* eb_center) {
-  SolveX<T> a{};
-  for (int d = 0; d < 3; ++d) {
-    a.src[d] = a.state[d] = e.Eh[d];
-    a.src[3 + d] = a.state[3 + d] = e.Bh[d];
-    a.src[6 + d] = e.Jh[d];
-    a.Dp[d] = e.tab.Dp[d];
-    a.Dm[d] = e.tab.Dm[d];
-  }
-  a.src[9] = a.rho_out = e.rh[1 - rho_old_slot];
-  a.src[10] = e.rh[rho_old_slot];
-  for (int i = 0; i < 6; ++i) a.out[i] = e.scratch[i];
-  a.C = e.tab.C;
-  a.Sw = e.tab.Sw;
-  a.X1 = e.tab.X1;
-  a.X2 = e.tab.X2;
-  a.X3 = e.tab.X3;
-  a.ny = c->p.ny;
-  a.nzh = e.fft.nzh;
-  a.pz = e.fft.pz;
-  e.fft.solve_x(a, step, j_center, eb_center, c->stream);
-}
-
 // The per-mode update, then the inverse transforms: of the staggered state into E_stag,
 // B_stag, or (spectral centering) of the nodal spectra the update also wrote, in place in
 // the scratch spectra, into E_nod, B_nod.
 template <typename T>
 void update_and_inverse(pic_ctx c, Engine<T>& e, pic_fields* f, int rho_old_slot, bool spectral = false,
-                        bool state_out = true, const LineCenter<T>* to_nodes = nullptr, int along_x = 0,
-                        const LineCenter<T>* j_center = nullptr) {
+                        bool state_out = true, const LineCenter<T>* to_nodes = nullptr) {
   const pic_params& p = c->p;
   const bool avg = averaged(p);
-  if (along_x) {  // (1: pic_step, 2: psatd_push_fields)
-    StageScope sc(c, ST_UPDATE);
-    solve_along_x<T>(c, e, rho_old_slot, along_x == 1, j_center, to_nodes);
-  } else {
+  {
     StageScope sc(c, ST_UPDATE);
     psatd_update<T>(e.tab, e.Eh, e.Bh, e.Jh, e.rh[rho_old_slot], e.rh[1 - rho_old_slot], p.nx, p.ny, e.fft.nzh,
                     e.fft.pz, spectral ? e.scratch : (avg ? e.Ah : nullptr), c->stream);
@@ -875,7 +836,7 @@ void update_and_inverse(pic_ctx c, Engine<T>& e, pic_fields* f, int rho_old_slot
     out.p[3 + d] = static_cast<T*>(nod ? f->B_nod[d] : f->B_stag[d]);
   }
   for (int i = 0; i < 6; ++i) scr.p[i] = e.scratch[i];
-  e.fft.inverse(in, scr, out, 6, 1.0 / (double)ncells(p), c->stream, to_nodes, !along_x);
+  e.fft.inverse(in, scr, out, 6, 1.0 / (double)ncells(p), c->stream, to_nodes);
 }
 
 // The staggered state E_stag, B_stag from the resident spectra (end of a spectral-
@@ -899,7 +860,6 @@ void state_inverse(pic_ctx c, Engine<T>& e, pic_fields* f) {
 template <typename T>
 pic_status do_push_fields(pic_ctx c, pic_fields* f) {
   Engine<T>& e = static_cast<Engine<T>&>(*c->eng);
-  const bool along_x = solves_along_x(c, e);
   {
     StageScope sc(c, ST_FFT_FWD);
     const T* src[11];
@@ -916,9 +876,9 @@ pic_status do_push_fields(pic_ctx c, pic_fields* f) {
     dst[9] = e.rh[0];
     src[10] = static_cast<const T*>(f->rho_new);
     dst[10] = e.rh[1];
-    forward_batch<T>(c, e, src, dst, 11, nullptr, !along_x);
+    forward_batch<T>(c, e, src, dst, 11);
   }
-  update_and_inverse<T>(c, e, f, 0, false, true, nullptr, along_x ? 2 : 0);
+  update_and_inverse<T>(c, e, f, 0);
   return c->check("psatd_push_fields");
 }
 
@@ -1006,7 +966,6 @@ pic_status do_step_yee(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int n
     if (he != hipSuccess) return c->fail(PIC_ENOMEM, std::string("pic_step: ") + hipGetErrorString(he));
   }
   const size_t N = ncells(p);
-  const bool along_x = solves_along_x(c, e);
   for (int n = 0; n < nsteps; ++n) {
     {
       StageScope sc(c, ST_CLEAR);
@@ -1040,9 +999,9 @@ pic_status do_step_yee(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int n
       const T* src[4] = {static_cast<const T*>(f->J_stag[0]), static_cast<const T*>(f->J_stag[1]),
                          static_cast<const T*>(f->J_stag[2]), static_cast<const T*>(f->rho_new)};
       cplx<T>* dst[4] = {e.Jh[0], e.Jh[1], e.Jh[2], e.rh[1 - slot]};
-      forward_batch<T>(c, e, src, dst, 4, nullptr, !along_x);
+      forward_batch<T>(c, e, src, dst, 4);
     }
-    update_and_inverse<T>(c, e, f, slot, false, true, nullptr, along_x ? 1 : 0);
+    update_and_inverse<T>(c, e, f, slot);
     slot = 1 - slot;
     if ((st = c->check("pic_step")) != PIC_OK) return st;
   }
@@ -1099,7 +1058,6 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
   const bool fused = !spectral && !nodal && !avg;
   const LineCenter<T> lc_j = fused ? transform_centering<T>(c, false) : LineCenter<T>();
   const LineCenter<T> lc_eb = fused ? transform_centering<T>(c, true) : LineCenter<T>();
-  const bool along_x = solves_along_x(c, e);
   for (int n = 0; n < nsteps; ++n) {
     const bool mid = fused && n + 1 < nsteps;  // this step's transforms centre
     const bool nod_ready = fused && n > 0;     // E_nod, B_nod from the previous step's inverse
@@ -1205,10 +1163,9 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
       const T* src[4] = {static_cast<const T*>(J[0]), static_cast<const T*>(J[1]), static_cast<const T*>(J[2]),
                          static_cast<const T*>(f->rho_new)};
       cplx<T>* dst[4] = {e.Jh[0], e.Jh[1], e.Jh[2], e.rh[1 - slot]};
-      forward_batch<T>(c, e, src, dst, 4, mid ? &lc_j : nullptr, !along_x);
+      forward_batch<T>(c, e, src, dst, 4, mid ? &lc_j : nullptr);
     }
-    update_and_inverse<T>(c, e, f, slot, spectral, !avg, mid ? &lc_eb : nullptr, along_x ? 1 : 0,
-                          mid ? &lc_j : nullptr);
+    update_and_inverse<T>(c, e, f, slot, spectral, !avg, mid ? &lc_eb : nullptr);
     slot = 1 - slot;
     if ((st = c->check("pic_step")) != PIC_OK) return st;
   }
