@@ -771,14 +771,14 @@ void copy_species(const SpeciesView<T>& from, const SpeciesView<T>& to, hipStrea
 // forward transforms of the state (E, B) and/or sources (J, rho_old, rho_new)
 template <typename T>
 void forward_batch(pic_ctx c, Engine<T>& e, const T* const* src, cplx<T>* const* dst, int count,
-                   const LineCenter<T>* lc = nullptr) {
+                   const LineCenter<T>* lc = nullptr, bool x_pass = true) {
   Batch<const T*> in{};
   Batch<cplx<T>*> out{};
   for (int i = 0; i < count; ++i) {
     in.p[i] = src[i];
     out.p[i] = dst[i];
   }
-  e.fft.forward(in, out, count, c->stream, lc);
+  e.fft.forward(in, out, count, c->stream, lc, x_pass);
 }
 
 // The centering of the real-space cycle as LineCenter of the transforms: J nodes -> Yee (J^d
@@ -857,9 +857,38 @@ void state_inverse(pic_ctx c, Engine<T>& e, pic_fields* f) {
   e.fft.inverse(in, scr, out, 6, 1.0 / (double)ncells(c->p), c->stream);
 }
 
+// The x pass of the eleven transforms, the update and the inverse x pass in one kernel, into the scratch
+// spectra.
+template <typename T>
+void solve_along_x(pic_ctx c, Engine<T>& e) {
+  SolveX<T> a{};
+  for (int d = 0; d < 3; ++d) {
+    a.src[d] = e.Eh[d];
+    a.src[3 + d] = e.Bh[d];
+    a.src[6 + d] = e.Jh[d];
+    a.Dp[d] = e.tab.Dp[d];
+    a.Dm[d] = e.tab.Dm[d];
+  }
+  a.src[9] = e.rh[1];
+  a.src[10] = e.rh[0];
+  for (int i = 0; i < 6; ++i) a.out[i] = e.scratch[i];
+  a.C = e.tab.C;
+  a.Sw = e.tab.Sw;
+  a.X1 = e.tab.X1;
+  a.X2 = e.tab.X2;
+  a.X3 = e.tab.X3;
+  a.ny = c->p.ny;
+  a.nzh = e.fft.nzh;
+  a.pz = e.fft.pz;
+  e.fft.solve_x(a, c->stream);
+}
+
 template <typename T>
 pic_status do_push_fields(pic_ctx c, pic_fields* f) {
   Engine<T>& e = static_cast<Engine<T>&>(*c->eng);
+  // x pass, update and inverse x pass in one kernel: the standard update (not the Galilean and averaged
+  // tables, nor the current correction) on grids where that is faster
+  const bool along_x = e.fft.solves_along_x() && !e.tab.G[0] && !e.tab.Av[0] && !e.tab.cc;
   {
     StageScope sc(c, ST_FFT_FWD);
     const T* src[11];
@@ -876,9 +905,26 @@ pic_status do_push_fields(pic_ctx c, pic_fields* f) {
     dst[9] = e.rh[0];
     src[10] = static_cast<const T*>(f->rho_new);
     dst[10] = e.rh[1];
-    forward_batch<T>(c, e, src, dst, 11);
+    forward_batch<T>(c, e, src, dst, 11, nullptr, !along_x);
   }
-  update_and_inverse<T>(c, e, f, 0);
+  if (!along_x) {
+    update_and_inverse<T>(c, e, f, 0);
+    return c->check("psatd_push_fields");
+  }
+  {
+    StageScope sc(c, ST_UPDATE);
+    solve_along_x<T>(c, e);
+  }
+  StageScope sc(c, ST_FFT_INV);
+  Batch<const cplx<T>*> in{};
+  Batch<cplx<T>*> scr{};
+  Batch<T*> out{};
+  for (int d = 0; d < 3; ++d) {
+    out.p[d] = static_cast<T*>(f->E_stag[d]);
+    out.p[3 + d] = static_cast<T*>(f->B_stag[d]);
+  }
+  for (int i = 0; i < 6; ++i) scr.p[i] = e.scratch[i];
+  e.fft.inverse(in, scr, out, 6, 1.0 / (double)ncells(c->p), c->stream, nullptr, false);
   return c->check("psatd_push_fields");
 }
 

@@ -101,21 +101,34 @@ void Fft3D<T>::release() {
 
 template <typename T>
 void Fft3D<T>::forward(const Batch<const T*>& in, const Batch<cplx<T>*>& out, int count, hipStream_t s,
-                       const LineCenter<T>* lcp) const {
+                       const LineCenter<T>* lcp, bool x_pass) const {
   const LineCenter<T> lc = lcp ? *lcp : LineCenter<T>();
   ops[2]->r2c(in, out, count, tw[2], nx * ny, pz, lc, s);
   Batch<const cplx<T>*> cin;
   for (int i = 0; i < count; ++i) cin.p[i] = out.p[i];
   ops[1]->strided[0](cin, out, count, tw[1], nx, nzh, (long long)ny * pz, pz, lc, 1, s);
-  ops[0]->strided[0](cin, out, count, tw[0], 1, ny * pz, 0, (long long)ny * pz, lc, 0, s);
+  if (x_pass) ops[0]->strided[0](cin, out, count, tw[0], 1, ny * pz, 0, (long long)ny * pz, lc, 0, s);
+}
+
+// From 3 MB per array on: below, the kernel's chain of 17 transforms in one workgroup takes longer than
+// three launches (FP32 32^3 31.6 against 27.8 us, 64 x 64 x 128 69.7 against 69.1, 96^3 102 against 105, 96 x 96 x 192
+// 146 against 168; FP64 32^3 33.5 against 31.7, 64^3 66.6 against 66.9, 64 x 64 x 128 91 against 102).
+template <typename T>
+bool Fft3D<T>::solves_along_x() const {
+  return ops[0]->solve_x != nullptr && (size_t)nx * ny * nz * sizeof(T) >= (size_t)3 << 20;
+}
+
+template <typename T>
+void Fft3D<T>::solve_x(const SolveX<T>& a, hipStream_t s) const {
+  ops[0]->solve_x(a, tw[0], s);
 }
 
 template <typename T>
 void Fft3D<T>::inverse(const Batch<const cplx<T>*>& in, const Batch<cplx<T>*>& scratch, const Batch<T*>& out,
-                       int count, double scale, hipStream_t s, const LineCenter<T>* lcp) const {
+                       int count, double scale, hipStream_t s, const LineCenter<T>* lcp, bool x_pass) const {
   const LineCenter<T> lc = lcp ? *lcp : LineCenter<T>();
   const T sc_hi = (T)scale, sc_lo = (T)(scale - (double)sc_hi);
-  ops[0]->strided[1](in, scratch, count, tw[0], 1, ny * pz, 0, (long long)ny * pz, lc, 0, s);
+  if (x_pass) ops[0]->strided[1](in, scratch, count, tw[0], 1, ny * pz, 0, (long long)ny * pz, lc, 0, s);
   Batch<const cplx<T>*> cs;
   for (int i = 0; i < count; ++i) cs.p[i] = scratch.p[i];
   ops[1]->strided[1](cs, scratch, count, tw[1], nx, nzh, (long long)ny * pz, pz, lc, 1, s);

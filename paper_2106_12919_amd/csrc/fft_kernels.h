@@ -2,6 +2,8 @@
 // table of launchers per length that fft.hip calls.  fft_len.hip instantiates the lengths.
 #pragma once
 
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace pic {
@@ -16,6 +18,8 @@ struct FftOps {
   void (*strided[2])(const Batch<const cplx<T>*>& in, const Batch<cplx<T>*>& out, int count, const cplx<T>* tw,
                      int outer_count, int inner_count, long long outer_stride, long long elem_stride,
                      const LineCenter<T>& lc, int axis, hipStream_t s);  // forward, inverse
+  // x pass, standard update and inverse x pass in one kernel (null where it is not built)
+  void (*solve_x)(const SolveX<T>& a, const cplx<T>* tw, hipStream_t s);
 };
 // The axis lengths pic_init accepts: every even 2^a 3^b in [8, 1024].  fft_len.hip is compiled once per
 // unit u = 0 .. kFftUnits - 1 (in parallel) with the lengths at u, u + kFftUnits, ...
@@ -225,19 +229,19 @@ __device__ inline cplx<T>* fft_lds_static(cplx<T>* a, cplx<T>* b, const cplx<T>*
 // The same stages in one LDS buffer: every thread first takes the inputs of all its butterflies
 // of a stage into registers, and writes the outputs after the block's barrier.  Half the LDS of
 // the two-buffer form for the same tile, at one more barrier per stage.
-template <typename T, int SIGN, int N, int NL, bool LINE_FASTEST, int S = 0>
-__device__ inline void fft_lds_static_inplace(cplx<T>* a, const cplx<T>* __restrict__ tw) {
+template <typename T, int SIGN, int N, int NL, bool LINE_FASTEST, int BLOCK = kBlock, int S = 0>
+__device__ inline void fft_lds_static_inplace(cplx<T>* a, const cplx<T>* __restrict__ tw, int tid) {
   constexpr FftPlan P = plan_of(N, !LINE_FASTEST);
   if constexpr (S < P.nstages) {
     constexpr int R = P.radix[S], NS = P.ns[S], NB = N / R, TOTAL = NL * NB;
     constexpr int LS = LINE_FASTEST ? 1 : N, JS = LINE_FASTEST ? NL : 1;
-    constexpr int IT = (TOTAL + kBlock - 1) / kBlock;
+    constexpr int IT = (TOTAL + BLOCK - 1) / BLOCK;
     const cplx<T>* tws = tw + P.twoff[S];
     cplx<T> v[IT][R];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-      const int w = it * kBlock + (int)threadIdx.x;
-      if (TOTAL % kBlock == 0 || w < TOTAL) {
+      const int w = it * BLOCK + tid;
+      if (TOTAL % BLOCK == 0 || w < TOTAL) {
         const int l = LINE_FASTEST ? w % NL : w / NB;
         const int bi = LINE_FASTEST ? w / NL : w % NB;
 #pragma unroll
@@ -257,8 +261,8 @@ __device__ inline void fft_lds_static_inplace(cplx<T>* a, const cplx<T>* __restr
     __syncthreads();
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-      const int w = it * kBlock + (int)threadIdx.x;
-      if (TOTAL % kBlock == 0 || w < TOTAL) {
+      const int w = it * BLOCK + tid;
+      if (TOTAL % BLOCK == 0 || w < TOTAL) {
         const int l = LINE_FASTEST ? w % NL : w / NB;
         const int bi = LINE_FASTEST ? w / NL : w % NB;
         const int j0 = (bi / NS) * NS * R + bi % NS;
@@ -267,7 +271,7 @@ __device__ inline void fft_lds_static_inplace(cplx<T>* a, const cplx<T>* __restr
       }
     }
     __syncthreads();
-    fft_lds_static_inplace<T, SIGN, N, NL, LINE_FASTEST, S + 1>(a, tw);
+    fft_lds_static_inplace<T, SIGN, N, NL, LINE_FASTEST, BLOCK, S + 1>(a, tw, tid);
   }
 }
 
@@ -495,7 +499,7 @@ __global__ void __launch_bounds__(kBlock) k_fft_strided_n(Batch<const cplx<T>*> 
   __syncthreads();
   const bool cen = (cmask >> blockIdx.y) & 1u;
   if (SIGN < 0 && cen) center_tile<T, N, TL, true, 0>(a, lc);  // forward: centre, then transform
-  fft_lds_static_inplace<T, SIGN, N, TL, true>(a, twl);
+  fft_lds_static_inplace<T, SIGN, N, TL, true>(a, twl, threadIdx.x);
   if (SIGN > 0 && cen) center_tile<T, N, TL, true, -1>(a, lc);  // inverse: transform, then centre
   if (i < nl) {
     cplx<T>* __restrict__ dst = out.p[blockIdx.y] + row0;
@@ -504,6 +508,162 @@ __global__ void __launch_bounds__(kBlock) k_fft_strided_n(Batch<const cplx<T>*> 
       const int e = (int)threadIdx.x + u * kBlock;
       if (TOTAL % kBlock == 0 || e < TOTAL) dst[u * step] = a[e];
     }
+  }
+}
+
+// ------------------------------------------------- x pass, update and inverse x pass in one kernel
+
+// Lines and workgroup of the fused pass at length N (lines = 0: not built).  A thread holds six complex
+// values (the updated E, B) for each of its elements, so a workgroup grows with the line: at most 6
+// elements per thread in FP32, 3 in FP64 (2 in workgroups of 1024, which have 128 registers per thread).
+// Tiles of 16 or 8 lines are 128- or 64-byte rows (FP64: 128 and 64 bytes at 8 and 4 lines).
+template <typename T>
+struct SolveShape {
+  int lines, block;
+};
+template <typename T>
+constexpr SolveShape<T> solve_shape(int n) {
+  const int per = sizeof(T) == 4 ? 6 : 3, wide = sizeof(T) == 4 ? 16 : 8;
+  if (n * wide <= 256 * per) return {wide, 256};
+  if (n * wide <= 512 * per) return {wide, 512};
+  if (n * wide / 2 <= 512 * per) return {wide / 2, 512};
+  if (n * wide / 2 <= 1024 * (sizeof(T) == 4 ? 6 : 2)) return {wide / 2, 1024};
+  return {0, 0};
+}
+
+// The standard update of psatd.hip between the transforms along x, for psatd_push_fields.  A workgroup
+// takes TL adjacent (ky, kz) columns for every x, transforms the eleven inputs along x one after the other
+// in the same LDS tile, adds each one's part of the update to the six updated fields, which stay in
+// registers, and transforms those back.  As three kernels (x pass, update, inverse x pass) they move 54
+// spectra between HBM and the chip, here 18 (the tables are even in kx, so lines read them for
+// kx <= N / 2 only).  216 x 216 x 288 FP64: 532 + 450 + 268 us -> 865; the whole solve at 256^3: FP32 1890 ->
+// 1507 us, FP64 3563 -> 2702.  Bound by its chain of 17 transforms (2 barriers per stage) at two
+// workgroups per CU.  The same fusion of pic_step's resident state (40 arrays against 25) was no faster
+// than the separate kernels (384 x 384 x 768 FP32 4.1 ms either way, 128 x 128 x 256 142 against 128 us).
+template <typename T, int N>
+__global__ void __launch_bounds__(solve_shape<T>(N).block, sizeof(T) == 4 ? 4 : 3) k_solve_x(SolveX<T> a, const cplx<T>* __restrict__ tw) {
+  constexpr int TL = solve_shape<T>(N).lines, BLOCK = solve_shape<T>(N).block;
+  constexpr int TOTAL = N * TL, PER = (TOTAL + BLOCK - 1) / BLOCK, ROWS = BLOCK / TL;
+  extern __shared__ __align__(16) unsigned char smem[];
+  cplx<T>* tile = reinterpret_cast<cplx<T>*>(smem);
+  cplx<T>* twl = tile + TOTAL;
+  for (int e = threadIdx.x; e < N - 1; e += BLOCK) twl[e] = tw[e];
+  const int col0 = xcd_major(blockIdx.x, gridDim.x) * TL;
+  const int i = (int)threadIdx.x % TL, j0 = (int)threadIdx.x / TL;
+  const int col = col0 + i, ky = col / a.pz, kz = col - ky * a.pz;
+  const bool mode = kz < a.nzh;  // not a padding column
+  // element u of this thread: a uniform row offset plus a 32-bit byte offset of the thread's own
+  const size_t step = (size_t)ROWS * a.ny * a.pz;
+  const unsigned off = (unsigned)(j0 * a.ny * a.pz + col) * (unsigned)sizeof(cplx<T>);
+  auto at = [&](auto* p, int u) -> decltype(*p) {
+    using C = std::conditional_t<std::is_const_v<std::remove_pointer_t<decltype(p)>>, const char, char>;
+    return *reinterpret_cast<decltype(p)>(reinterpret_cast<C*>(p + u * step) + off);
+  };
+  auto has = [&](int u) { return TOTAL % BLOCK == 0 || (int)threadIdx.x + u * BLOCK < TOTAL; };
+  auto load = [&](const cplx<T>* src, cplx<T>* v) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) v[u] = has(u) ? at(src, u) : cmake((T)0, (T)0);
+  };
+  // a fresh copy of the thread index: indices derived from it are recomputed by each transform instead of
+  // being kept in registers from the first to the last
+  auto tid = [&]() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+  };
+  auto put = [&](const cplx<T>* v) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if (has(u)) tile[threadIdx.x + u * BLOCK] = v[u];
+    __syncthreads();
+  };
+  auto own = [&](int u) { return has(u) ? tile[threadIdx.x + u * BLOCK] : cmake((T)0, (T)0); };
+  // per element: its row of the tables (kx and N - kx share it) and the operators along x
+  auto table = [&](const T* t, int u) {
+    const int j = tid() / TL + u * ROWS, jm = 2 * j > N ? N - j : j;
+    const unsigned o = (unsigned)((jm * a.ny + ky) * a.nzh + kz) * (unsigned)sizeof(T);
+    return mode && has(u) ? *reinterpret_cast<const T*>(reinterpret_cast<const char*>(t) + o) : (T)0;
+  };
+  auto dx = [&](const cplx<T>* d, int u) { return d[min(tid() / TL + u * ROWS, N - 1)]; };
+  const int kzc = mode ? kz : 0;
+  const cplx<T> py = a.Dp[1][ky], my = a.Dm[1][ky], pz = a.Dp[2][kzc], mz = a.Dm[2][kzc];
+
+  cplx<T> F[6][PER];  // E, B, then their update
+  // forms the six values of element u here: left alone, the compiler moves the additions towards their
+  // last use and keeps every source's terms in registers until then (190 instead of 110 at 128 points)
+  auto settle = [&](int u) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) asm volatile("" : "+v"(F[c][u].x), "+v"(F[c][u].y)::"memory");
+  };
+  cplx<T> v[PER];
+  load(a.src[0], v);
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    put(v);
+    load(a.src[c + 1], v);
+    fft_lds_static_inplace<T, -1, N, TL, true, BLOCK>(tile, twl, tid());
+#pragma unroll
+    for (int u = 0; u < PER; ++u) F[c][u] = own(u);
+  }
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {  // the fields' own part: C E + Sw D- x B, C B - Sw D+ x E
+    const T C = table(a.C, u), Sw = table(a.Sw, u);
+    const cplx<T> px = dx(a.Dp[0], u), mx = dx(a.Dm[0], u);
+    const cplx<T> ex = F[0][u], ey = F[1][u], ez = F[2][u], bx = F[3][u], by = F[4][u], bz = F[5][u];
+    F[0][u] = cadd(cscale(ex, C), cscale(csub(cmul(my, bz), cmul(mz, by)), Sw));
+    F[1][u] = cadd(cscale(ey, C), cscale(csub(cmul(mz, bx), cmul(mx, bz)), Sw));
+    F[2][u] = cadd(cscale(ez, C), cscale(csub(cmul(mx, by), cmul(my, bx)), Sw));
+    F[3][u] = csub(cscale(bx, C), cscale(csub(cmul(py, ez), cmul(pz, ey)), Sw));
+    F[4][u] = csub(cscale(by, C), cscale(csub(cmul(pz, ex), cmul(px, ez)), Sw));
+    F[5][u] = csub(cscale(bz, C), cscale(csub(cmul(px, ey), cmul(py, ex)), Sw));
+    settle(u);
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {  // J^d: -Sw J to E^d, X1 D+ x J to the two other components of B
+    put(v);
+    load(a.src[7 + d], v);
+    fft_lds_static_inplace<T, -1, N, TL, true, BLOCK>(tile, twl, tid());
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const T Sw = table(a.Sw, u), X1 = table(a.X1, u);
+      const cplx<T> j = own(u), xj = cscale(j, X1);
+      F[d][u] = csub(F[d][u], cscale(j, Sw));
+      const cplx<T> px = dx(a.Dp[0], u);
+      if (d == 0) {
+        F[4][u] = cadd(F[4][u], cmul(pz, xj));
+        F[5][u] = csub(F[5][u], cmul(py, xj));
+      } else if (d == 1) {
+        F[5][u] = cadd(F[5][u], cmul(px, xj));
+        F[3][u] = csub(F[3][u], cmul(pz, xj));
+      } else {
+        F[3][u] = cadd(F[3][u], cmul(py, xj));
+        F[4][u] = csub(F[4][u], cmul(px, xj));
+      }
+      settle(u);
+    }
+  }
+  // rho^{n+1}, then rho^n: (X3 rho^n - X2 rho^{n+1}) D+ to E
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    put(v);
+    load(a.src[10], v);  // rho^n (the second time a reload that nothing uses)
+    fft_lds_static_inplace<T, -1, N, TL, true, BLOCK>(tile, twl, tid());
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const cplx<T> rr = cscale(own(u), r == 0 ? -table(a.X2, u) : table(a.X3, u));
+      F[0][u] = cadd(F[0][u], cmul(rr, dx(a.Dp[0], u)));
+      F[1][u] = cadd(F[1][u], cmul(rr, py));
+      F[2][u] = cadd(F[2][u], cmul(rr, pz));
+      settle(u);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    put(F[c]);
+    fft_lds_static_inplace<T, +1, N, TL, true, BLOCK>(tile, twl, tid());
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if (has(u)) at(a.out[c], u) = own(u);
   }
 }
 
@@ -543,7 +703,16 @@ struct FftLength {
     hipLaunchKernelGGL((k_fft_strided_n<T, SIGN, N>), dim3(outer_count * tpo, count), dim3(kBlock), lds, s, in, out,
                        tw, inner_count, tpo, outer_stride, elem_stride, lc, lc.m > 0 ? lc.mask[axis] : 0u);
   }
-  static constexpr FftOps<T> ops = {&r2c, &c2r, {&strided<-1>, &strided<+1>}};
+  static void solve_x(const SolveX<T>& a, const cplx<T>* tw, hipStream_t s) {
+    constexpr SolveShape<T> S = solve_shape<T>(N);
+    if constexpr (S.lines > 0) {
+      constexpr size_t lds = fft_lds_bytes<T>((size_t)S.lines * N, N);
+      allow_lds((const void*)k_solve_x<T, N>, lds);
+      hipLaunchKernelGGL((k_solve_x<T, N>), dim3((unsigned)(a.ny * a.pz / S.lines)), dim3(S.block), lds, s, a, tw);
+    }
+  }
+  static constexpr FftOps<T> ops = {&r2c, &c2r, {&strided<-1>, &strided<+1>},
+                                    solve_shape<T>(N).lines > 0 ? &solve_x : nullptr};
 };
 
 }  // namespace

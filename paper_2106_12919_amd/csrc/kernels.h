@@ -23,6 +23,17 @@ struct LineCenter {
   T c[16] = {};
 };
 
+// Arguments of the fused x pass, standard update and inverse x pass.  src: E (0..2), B (3..5), J (6..8),
+// rho^{n+1} (9), rho^n (10) after their z and y passes; out: the updated E, B after their inverse x pass.
+template <typename T>
+struct SolveX {
+  const cplx<T>* src[11];
+  cplx<T>* out[6];
+  const T *C, *Sw, *X1, *X2, *X3;
+  const cplx<T>*Dp[3], *Dm[3];
+  int ny, nzh, pz;
+};
+
 template <typename T>
 struct FftOps;  // launchers of one axis length (fft_kernels.h)
 
@@ -37,14 +48,19 @@ struct Fft3D {
   size_t spectrum_elems() const { return (size_t)nx * ny * pz; }
   // count <= kMaxBatch arrays, real -> spectrum; lc (optional): centering of the inputs folded into
   // the passes
+  // (x_pass = false: the z and y passes only)
   void forward(const Batch<const T*>& in, const Batch<cplx<T>*>& out, int count, hipStream_t s,
-               const LineCenter<T>* lc = nullptr) const;
+               const LineCenter<T>* lc = nullptr, bool x_pass = true) const;
+  // whether the fused x pass exists for nx and is the faster one on this grid, and its launch
+  bool solves_along_x() const;
+  void solve_x(const SolveX<T>& a, hipStream_t s) const;
   // spectrum -> real; ``scratch`` receives the partially transformed spectra (``in`` is preserved);
   // the result is scaled by ``scale`` (given in FP64 and applied to twice the run precision: 1/N is
   // inexact in binary when N has a factor 3, and a rounded scale would change the field energy by
   // the same factor on every inverse transform).
+  // (x_pass = false: ``scratch`` already holds the x-transformed spectra and ``in`` is not read)
   void inverse(const Batch<const cplx<T>*>& in, const Batch<cplx<T>*>& scratch, const Batch<T*>& out, int count,
-               double scale, hipStream_t s, const LineCenter<T>* lc = nullptr) const;
+               double scale, hipStream_t s, const LineCenter<T>* lc = nullptr, bool x_pass = true) const;
 };
 
 // ---------------------------------------------------------------- centering (centering.hip)

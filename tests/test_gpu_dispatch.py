@@ -129,3 +129,34 @@ def test_tile_sort_tables(shape, order):
     with pytest.raises(RuntimeError, match="out-of-range"):
         piclib.pic_sync(ctx.ctx)
     ctx.close()
+
+
+# every workgroup and tile shape of the fused x pass, and the first lengths past its last one
+FUSED = [("f32", (8, 288, 384)), ("f32", (96, 96, 96)), ("f32", (108, 96, 96)), ("f32", (216, 64, 64)),
+         ("f32", (432, 48, 48)), ("f32", (768, 36, 36)), ("f32", (864, 32, 36)),
+         ("f64", (8, 216, 256)), ("f64", (54, 96, 96)), ("f64", (108, 64, 72)), ("f64", (216, 48, 48)),
+         ("f64", (512, 32, 32)), ("f64", (576, 32, 32))]
+
+
+@pytest.mark.parametrize("dtype,shape,nodal", [(*c, False) for c in FUSED] + [("f32", (108, 96, 96), True),
+                                                                              ("f64", (216, 48, 48), True)])
+def test_field_solve_fused_along_x(dtype, shape, nodal):
+    """psatd_push_fields on grids large enough for the x pass, update and inverse x pass in one kernel."""
+    banner(f"psatd_push_fields fused along x dtype={dtype} shape={shape} nodal={nodal}")
+    p = ostep.Params(shape, (1.0, 1.0, 1.0), 0.5, 1, 8, 16, nodal=nodal)
+    ctx = piclib.Context(shape, (1.0, 1.0, 1.0), 0.5, 1, 8, 16, dtype,
+                         flags=piclib.PIC_NODAL_SOLVER if nodal else 0)
+    f = piclib.Fields(shape, dtype)
+    src = rounded(inputs.random_grid(shape, seed=3, count=11), dtype)
+    put(f.E_stag, src[0:3])
+    put(f.B_stag, src[3:6])
+    put(f.J_stag, src[6:9])
+    put([f.rho_old, f.rho_new], src[9:11])
+    piclib.psatd_push_fields(ctx.ctx, f)
+    piclib.pic_sync(ctx.ctx)
+    E, B = ostep.push_fields(src[0:3], src[3:6], src[6:9], src[9], src[10], p)
+    tol = 10 * 2 * np.log2(np.prod(shape)) * EPS[dtype] * 3
+    for d in range(3):
+        assert max_rel(np64(f.E_stag[d]), E[d]) <= tol, ("E", d)
+        assert max_rel(np64(f.B_stag[d]), B[d]) <= tol, ("B", d)
+    ctx.close()
