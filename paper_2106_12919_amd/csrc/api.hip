@@ -403,7 +403,7 @@ hipError_t build_engine(const pic_params& p, Engine<T>& e) {
   // the row layout of deposit_tiled (B x B x 16 per component) holds the node-major boxes
   // (B^3) of the staggered cycle's deposition too
   const size_t slot = (size_t)deposit_stage_slot(p.shape_order);
-  if ((err = e.alloc(&e.stage, (size_t)e.tiles.ntiles * 4 * slot)) != hipSuccess) return err;
+  if ((err = e.alloc(&e.stage, stage_slots(e.tiles) * 4 * slot)) != hipSuccess) return err;
   return hipStreamSynchronize(nullptr);  // everything cleared above, before any stream's use
 }
 
@@ -604,12 +604,13 @@ struct SourceSum {
     flag = e.spill_flag + (e.dep_k & 1u);
     return flag;
   }
-  ReduceArgs<T> reduce_args(bool with_j) {
+  ReduceArgs<T> reduce_args(bool with_j, int parts) {
     ReduceArgs<T> ra;
     ra.acc_mask = (rho_done ? 1 : 0) | (j_done ? 2 : 0);
     ra.base = rho_done ? nullptr : static_cast<const T*>(f->rho_static);
     for (int q = 0; q < 4; ++q) ra.spill[q] = e.spill[q];
-    ra.box_faces = e.box_faces;
+    ra.box_faces = parts > 1 ? nullptr : e.box_faces;
+    ra.parts = parts;
     ra.rows = 1;  // deposit_tiled's staging layout
     ra.flag = flag;
     ra.work = e.work;
@@ -699,10 +700,11 @@ pic_status do_deposit(pic_ctx c, const pic_species* sp, int nsp, pic_fields* f, 
     tile_sort(g, e.tiles, v.cell, v.n, e.t_counts, e.t_starts, e.t_cursor, perm, c->d_bad, c->stream);
     const bool mobile = std::isfinite(sp[s].m);
     int* flag = sum.begin();
+    const int parts = deposit_parts<T>(g, e.tiles, v.n);
     deposit_tiled<T>(g, e.tiles, v, perm, e.t_starts, with_j && mobile, e.stage, c->d_bad, nullptr, nullptr, e.work,
-                     sum.spill_rho(), sum.spill_j(), c->stream, flag, e.box_faces);
+                     sum.spill_rho(), sum.spill_j(), c->stream, flag, e.box_faces, nullptr, parts);
     deposit_reduce<T>(g, e.tiles, e.t_starts, e.stage, with_j && mobile, static_cast<T*>(f->rho_new), J, c->stream,
-                      sum.reduce_args(with_j && mobile));
+                      sum.reduce_args(with_j && mobile, parts));
   }
   sum.finish(c, with_j);
   return c->check("pic_deposit");
@@ -1125,6 +1127,7 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
       if (keep) {  // caller's order: every step visits the particles through a tile permutation
         const SpeciesView<T> v = view<T>(sp[q]);
         const bool mobile = std::isfinite(sp[q].m);
+        const int parts = deposit_parts<T>(g, e.tiles, v.n);
         {
           StageScope sc(c, ST_SORT);
           tile_sort(g, e.tiles, v.cell, v.n, x.counts[0], x.starts[0], x.cursor, x.perm, c->d_bad, c->stream);
@@ -1137,12 +1140,12 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
         {
           StageScope sc(c, ST_DEPOSIT);  // positions moved < 1 cell: the grouping still holds them
           deposit_tiled<T>(g, e.tiles, v, x.perm, x.starts[0], mobile, e.stage, c->d_bad, nullptr, nullptr, e.work,
-                           sum.spill_rho(), sum.spill_j(), c->stream, sum.begin(), e.box_faces);
+                           sum.spill_rho(), sum.spill_j(), c->stream, sum.begin(), e.box_faces, nullptr, parts);
         }
         {
           StageScope sc(c, ST_REDUCE);
           deposit_reduce<T>(g, e.tiles, x.starts[0], e.stage, mobile, static_cast<T*>(f->rho_new), Jn, c->stream,
-                            sum.reduce_args(mobile));
+                            sum.reduce_args(mobile, parts));
         }
         continue;
       }
@@ -1153,13 +1156,16 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
       // the deposition of the previous step has counted the tiles of the current cells.
       const int L = layout[q];
       const bool first = (n == 0);
+      // small grids: tiles in parts, whose regrouping reserves its runs by itself (no neighbour bases)
+      const int parts = deposit_parts<T>(g, e.tiles, cur.n);
       {
         StageScope sc(c, ST_SORT);
         if (first) {
           tile_sort(g, e.tiles, cur.cell, cur.n, x.counts[0], x.starts[0], x.cursor, x.perm, c->d_bad, c->stream);
         } else if (mobile) {
           scan_counts(e.tiles, x.counts[1 - L], x.starts[1 - L], x.cursor, c->stream);
-          neighbour_bases(e.tiles, x.starts[L], x.nbr, x.starts[1 - L], x.nbr_base, x.cursor, c->stream);
+          if (parts == 1)
+            neighbour_bases(e.tiles, x.starts[L], x.nbr, x.starts[1 - L], x.nbr_base, x.cursor, c->stream);
         }
       }
       const int* dep_starts = first ? x.starts[0] : (mobile ? x.starts[1 - L] : x.starts[L]);
@@ -1171,8 +1177,8 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
         else if (first)
           permute_species<T>(cur, alt, x.perm, c->stream);
         else if (mobile)
-          gather_push_tiled<T>(g, e.tiles, Enod, Bnod, cur, alt, nullptr, x.starts[L], true, x.cursor, x.nbr_base,
-                               c->stream, x.deal);
+          gather_push_tiled<T>(g, e.tiles, Enod, Bnod, cur, alt, nullptr, x.starts[L], true, x.cursor,
+                               parts == 1 ? x.nbr_base : nullptr, c->stream, x.deal);
       }
       const SpeciesView<T> dep = (first || mobile) ? alt : cur;  // immobile species stay put after the first step
       {
@@ -1181,13 +1187,13 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
         // last step counts nothing)
         int* nextc = mobile && n + 1 < nsteps ? x.counts[first ? 1 : L] : nullptr;
         deposit_tiled<T>(g, e.tiles, dep, nullptr, dep_starts, mobile, e.stage, c->d_bad, nextc,
-                         nextc ? x.nbr : nullptr, e.work, sum.spill_rho(), sum.spill_j(), c->stream, sum.begin(),
-                         e.box_faces, nextc ? x.deal : nullptr);
+                         nextc && parts == 1 ? x.nbr : nullptr, e.work, sum.spill_rho(), sum.spill_j(), c->stream,
+                         sum.begin(), e.box_faces, nextc ? x.deal : nullptr, parts);
       }
       {
         StageScope sc(c, ST_REDUCE);
         deposit_reduce<T>(g, e.tiles, dep_starts, e.stage, mobile, static_cast<T*>(f->rho_new), Jn, c->stream,
-                          sum.reduce_args(mobile));
+                          sum.reduce_args(mobile, parts));
       }
       if (first || mobile) in_scratch[q] = !in_scratch[q];
       // layout index of the grouping the particles are now in

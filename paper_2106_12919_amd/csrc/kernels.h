@@ -235,7 +235,17 @@ template <typename T>
 void deposit_tiled(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& sp, const int* perm, const int* starts,
                    bool with_j, T* stage, int* bad, int* next_counts, int* nbr_counts, int* work, T* rho,
                    T* const J[3], hipStream_t s, int* spill_flag = nullptr, int* box_faces = nullptr,
-                   unsigned short* deal = nullptr);
+                   unsigned short* deal = nullptr, int parts = 1);
+// Parts each tile of a species of n particles is best deposited in (1 on all but small grids): parts > 1
+// of deposit_tiled and ReduceArgs need stage room for ntiles * parts slots and no nbr_counts.
+constexpr int kMaxParts = 8;
+template <typename T>
+int deposit_parts(const GridGeom& g, const TileGeom& t, int64_t n);
+// Slots of the staging buffer a grid of t.ntiles tiles may use.
+inline size_t stage_slots(const TileGeom& t) {
+  const int fill = 512 / t.ntiles;
+  return (size_t)t.ntiles * (size_t)(fill < 1 ? 1 : fill > kMaxParts ? kMaxParts : fill);
+}
 // How deposit_reduce starts each node and what else it folds in.  By default it adds to the
 // nodal arrays.  With bit 0 (rho) or bit 1 (J) of acc_mask clear it overwrites them instead,
 // rho starting from ``base`` when given, else from zero.  When *flag != 0, the ``spill``
@@ -248,6 +258,7 @@ struct ReduceArgs {
   T* spill[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   const int* flag = nullptr;
   int* next_flag = nullptr;
+  int parts = 1;        // of the deposition (its box_faces are not used when > 1)
   int* work = nullptr;  // the deposition's tile counter, zeroed for the next one (optional)
   const int* box_faces = nullptr;  // per tile, the outer faces its deposition staged (null: all)
   // Staging layout: 0 = node-major boxes (B^3 per component); 1 = the zero-padded rows that

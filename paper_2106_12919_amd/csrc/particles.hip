@@ -10,6 +10,7 @@
 // Positions are an integer cell plus an offset in [0,1): the offset carries the
 // full precision of the dtype everywhere in the box.
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -587,10 +588,11 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_perm(G
   extern __shared__ __align__(16) unsigned char smem[];
   T* box = reinterpret_cast<T*>(smem);
   const int tile = xcd_major(blockIdx.x, gridDim.x);
-  const int beg = starts[tile], end = starts[tile + 1];
-  if (beg == end) return;
+  const int beg = starts[tile] + (int)(blockIdx.y * blockDim.x), end = starts[tile + 1];  // part blockIdx.y
+  const int step = (int)(gridDim.y * blockDim.x);
+  if (beg >= end) return;
   if (tile == tg.ntiles) {
-    for (int qq = beg + threadIdx.x; qq < end; qq += blockDim.x) {
+    for (int qq = beg + threadIdx.x; qq < end; qq += step) {
       const int p = perm[qq];
       copy_particle(in, p, out, write_sorted ? qq : p);
     }
@@ -601,7 +603,7 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_perm(G
   const int t0x = tx * kTile, t0y = ty * kTile, t0z = tz * kTile;
   load_field_box<T, ORDER, true, kGatherBlock<T, ORDER>>(box, F, g, t0x, t0y, t0z);
   __syncthreads();
-  for (int qq = beg + threadIdx.x; qq < end; qq += blockDim.x) {
+  for (int qq = beg + threadIdx.x; qq < end; qq += step) {
     const int p = perm[qq];
     const int wi = write_sorted ? qq : p;
     int i, j, k;
@@ -667,12 +669,15 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_home(G
   __shared__ int cnt[27];
   __shared__ int base[27];
   const int tile = xcd_major(blockIdx.x, gridDim.x);
-  const int beg = home[tile], end = home[tile + 1];
-  if (beg == end) return;
+  const int tbeg = home[tile], end = home[tile + 1];
+  const int beg = tbeg + (int)(blockIdx.y * blockDim.x);  // part blockIdx.y (of one, when nbr_bases are given)
+  const int step = (int)(gridDim.y * blockDim.x);
+  if (beg >= end) return;
   if (tile == tg.ntiles) {
-    if (threadIdx.x == 0) base[0] = atomicAdd(&cursor[tg.ntiles], end - beg);
+    if (blockIdx.y > 0) return;
+    if (threadIdx.x == 0) base[0] = atomicAdd(&cursor[tg.ntiles], end - tbeg);
     __syncthreads();
-    for (int qq = beg + threadIdx.x; qq < end; qq += blockDim.x) copy_particle(in, qq, out, base[0] + qq - beg);
+    for (int qq = tbeg + threadIdx.x; qq < end; qq += blockDim.x) copy_particle(in, qq, out, base[0] + qq - tbeg);
     return;
   }
   int tx, ty, tz;
@@ -684,13 +689,17 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_home(G
   }
   load_field_box<T, ORDER, true, kGatherBlock<T, ORDER>>(box, F, g, t0x, t0y, t0z);
   __syncthreads();
+  auto at = [&](int qq) {  // the particle at place qq of the dealt order
+    constexpr int CH = DepositOrder<T>::CH;
+    return (ORDER == 3 && deal) ? tbeg + ((qq - tbeg) & ~(CH - 1)) + deal[qq] : qq;
+  };
   if (!nbr_bases) {
     // pass 1: particles per neighbour tile of the new grouping (the home tile, the
     // common case, is counted once per wave), then one contiguous run per neighbour
     // tile, reserved with a single atomic each
-    for (int qq = beg + threadIdx.x; qq < end; qq += blockDim.x) {
+    for (int qq = beg + threadIdx.x; qq < end; qq += step) {
       int i, j, k;
-      (void)decode_cell(in.cell[qq], g, nullptr, i, j, k);
+      (void)decode_cell(in.cell[at(qq)], g, nullptr, i, j, k);
       const int nb = neighbour_of_cell(i, j, k, tx, ty, tz, tg);
       const unsigned long long own = __ballot(nb == 13);
       if (nb == 13) {
@@ -711,17 +720,13 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_home(G
   // loads in flight meanwhile.  They are issued after the slot is reserved: the rare
   // global reservation returns into the slot's register, and the wait for it would
   // otherwise also wait for the prefetch.
-  auto at = [&](int qq) {  // the particle at place qq of the dealt order
-    constexpr int CH = DepositOrder<T>::CH;
-    return (ORDER == 3 && deal) ? beg + ((qq - beg) & ~(CH - 1)) + deal[qq] : qq;
-  };
   Raw<T> nxt;
   int pn = 0;  // the particle after the one in ``nxt``
   if (beg + (int)threadIdx.x < end) {
     load_raw<T, true>(in, at(beg + threadIdx.x), nxt);
-    pn = at(min(beg + (int)threadIdx.x + (int)blockDim.x, end - 1));
+    pn = at(min(beg + (int)threadIdx.x + step, end - 1));
   }
-  for (int qq = beg + threadIdx.x; qq < end; qq += blockDim.x) {
+  for (int qq = beg + threadIdx.x; qq < end; qq += step) {
     const Raw<T> r = nxt;
     int i, j, k;
     (void)decode_cell(r.cell, g, nullptr, i, j, k);
@@ -739,7 +744,7 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_home(G
       slot = nb >= 0 ? base[nb] + atomicAdd(&cnt[nb], 1) : atomicAdd(&cursor[tile_of(i, j, k, tg)], 1);
     }
     load_raw<T, true>(in, pn, nxt);
-    pn = at(min(qq + 2 * (int)blockDim.x, end - 1));
+    pn = at(min(qq + 2 * step, end - 1));
     T ox = r.o[0], oy = r.o[1], oz = r.o[2];
     T ux = r.u[0], uy = r.u[1], uz = r.u[2];
     const int lx = box_index(i, t0x, g.nx), ly = box_index(j, t0y, g.ny), lz = box_index(k, t0z, g.nz);
@@ -1054,9 +1059,19 @@ struct DepositLds {
   int rowstart[O::RMAX];
 };
 
-// Deposition of one tile by the whole workgroup (see k_deposit_tiled).
+// How many of the ``parts`` a tile of len particles is split into hold particles, and the particles
+// per part (whole chunks, so that a part's chunks are the tile's).
+template <typename T>
+__device__ inline int tile_parts(int len, int parts, int& per) {
+  constexpr int CH = DepositOrder<T>::CH;
+  const int chunks = (len + CH - 1) / CH, cpp = (chunks + parts - 1) / parts;
+  per = cpp * CH;
+  return cpp > 0 ? (chunks + cpp - 1) / cpp : 0;
+}
+
+// Deposition of one tile (or of one of its parts) by the whole workgroup (see k_deposit_tiled).
 template <typename T, int ORDER, bool WJ>
-__device__ inline void deposit_tile(int tile, const GridGeom& g, const TileGeom& tg, const SpeciesView<T>& sp,
+__device__ inline void deposit_tile(int item, int parts, const GridGeom& g, const TileGeom& tg, const SpeciesView<T>& sp,
                                     const int* __restrict__ perm, const int* __restrict__ starts,
                                     const Batch<T*>& out, T* __restrict__ stage, T qdv, T hdtx, T hdty, T hdtz,
                                     int* bad, int* next_counts, int* nbr_counts, int* spill_flag, int* box_faces,
@@ -1078,11 +1093,19 @@ __device__ inline void deposit_tile(int tile, const GridGeom& g, const TileGeom&
   unsigned short* order = L.order;
   unsigned* rowmask = L.rowmask;
   int* rowstart = L.rowstart;
-  const int beg = starts[tile], end = starts[tile + 1];
+  const int tile = parts == 1 ? item : item / parts;  // (item ntiles * parts: the invalid cells)
+  int beg = starts[tile], end = starts[tile + 1];
   if (beg == end) return;
   if (tile == tg.ntiles) {  // invalid cells: never deposited, kept in the last bucket
     if (next_counts && threadIdx.x == 0) atomicAdd(&next_counts[tg.ntiles], end - beg);
     return;
+  }
+  if (parts > 1) {
+    int per;
+    (void)tile_parts<T>(end - beg, parts, per);
+    beg += (item - tile * parts) * per;
+    end = min(beg + per, end);
+    if (beg >= end) return;
   }
   int ti, tj, tk;
   tile_coords(tile, tg, ti, tj, tk);
@@ -1321,7 +1344,7 @@ __device__ inline void deposit_tile(int tile, const GridGeom& g, const TileGeom&
   // four consecutive positions of row it / 4, every component, zeros outside the box row
   using RL = StageRows<ORDER>;
   static_assert(RL::B == X::B, "stage rows match the box");
-  T* const dstage = stage + (size_t)tile * ncomp * RL::SLOT;
+  T* const dstage = stage + (size_t)item * ncomp * RL::SLOT;
   const int sh0 = -shs[0], sh1 = -shs[1], sh2 = -shs[2], sh3 = -shs[3];
   for (int it = threadIdx.x; it < X::B2 * (RL::PZ / 4); it += blockDim.x) {
     const int r = it >> 2, p0 = (it & 3) * 4;
@@ -1363,7 +1386,7 @@ __global__ void __launch_bounds__(PIC_DEPOSIT_BLOCK, sizeof(T) == 4 ? (ORDER == 
     k_deposit_tiled(GridGeom g, TileGeom tg, SpeciesView<T> sp, const int* __restrict__ perm,
                     const int* __restrict__ starts, Batch<T*> out, T* __restrict__ stage, T qdv, T hdtx, T hdty,
                     T hdtz, int* bad, int* next_counts, int* nbr_counts, int* work, int* spill_flag,
-                    int* box_faces, unsigned short* deal) {
+                    int* box_faces, unsigned short* deal, int parts) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ DepositLds<T> L;
   auto* box = reinterpret_cast<typename Fixed<T>::acc_t*>(smem);
@@ -1371,14 +1394,14 @@ __global__ void __launch_bounds__(PIC_DEPOSIT_BLOCK, sizeof(T) == 4 ? (ORDER == 
     for (;;) {
       if (threadIdx.x == 0) L.next_tile = atomicAdd(work, 1);
       __syncthreads();
-      const int tile = L.next_tile;
+      const int item = L.next_tile;
       __syncthreads();
-      if (tile > tg.ntiles) break;
-      deposit_tile<T, ORDER, WJ>(tile, g, tg, sp, perm, starts, out, stage, qdv, hdtx, hdty, hdtz, bad, next_counts,
+      if (item > tg.ntiles * parts) break;
+      deposit_tile<T, ORDER, WJ>(item, parts, g, tg, sp, perm, starts, out, stage, qdv, hdtx, hdty, hdtz, bad, next_counts,
                                  nbr_counts, spill_flag, box_faces, deal, box, L);
     }
   } else {
-    deposit_tile<T, ORDER, WJ>(blockIdx.x, g, tg, sp, perm, starts, out, stage, qdv, hdtx, hdty, hdtz, bad,
+    deposit_tile<T, ORDER, WJ>(blockIdx.x, parts, g, tg, sp, perm, starts, out, stage, qdv, hdtx, hdty, hdtz, bad,
                                next_counts, nbr_counts, spill_flag, box_faces, deal, box, L);
   }
 }
@@ -1490,16 +1513,19 @@ __global__ void __launch_bounds__(256) k_deposit_reduce_whole(GridGeom g, TileGe
 // tile tz = z0 / kTile and in the box of tz - 1 (first half of the tile) or of tz + 1 (second
 // half); along x and y the candidates are those of the node.  Grid (z blocks, ny, nx),
 // XCD-major.
-template <typename T, int ORDER, int NCOMP>
+template <typename T, int ORDER, int NCOMP, bool PARTS>
 __global__ void __launch_bounds__(256) k_deposit_reduce_rows(GridGeom g, TileGeom tg, const int* __restrict__ starts,
                                                              const T* __restrict__ stage, Batch<T*> out,
                                                              ReduceArgs<T> ra) {
   using RL = StageRows<ORDER>;
   static_assert(kTile == 8, "two groups of four nodes per tile along z");
   __shared__ unsigned char occ[4][kMaxTilesZ];
+  __shared__ unsigned char split[4][PARTS ? kMaxTilesZ : 1];  // parts of the tile that hold particles
   if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) ra.reset();
-  const int nzb = gridDim.x;
-  const int L = xcd_major(blockIdx.x + nzb * (blockIdx.y + gridDim.y * blockIdx.z), nzb * gridDim.y * gridDim.z);
+  // PARTS (small grids): one component per block, blockIdx.x = component + NCOMP x z block
+  const int q0 = PARTS ? (int)blockIdx.x % NCOMP : 0, q1 = PARTS ? q0 + 1 : NCOMP;
+  const int nzb = PARTS ? (int)gridDim.x / NCOMP : (int)gridDim.x, bx = PARTS ? (int)blockIdx.x / NCOMP : (int)blockIdx.x;
+  const int L = xcd_major(bx + nzb * (blockIdx.y + gridDim.y * blockIdx.z), nzb * gridDim.y * gridDim.z);
   const int z0 = 4 * ((L % nzb) * blockDim.x + threadIdx.x);
   const int y = (L / nzb) % g.ny, x = L / (nzb * g.ny);
   int tx[2], lx[2], ty[2], ly[2];
@@ -1512,6 +1538,10 @@ __global__ void __launch_bounds__(256) k_deposit_reduce_rows(GridGeom g, TileGeo
       const int tile = (tx[a] * tg.nty + ty[b]) * tg.ntz + t3;
       occ[ab][t3] = starts[tile] != starts[tile + 1] ? (unsigned char)(1 + 2 * (ra.box_faces ? ra.box_faces[tile] : 0x3F))
                                                      : (unsigned char)0;
+      if (PARTS) {
+        int per;
+        split[ab][t3] = (unsigned char)tile_parts<T>(starts[tile + 1] - starts[tile], ra.parts, per);
+      }
     }
   }
   __syncthreads();
@@ -1528,6 +1558,7 @@ __global__ void __launch_bounds__(256) k_deposit_reduce_rows(GridGeom g, TileGeo
   const size_t idx = ((size_t)x * g.ny + y) * g.nz + z0;
   bool use[8];
   const T* sb[8];
+  int np[8];
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
     const int a = m >> 2, b = (m >> 1) & 1, c = m & 1;
@@ -1539,13 +1570,14 @@ __global__ void __launch_bounds__(256) k_deposit_reduce_rows(GridGeom g, TileGeo
     const bool in = (lx[ia] > 0 || (f & 1)) && (lx[ia] < RL::B - 1 || (f & 8)) && (ly[ib] > 0 || (f & 2)) &&
                     (ly[ib] < RL::B - 1 || (f & 16));
     use[m] = present && (o & 1) && in;
-    sb[m] = stage + (size_t)tile * NCOMP * RL::SLOT + (lx[ia] * RL::B + ly[ib]) * RL::PZ + pz[c];
+    np[m] = PARTS && use[m] ? split[2 * ia + ib][tz[c]] : 1;
+    sb[m] = stage + (size_t)tile * (PARTS ? ra.parts : 1) * NCOMP * RL::SLOT + (lx[ia] * RL::B + ly[ib]) * RL::PZ + pz[c];
   }
   const bool spilled = ra.flag && *ra.flag;
   // one component at a time (its eight vectors in flight together); the empty asm keeps the
   // compiler from hoisting the next component's loads, which would multiply the registers held
 #pragma unroll
-  for (int q = 0; q < NCOMP; ++q) {
+  for (int q = q0; q < q1; ++q) {
     T acc[4], v[8][4];
     if (ra.acc_mask & (q == 0 ? 1 : 2)) load4(out.p[q] + idx, acc);
     else if (q == 0 && ra.base) load4(ra.base + idx, acc);
@@ -1563,6 +1595,21 @@ __global__ void __launch_bounds__(256) k_deposit_reduce_rows(GridGeom g, TileGeo
     for (int m = 0; m < 8; ++m)
 #pragma unroll
       for (int i = 0; i < 4; ++i) acc[i] += v[m][i];
+    if (PARTS) {
+      for (int p = 1; p < ra.parts; ++p) {  // the eight boxes' part p in flight together
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+          if (p < np[m]) load4(sb[m] + ((size_t)p * NCOMP + q) * RL::SLOT, v[m]);
+          else
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[m][i] = (T)0;
+        }
+#pragma unroll
+        for (int m = 0; m < 8; ++m)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[i] += v[m][i];
+      }
+    }
     if (spilled)
 #pragma unroll
       for (int i = 0; i < 4; ++i) acc[i] += ra.take_spill(q, idx + i);
@@ -1623,8 +1670,11 @@ __global__ void __launch_bounds__(256) k_deposit_reduce(GridGeom g, TileGeom tg,
           if (starts[tile] == starts[tile + 1]) continue;
           const int slot = ra.rows ? StageRows<ORDER>::SLOT : X::B3;
           const int at = ra.rows ? StageRows<ORDER>::at(clx[a], cly[b], clz[c]) : X::at(clx[a], cly[b], clz[c]);
-          const T* sb = stage + (size_t)tile * ncomp * slot + at;
-          for (int q = 0; q < ncomp; ++q) acc[q] += sb[(size_t)q * slot];
+          const T* sb = stage + (size_t)tile * ra.parts * ncomp * slot + at;
+          int per;
+          const int np = ra.parts > 1 ? tile_parts<T>(starts[tile + 1] - starts[tile], ra.parts, per) : 1;
+          for (int p = 0; p < np; ++p)
+            for (int q = 0; q < ncomp; ++q) acc[q] += sb[(size_t)(p * ncomp + q) * slot];
         }
     for (int q = 0; q < ncomp; ++q) out.p[q][idx] = ra.start(q, out.p[q], idx) + acc[q] + (spilled ? ra.take_spill(q, idx) : (T)0);
   }
@@ -2432,6 +2482,19 @@ void allow_lds(const void* kernel, size_t bytes) {
 
 int deposit_box(int shape_order) { return kTile + (shape_order == 1 ? 2 : 4) + 1; }
 int deposit_stage_slot(int shape_order) { return shape_order == 1 ? StageRows<1>::SLOT : StageRows<3>::SLOT; }
+// Workgroups per tile on grids of few tiles: as many as fill the device twice, as long as each has
+// ``least`` particles on average, at most kMaxParts.  One workgroup per tile leaves most compute units idle
+// there: 32^3 (64 tiles), 8 per cell, linear, FP64: deposition 110 -> 29 us, gather 42 -> 16 (reduction 9 ->
+// 24: it sums the parts); the whole call of one step 208 -> 172; cubic FP32, 5 steps 1414 -> 683.
+int tile_parts_for(const TileGeom& t, int64_t n, int least) {
+  const int64_t fill = 512 / t.ntiles, have = n / ((int64_t)t.ntiles * least);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(std::min(fill, have), kMaxParts));
+}
+template <typename T>
+int deposit_parts(const GridGeom& g, const TileGeom& t, int64_t n) {
+  if (g.det) return 1;  // a part's scale would depend on which of the tile's particles it holds
+  return tile_parts_for(t, n, DepositOrder<T>::CH);
+}
 template <typename T>
 void gather_push_tiled(const GridGeom& g, const TileGeom& t, const T* const E[3], const T* const B[3],
                        const SpeciesView<T>& in, const SpeciesView<T>& out, const int* perm, const int* starts,
@@ -2447,8 +2510,11 @@ void gather_push_tiled(const GridGeom& g, const TileGeom& t, const T* const E[3]
   const T dtx = (T)(g.dt / g.dx), dty = (T)(g.dt / g.dy), dtz = (T)(g.dt / g.dz);
   const int Bx = deposit_box(g.shape_order);
   const size_t lds = (size_t)Bx * Bx * Bx * GatherBox<T, 1>::SLOTS * sizeof(T);
-  const dim3 grid(t.ntiles + 1);
   const dim3 block(g.shape_order == 1 ? kGatherBlock<T, 1> : kGatherBlock<T, 3>);
+  // few tiles: several workgroups per tile, each with the tile's field box (not with nbr_bases, whose runs
+  // one workgroup fills)
+  const int parts = nbr_bases ? 1 : tile_parts_for(t, in.n, (int)block.x);
+  const dim3 grid(t.ntiles + 1, parts);
   if (home_cursor) {
     if (g.shape_order == 1) {
       allow_lds((const void*)k_gather_push_home<T, 1>, lds);
@@ -2488,14 +2554,14 @@ int resident_blocks(const void* kernel, int block, size_t lds) {
 template <typename T, int ORDER, bool WJ>
 void launch_deposit(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& sp, const int* perm, const int* starts,
                     T* stage, int* bad, int* next_counts, int* nbr_counts, int* work, int* spill_flag,
-                    int* box_faces, unsigned short* deal, const Batch<T*>& out, hipStream_t s) {
+                    int* box_faces, unsigned short* deal, int parts, const Batch<T*>& out, hipStream_t s) {
   const T qdv = (T)(sp.q / (g.dx * g.dy * g.dz));
   const T hx = (T)(0.5 * g.dt / g.dx), hy = (T)(0.5 * g.dt / g.dy), hz = (T)(0.5 * g.dt / g.dz);
   constexpr int B = Box<Shape<T, ORDER>::NW>::B;
   const size_t lds = (size_t)(WJ ? 4 : 1) * B * B * B * sizeof(typename Fixed<T>::acc_t);
   const void* k = (const void*)k_deposit_tiled<T, ORDER, WJ>;
   allow_lds(k, lds);
-  int nb = t.ntiles + 1;
+  int nb = t.ntiles * parts + 1;
   if (ORDER == 3) {  // persistent launch (see k_deposit_tiled)
     static int resident = 0;  // per instantiation; the device's occupancy does not change
     if (resident == 0) resident = resident_blocks(k, PIC_DEPOSIT_BLOCK, lds);
@@ -2503,25 +2569,25 @@ void launch_deposit(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& 
   }
   hipLaunchKernelGGL((k_deposit_tiled<T, ORDER, WJ>), dim3(nb), dim3(PIC_DEPOSIT_BLOCK), lds, s, g, t, sp, perm,
                      starts, out, stage, qdv, hx, hy, hz, bad, next_counts, nbr_counts, work, spill_flag, box_faces,
-                     deal);
+                     deal, parts);
 }
 
 template <typename T>
 void deposit_tiled(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& sp, const int* perm, const int* starts,
                    bool with_j, T* stage, int* bad, int* next_counts, int* nbr_counts, int* work, T* rho,
-                   T* const J[3], hipStream_t s, int* spill_flag, int* box_faces, unsigned short* deal) {
+                   T* const J[3], hipStream_t s, int* spill_flag, int* box_faces, unsigned short* deal, int parts) {
   if (sp.n <= 0) return;
-  // the face masks serve the whole-tile reduction only; the other one reads whole boxes
-  if (!(g.nx % kTile == 0 && g.ny % kTile == 0 && g.nz % kTile == 0)) box_faces = nullptr;
+  // the face masks serve the whole-tile reduction of unsplit tiles only; the others read whole boxes
+  if (parts > 1 || !(g.nx % kTile == 0 && g.ny % kTile == 0 && g.nz % kTile == 0)) box_faces = nullptr;
   Batch<T*> out{};
   out.p[0] = rho;
   for (int d = 0; d < 3; ++d) out.p[1 + d] = J ? J[d] : nullptr;
   if (g.shape_order == 1) {
-    if (with_j) launch_deposit<T, 1, true>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, deal, out, s);
-    else launch_deposit<T, 1, false>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, deal, out, s);
+    if (with_j) launch_deposit<T, 1, true>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, deal, parts, out, s);
+    else launch_deposit<T, 1, false>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, deal, parts, out, s);
   } else {
-    if (with_j) launch_deposit<T, 3, true>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, deal, out, s);
-    else launch_deposit<T, 3, false>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, deal, out, s);
+    if (with_j) launch_deposit<T, 3, true>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, deal, parts, out, s);
+    else launch_deposit<T, 3, false>(g, t, sp, perm, starts, stage, bad, next_counts, nbr_counts, work, spill_flag, box_faces, deal, parts, out, s);
   }
 }
 
@@ -2535,14 +2601,20 @@ void deposit_reduce(const GridGeom& g, const TileGeom& t, const int* starts, con
   if (ra.rows && g.nx % kTile == 0 && g.ny % kTile == 0 && g.nz % kTile == 0) {
     const int groups = g.nz / 4;
     const unsigned bz = (unsigned)std::min(256, (groups + 63) / 64 * 64);
-    const dim3 grid((unsigned)((groups + bz - 1) / bz), (unsigned)g.ny, (unsigned)g.nx);
-    if (g.shape_order == 1) {
-      if (with_j) hipLaunchKernelGGL((k_deposit_reduce_rows<T, 1, 4>), grid, dim3(bz), 0, s, g, t, starts, stage, out, ra);
-      else hipLaunchKernelGGL((k_deposit_reduce_rows<T, 1, 1>), grid, dim3(bz), 0, s, g, t, starts, stage, out, ra);
-    } else {
-      if (with_j) hipLaunchKernelGGL((k_deposit_reduce_rows<T, 3, 4>), grid, dim3(bz), 0, s, g, t, starts, stage, out, ra);
-      else hipLaunchKernelGGL((k_deposit_reduce_rows<T, 3, 1>), grid, dim3(bz), 0, s, g, t, starts, stage, out, ra);
-    }
+    const dim3 blocks((unsigned)((groups + bz - 1) / bz), (unsigned)g.ny, (unsigned)g.nx);
+    auto launch = [&](auto parts) {
+      constexpr bool P = decltype(parts)::value;
+      const dim3 grid(blocks.x * (P ? ncomp : 1), blocks.y, blocks.z);
+      if (g.shape_order == 1) {
+        if (with_j) hipLaunchKernelGGL((k_deposit_reduce_rows<T, 1, 4, P>), grid, dim3(bz), 0, s, g, t, starts, stage, out, ra);
+        else hipLaunchKernelGGL((k_deposit_reduce_rows<T, 1, 1, P>), grid, dim3(bz), 0, s, g, t, starts, stage, out, ra);
+      } else {
+        if (with_j) hipLaunchKernelGGL((k_deposit_reduce_rows<T, 3, 4, P>), grid, dim3(bz), 0, s, g, t, starts, stage, out, ra);
+        else hipLaunchKernelGGL((k_deposit_reduce_rows<T, 3, 1, P>), grid, dim3(bz), 0, s, g, t, starts, stage, out, ra);
+      }
+    };
+    if (ra.parts > 1) launch(std::true_type{});
+    else launch(std::false_type{});
     return;
   }
   if (g.nx % kTile == 0 && g.ny % kTile == 0 && g.nz % kTile == 0) {
@@ -2724,10 +2796,11 @@ void deposit_yee(const GridGeom& g, const SpeciesView<T>& sp, bool with_j, T* rh
 }
 
 #define PIC_INST(T)                                                                                              \
+  template int deposit_parts<T>(const GridGeom&, const TileGeom&, int64_t);                                      \
   template void permute_species<T>(const SpeciesView<T>&, const SpeciesView<T>&, const int*, hipStream_t);       \
   template void deposit_tiled<T>(const GridGeom&, const TileGeom&, const SpeciesView<T>&, const int*, const int*, \
                                  bool, T*, int*, int*, int*, int*, T*, T* const*, hipStream_t, int*, int*,       \
-                                 unsigned short*);                                                               \
+                                 unsigned short*, int);                                                          \
   template void deposit_reduce<T>(const GridGeom&, const TileGeom&, const int*, const T*, bool, T*, T* const*,   \
                                   hipStream_t, const ReduceArgs<T>&);                                            \
   template void gather_push_tiled<T>(const GridGeom&, const TileGeom&, const T* const*, const T* const*,         \

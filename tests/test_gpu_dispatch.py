@@ -160,3 +160,14 @@ def test_field_solve_fused_along_x(dtype, shape, nodal):
         assert max_rel(np64(f.E_stag[d]), E[d]) <= tol, ("E", d)
         assert max_rel(np64(f.B_stag[d]), B[d]) <= tol, ("B", d)
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("shape,ppc,order", [((16, 16, 16), 7, 1), ((16, 16, 16), 5, 3), ((12, 18, 24), 6, 1),
+                                             ((8, 8, 16), 9, 3)])
+@pytest.mark.parametrize("flags", [0, piclib.PIC_KEEP_ORDER])
+def test_few_tiles_in_parts(dtype, shape, ppc, order, flags):
+    """Grids of few tiles: each tile is deposited and gathered in parts by several workgroups, the last part
+    of a tile holding fewer chunks than the others or none; grouped and in the caller's order."""
+    banner(f"pic_step 3 steps, few tiles dtype={dtype} shape={shape} ppc={ppc} order={order} flags={flags}")
+    steps_against_oracle(shape, ppc, order, 8, dtype, 3, flags=flags)
