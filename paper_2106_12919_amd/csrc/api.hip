@@ -177,7 +177,7 @@ struct Engine : EngineBase {
   // say whether a deposition spilled, and the count of depositions that chose between them
   T* spill[4] = {nullptr, nullptr, nullptr, nullptr};
   int* spill_flag = nullptr;
-  int* box_faces = nullptr;  // per tile, the outer faces of its deposition box that were staged
+  int* box_faces = nullptr;  // per tile, the outer faces of its deposition box that were staged (split tiles: 4 scales)
   unsigned dep_k = 0;
   std::vector<SpeciesScratch<T>> sps;
   cplx<T>* Eh[3] = {nullptr, nullptr, nullptr};
@@ -393,7 +393,7 @@ hipError_t build_engine(const pic_params& p, Engine<T>& e) {
   const GridGeom g = make_geom(p.nx, p.ny, p.nz, p.dx, p.dy, p.dz, p.dt, p.shape_order);
   e.tiles = make_tiles(g);
   if ((err = e.alloc(&e.tiles.scan_tmp, (size_t)(e.tiles.ntiles + 1) / 8192 + 2)) != hipSuccess) return err;
-  if ((err = e.alloc(&e.box_faces, (size_t)e.tiles.ntiles)) != hipSuccess) return err;
+  if ((err = e.alloc(&e.box_faces, 4 * (size_t)e.tiles.ntiles)) != hipSuccess) return err;
   if ((err = e.alloc(&e.t_counts, (size_t)e.tiles.ntiles + 1)) != hipSuccess) return err;
   if ((err = e.alloc(&e.t_starts, (size_t)e.tiles.ntiles + 2)) != hipSuccess) return err;
   if ((err = e.alloc(&e.t_cursor, (size_t)e.tiles.ntiles + 1)) != hipSuccess) return err;
@@ -609,7 +609,7 @@ struct SourceSum {
     ra.acc_mask = (rho_done ? 1 : 0) | (j_done ? 2 : 0);
     ra.base = rho_done ? nullptr : static_cast<const T*>(f->rho_static);
     for (int q = 0; q < 4; ++q) ra.spill[q] = e.spill[q];
-    ra.box_faces = parts > 1 ? nullptr : e.box_faces;
+    ra.box_faces = e.box_faces;
     ra.parts = parts;
     ra.rows = 1;  // deposit_tiled's staging layout
     ra.flag = flag;
@@ -700,7 +700,7 @@ pic_status do_deposit(pic_ctx c, const pic_species* sp, int nsp, pic_fields* f, 
     tile_sort(g, e.tiles, v.cell, v.n, e.t_counts, e.t_starts, e.t_cursor, perm, c->d_bad, c->stream);
     const bool mobile = std::isfinite(sp[s].m);
     int* flag = sum.begin();
-    const int parts = deposit_parts<T>(g, e.tiles, v.n);
+    const int parts = deposit_parts<T>(e.tiles, v.n);
     deposit_tiled<T>(g, e.tiles, v, perm, e.t_starts, with_j && mobile, e.stage, c->d_bad, nullptr, nullptr, e.work,
                      sum.spill_rho(), sum.spill_j(), c->stream, flag, e.box_faces, nullptr, parts);
     deposit_reduce<T>(g, e.tiles, e.t_starts, e.stage, with_j && mobile, static_cast<T*>(f->rho_new), J, c->stream,
@@ -1127,7 +1127,7 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
       if (keep) {  // caller's order: every step visits the particles through a tile permutation
         const SpeciesView<T> v = view<T>(sp[q]);
         const bool mobile = std::isfinite(sp[q].m);
-        const int parts = deposit_parts<T>(g, e.tiles, v.n);
+        const int parts = deposit_parts<T>(e.tiles, v.n);
         {
           StageScope sc(c, ST_SORT);
           tile_sort(g, e.tiles, v.cell, v.n, x.counts[0], x.starts[0], x.cursor, x.perm, c->d_bad, c->stream);
@@ -1157,7 +1157,7 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
       const int L = layout[q];
       const bool first = (n == 0);
       // small grids: tiles in parts, whose regrouping reserves its runs by itself (no neighbour bases)
-      const int parts = deposit_parts<T>(g, e.tiles, cur.n);
+      const int parts = deposit_parts<T>(e.tiles, cur.n);
       {
         StageScope sc(c, ST_SORT);
         if (first) {

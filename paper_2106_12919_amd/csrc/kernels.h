@@ -236,11 +236,12 @@ void deposit_tiled(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& s
                    bool with_j, T* stage, int* bad, int* next_counts, int* nbr_counts, int* work, T* rho,
                    T* const J[3], hipStream_t s, int* spill_flag = nullptr, int* box_faces = nullptr,
                    unsigned short* deal = nullptr, int parts = 1);
-// Parts each tile of a species of n particles is best deposited in (1 on all but small grids): parts > 1
-// of deposit_tiled and ReduceArgs need stage room for ntiles * parts slots and no nbr_counts.
+// Parts each tile of a species of n particles is best deposited in (1 on all but small grids).  With parts > 1
+// deposit_tiled stages each part's integers in a slot of its own (room for ntiles * parts), writes the tiles'
+// scales (4 ntiles ints) to box_faces and takes no nbr_counts; ReduceArgs::parts says so to deposit_reduce.
 constexpr int kMaxParts = 8;
 template <typename T>
-int deposit_parts(const GridGeom& g, const TileGeom& t, int64_t n);
+int deposit_parts(const TileGeom& t, int64_t n);
 // Slots of the staging buffer a grid of t.ntiles tiles may use.
 inline size_t stage_slots(const TileGeom& t) {
   const int fill = 512 / t.ntiles;
@@ -258,7 +259,7 @@ struct ReduceArgs {
   T* spill[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   const int* flag = nullptr;
   int* next_flag = nullptr;
-  int parts = 1;        // of the deposition (its box_faces are not used when > 1)
+  int parts = 1;        // of the deposition; when > 1 the slots hold integers and box_faces the tiles' scales
   int* work = nullptr;  // the deposition's tile counter, zeroed for the next one (optional)
   const int* box_faces = nullptr;  // per tile, the outer faces its deposition staged (null: all)
   // Staging layout: 0 = node-major boxes (B^3 per component); 1 = the zero-padded rows that

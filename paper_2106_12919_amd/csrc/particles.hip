@@ -820,6 +820,9 @@ struct Fixed<float> {
     return __float_as_int(fmaf(a, b, 12582912.0f)) - 0x4B400000;
   }
   __device__ static inline void add(acc_t* a, acc_t v) { atomicAdd(a, v); }
+  // an accumulator as the bits of a T and back (the staging slots of split tiles)
+  __device__ static inline float bits(acc_t v) { return __int_as_float(v); }
+  __device__ static inline acc_t value(float v) { return __float_as_int(v); }
 };
 
 template <>
@@ -833,6 +836,8 @@ struct Fixed<double> {
   __device__ static inline void add(acc_t* a, acc_t v) {
     atomicAdd(reinterpret_cast<unsigned long long*>(a), (unsigned long long)v);
   }
+  __device__ static inline double bits(acc_t v) { return __longlong_as_double(v); }
+  __device__ static inline acc_t value(double v) { return __double_as_longlong(v); }
 };
 
 // Largest single-node weight of the 3D shape: 1 (linear) and (2/3)^3 (cubic).
@@ -1100,11 +1105,14 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
     if (next_counts && threadIdx.x == 0) atomicAdd(&next_counts[tg.ntiles], end - beg);
     return;
   }
+  // the tile's range; a part deposits [beg, end) of it with the scales of the whole tile, so that the
+  // parts' integer sums add up to the tile's whatever particles each holds
+  const int tbeg = beg, tend = end;
   if (parts > 1) {
     int per;
-    (void)tile_parts<T>(end - beg, parts, per);
+    (void)tile_parts<T>(tend - tbeg, parts, per);
     beg += (item - tile * parts) * per;
-    end = min(beg + per, end);
+    end = min(beg + per, tend);
     if (beg >= end) return;
   }
   int ti, tj, tk;
@@ -1116,7 +1124,7 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
   // MaxWeight times the tile's sum of those magnitudes (< 2^e_sum), every contribution
   // by their max (< 2^e_max).  A tile of one chunk takes the bounds in the chunk's
   // first pass; a larger one in a pass of its own.
-  const bool single = end - beg <= O::CH;
+  const bool single = parts == 1 && tend - tbeg <= O::CH;
   T sw[4] = {0, 0, 0, 0}, mw[4] = {0, 0, 0, 0};
   auto publish_bounds = [&]() {  // wave partials -> red / redm
 #pragma unroll
@@ -1139,19 +1147,19 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
         m += red[c * kWaves + w];
         x = fmax(x, redm[c * kWaves + w]);
       }
-      if (g.det) m = x * (T)(end - beg);  // order-independent bound (see GridGeom::det)
+      if (g.det) m = x * (T)(tend - tbeg);  // order-independent bound (see GridGeom::det)
       // a little slack on the bound covers the rounding of the FP sum itself
       int e_sum = 0, e_max = 0;
       (void)frexp(m * fabs(qdv) * (T)(MaxWeight<ORDER>::value * 1.001), &e_sum);
       (void)frexp(x * fabs(qdv) * (T)1.001, &e_max);
-      shs[c] = Fixed<T>::shift(e_sum, e_max, 32 - __clz(end - beg));
+      shs[c] = Fixed<T>::shift(e_sum, e_max, 32 - __clz(tend - tbeg));
     }
   };
   if (!single) {
-    for (int q0 = beg + threadIdx.x; q0 < end; q0 += O::U * PIC_DEPOSIT_BLOCK) {
+    for (int q0 = tbeg + threadIdx.x; q0 < tend; q0 += O::U * PIC_DEPOSIT_BLOCK) {
       int qi[O::U];
 #pragma unroll
-      for (int u = 0; u < O::U; ++u) qi[u] = min(q0 + u * PIC_DEPOSIT_BLOCK, end - 1);
+      for (int u = 0; u < O::U; ++u) qi[u] = min(q0 + u * PIC_DEPOSIT_BLOCK, tend - 1);
       through_perm(perm, qi);
       Raw<T> r[O::U];
 #pragma unroll
@@ -1160,7 +1168,7 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
       }
 #pragma unroll
       for (int u = 0; u < O::U; ++u)
-        if (q0 + u * PIC_DEPOSIT_BLOCK < end) bound_add<T, WJ>(r[u], sw, mw);
+        if (q0 + u * PIC_DEPOSIT_BLOCK < tend) bound_add<T, WJ>(r[u], sw, mw);
     }
     publish_bounds();
     __syncthreads();
@@ -1314,7 +1322,7 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
   // layer 0, then at layer B - 1) is set when face f does, and the reduction reads nothing
   // outside.  z rows are always staged whole (their ends share memory sectors with the rest).
   int faces = 0x3F;
-  if (box_faces) {
+  if (box_faces && parts == 1) {
     int mine = 4 | 32;  // faces this thread found nonzero, then OR-reduced over the wave: one atomic per wave
     for (int e = threadIdx.x; e < 4 * X::B2; e += blockDim.x) {
       const int k = e / X::B2, uv = e - k * X::B2, u = uv / X::B, v = uv - u * X::B;
@@ -1345,6 +1353,33 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
   using RL = StageRows<ORDER>;
   static_assert(RL::B == X::B, "stage rows match the box");
   T* const dstage = stage + (size_t)item * ncomp * RL::SLOT;
+  if (parts > 1) {  // the integers themselves, whole boxes; the tile's scales go to box_faces
+    if (item == tile * parts && threadIdx.x < ncomp) box_faces[4 * tile + threadIdx.x] = shs[threadIdx.x];
+    for (int it = threadIdx.x; it < X::B2 * (RL::PZ / 4); it += blockDim.x) {
+      const int r = it >> 2, p0 = (it & 3) * 4;
+      T v[4][4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int lz = p0 + i - RL::OFF;
+        const bool in = lz >= 0 && lz < X::B;
+        const int n = r * X::B + (in ? lz : 0);
+        v[0][i] = Fixed<T>::bits(in ? rbox[n] : 0);
+        if constexpr (PACK) {
+          int jx, jy;
+          unpack_xy(reinterpret_cast<const unsigned long long*>(box)[n], jx, jy);
+          v[1][i] = Fixed<T>::bits(in ? jx : 0);
+          v[2][i] = Fixed<T>::bits(in ? jy : 0);
+          v[3][i] = Fixed<T>::bits(in ? box[2 * X::B3 + n] : 0);
+        } else if (WJ) {
+#pragma unroll
+          for (int q = 1; q < 4; ++q) v[q][i] = Fixed<T>::bits(in ? box[q * X::B3 + n] : 0);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < ncomp; ++q) store4(dstage + r * RL::PZ + p0 + q * RL::SLOT, v[q]);
+    }
+    return;
+  }
   const int sh0 = -shs[0], sh1 = -shs[1], sh2 = -shs[2], sh3 = -shs[3];
   for (int it = threadIdx.x; it < X::B2 * (RL::PZ / 4); it += blockDim.x) {
     const int r = it >> 2, p0 = (it & 3) * 4;
@@ -1536,7 +1571,7 @@ __global__ void __launch_bounds__(256) k_deposit_reduce_rows(GridGeom g, TileGeo
     const int a = ab >> 1, b = ab & 1;
     if (a < nxc && b < nyc) {
       const int tile = (tx[a] * tg.nty + ty[b]) * tg.ntz + t3;
-      occ[ab][t3] = starts[tile] != starts[tile + 1] ? (unsigned char)(1 + 2 * (ra.box_faces ? ra.box_faces[tile] : 0x3F))
+      occ[ab][t3] = starts[tile] != starts[tile + 1] ? (unsigned char)(1 + 2 * (!PARTS && ra.box_faces ? ra.box_faces[tile] : 0x3F))
                                                      : (unsigned char)0;
       if (PARTS) {
         int per;
@@ -1558,7 +1593,7 @@ __global__ void __launch_bounds__(256) k_deposit_reduce_rows(GridGeom g, TileGeo
   const size_t idx = ((size_t)x * g.ny + y) * g.nz + z0;
   bool use[8];
   const T* sb[8];
-  int np[8];
+  int np[8], tl[8];
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
     const int a = m >> 2, b = (m >> 1) & 1, c = m & 1;
@@ -1570,6 +1605,7 @@ __global__ void __launch_bounds__(256) k_deposit_reduce_rows(GridGeom g, TileGeo
     const bool in = (lx[ia] > 0 || (f & 1)) && (lx[ia] < RL::B - 1 || (f & 8)) && (ly[ib] > 0 || (f & 2)) &&
                     (ly[ib] < RL::B - 1 || (f & 16));
     use[m] = present && (o & 1) && in;
+    tl[m] = tile;
     np[m] = PARTS && use[m] ? split[2 * ia + ib][tz[c]] : 1;
     sb[m] = stage + (size_t)tile * (PARTS ? ra.parts : 1) * NCOMP * RL::SLOT + (lx[ia] * RL::B + ly[ib]) * RL::PZ + pz[c];
   }
@@ -1584,31 +1620,39 @@ __global__ void __launch_bounds__(256) k_deposit_reduce_rows(GridGeom g, TileGeo
     else
 #pragma unroll
       for (int i = 0; i < 4; ++i) acc[i] = (T)0;
-#pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      if (use[m]) load4(sb[m] + (size_t)q * RL::SLOT, v[m]);
-      else
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[m][i] = (T)0;
-    }
-#pragma unroll
-    for (int m = 0; m < 8; ++m)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] += v[m][i];
-    if (PARTS) {
-      for (int p = 1; p < ra.parts; ++p) {  // the eight boxes' part p in flight together
+    if (PARTS) {  // the parts' integers summed, then converted with the tile's scale
+      typename Fixed<T>::acc_t sum[8][4];
+      for (int p = 0; p < ra.parts; ++p) {  // the eight boxes' part p in flight together
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
-          if (p < np[m]) load4(sb[m] + ((size_t)p * NCOMP + q) * RL::SLOT, v[m]);
+          if (use[m] && p < np[m]) load4(sb[m] + ((size_t)p * NCOMP + q) * RL::SLOT, v[m]);
           else
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v[m][i] = (T)0;
+            for (int i = 0; i < 4; ++i) v[m][i] = Fixed<T>::bits(0);
         }
 #pragma unroll
         for (int m = 0; m < 8; ++m)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) acc[i] += v[m][i];
+          for (int i = 0; i < 4; ++i) sum[m][i] = (p == 0 ? 0 : sum[m][i]) + Fixed<T>::value(v[m][i]);
       }
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const int sh = use[m] ? -ra.box_faces[4 * tl[m] + q] : 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] += ldexp((T)sum[m][i], sh);
+      }
+    } else {
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        if (use[m]) load4(sb[m] + (size_t)q * RL::SLOT, v[m]);
+        else
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[m][i] = (T)0;
+      }
+#pragma unroll
+      for (int m = 0; m < 8; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] += v[m][i];
     }
     if (spilled)
 #pragma unroll
@@ -1671,10 +1715,17 @@ __global__ void __launch_bounds__(256) k_deposit_reduce(GridGeom g, TileGeom tg,
           const int slot = ra.rows ? StageRows<ORDER>::SLOT : X::B3;
           const int at = ra.rows ? StageRows<ORDER>::at(clx[a], cly[b], clz[c]) : X::at(clx[a], cly[b], clz[c]);
           const T* sb = stage + (size_t)tile * ra.parts * ncomp * slot + at;
-          int per;
-          const int np = ra.parts > 1 ? tile_parts<T>(starts[tile + 1] - starts[tile], ra.parts, per) : 1;
-          for (int p = 0; p < np; ++p)
-            for (int q = 0; q < ncomp; ++q) acc[q] += sb[(size_t)(p * ncomp + q) * slot];
+          if (ra.parts > 1) {  // the parts' integers summed, then converted with the tile's scale
+            int per;
+            const int np = tile_parts<T>(starts[tile + 1] - starts[tile], ra.parts, per);
+            for (int q = 0; q < ncomp; ++q) {
+              typename Fixed<T>::acc_t sum = 0;
+              for (int p = 0; p < np; ++p) sum += Fixed<T>::value(sb[(size_t)(p * ncomp + q) * slot]);
+              acc[q] += ldexp((T)sum, -ra.box_faces[4 * tile + q]);
+            }
+          } else {
+            for (int q = 0; q < ncomp; ++q) acc[q] += sb[(size_t)q * slot];
+          }
         }
     for (int q = 0; q < ncomp; ++q) out.p[q][idx] = ra.start(q, out.p[q], idx) + acc[q] + (spilled ? ra.take_spill(q, idx) : (T)0);
   }
@@ -2485,14 +2536,13 @@ int deposit_stage_slot(int shape_order) { return shape_order == 1 ? StageRows<1>
 // Workgroups per tile on grids of few tiles: as many as fill the device twice, as long as each has
 // ``least`` particles on average, at most kMaxParts.  One workgroup per tile leaves most compute units idle
 // there: 32^3 (64 tiles), 8 per cell, linear, FP64: deposition 110 -> 29 us, gather 42 -> 16 (reduction 9 ->
-// 24: it sums the parts); the whole call of one step 208 -> 172; cubic FP32, 5 steps 1414 -> 683.
+// 24: it sums the parts); the whole call of one step 208 -> 166; cubic FP32, 5 steps 1414 -> 663.
 int tile_parts_for(const TileGeom& t, int64_t n, int least) {
   const int64_t fill = 512 / t.ntiles, have = n / ((int64_t)t.ntiles * least);
   return (int)std::max<int64_t>(1, std::min<int64_t>(std::min(fill, have), kMaxParts));
 }
 template <typename T>
-int deposit_parts(const GridGeom& g, const TileGeom& t, int64_t n) {
-  if (g.det) return 1;  // a part's scale would depend on which of the tile's particles it holds
+int deposit_parts(const TileGeom& t, int64_t n) {
   return tile_parts_for(t, n, DepositOrder<T>::CH);
 }
 template <typename T>
@@ -2577,8 +2627,8 @@ void deposit_tiled(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& s
                    bool with_j, T* stage, int* bad, int* next_counts, int* nbr_counts, int* work, T* rho,
                    T* const J[3], hipStream_t s, int* spill_flag, int* box_faces, unsigned short* deal, int parts) {
   if (sp.n <= 0) return;
-  // the face masks serve the whole-tile reduction of unsplit tiles only; the others read whole boxes
-  if (parts > 1 || !(g.nx % kTile == 0 && g.ny % kTile == 0 && g.nz % kTile == 0)) box_faces = nullptr;
+  // the face masks serve the whole-tile reduction only; the other one reads whole boxes
+  if (parts == 1 && !(g.nx % kTile == 0 && g.ny % kTile == 0 && g.nz % kTile == 0)) box_faces = nullptr;
   Batch<T*> out{};
   out.p[0] = rho;
   for (int d = 0; d < 3; ++d) out.p[1 + d] = J ? J[d] : nullptr;
@@ -2796,7 +2846,7 @@ void deposit_yee(const GridGeom& g, const SpeciesView<T>& sp, bool with_j, T* rh
 }
 
 #define PIC_INST(T)                                                                                              \
-  template int deposit_parts<T>(const GridGeom&, const TileGeom&, int64_t);                                      \
+  template int deposit_parts<T>(const TileGeom&, int64_t);                                                       \
   template void permute_species<T>(const SpeciesView<T>&, const SpeciesView<T>&, const int*, hipStream_t);       \
   template void deposit_tiled<T>(const GridGeom&, const TileGeom&, const SpeciesView<T>&, const int*, const int*, \
                                  bool, T*, int*, int*, int*, int*, T*, T* const*, hipStream_t, int*, int*,       \
