@@ -381,7 +381,9 @@ hipError_t build_engine(const pic_params& p, Engine<T>& e) {
       if ((err = e.alloc(&e.Ah[q], ns)) != hipSuccess) return err;
       if ((err = hipMemset(e.Ah[q], 0, ns * sizeof(cplx<T>))) != hipSuccess) return err;
     }
-  if ((err = e.alloc(&e.tmp, (size_t)p.nx * p.ny * p.nz)) != hipSuccess) return err;
+  // between the passes of a two-axis centering: one array, three where the centerings are batched
+  const size_t cells = (size_t)p.nx * p.ny * p.nz;
+  if ((err = e.alloc(&e.tmp, (cells <= kCenterBatchCells ? 3 : 1) * cells)) != hipSuccess) return err;
   for (int q = 0; q < 4; ++q) {
     if ((err = e.alloc(&e.spill[q], (size_t)p.nx * p.ny * p.nz)) != hipSuccess) return err;
     if ((err = hipMemset(e.spill[q], 0, (size_t)p.nx * p.ny * p.nz * sizeof(T))) != hipSuccess) return err;
@@ -540,49 +542,63 @@ size_t ncells(const pic_params& p) { return (size_t)p.nx * p.ny * p.nz; }
 
 // ------------------------------------------------------------------ stages
 
-// accumulate: the N2S transposes of E and B add into E_stag / B_stag instead of writing them.
+// Centerings in one launch where that pays, else one by one.
 template <typename T>
-pic_status do_center(pic_ctx c, int dir, int what, pic_fields* f, bool accumulate = false) {
+void center_all(pic_ctx c, const CenterJob<T>* job, int count, int shift) {
   Engine<T>& e = static_cast<Engine<T>&>(*c->eng);
   const pic_params& p = c->p;
   const int m = p.center_order / 2;
   const double* cf = c->ccoef.data();
-  if (dir == PIC_N2S && what == PIC_J) {
-    for (int d = 0; d < 3; ++d)
-      center_axis<T>(static_cast<const T*>(f->J_nod[d]), static_cast<T*>(f->J_stag[d]), p.nx, p.ny, p.nz, d, 0, m,
-                     cf, c->stream);
-  } else if (dir == PIC_S2N && what == PIC_E) {
-    for (int d = 0; d < 3; ++d)
-      center_axis<T>(static_cast<const T*>(f->E_stag[d]), static_cast<T*>(f->E_nod[d]), p.nx, p.ny, p.nz, d, -1, m,
-                     cf, c->stream);
-  } else if (dir == PIC_S2N && what == PIC_B) {
-    for (int d = 0; d < 3; ++d) {
-      const int a0 = (d == 0) ? 1 : 0;
-      const int a1 = (d == 2) ? 1 : 2;
-      if (a1 == 2 && center_axis_then_z<T>(static_cast<const T*>(f->B_stag[d]), static_cast<T*>(f->B_nod[d]), p.nx,
-                                           p.ny, p.nz, a0, -1, m, cf, c->stream))
-        continue;  // B^x, B^y: both axes in one pass
-      center_axis<T>(static_cast<const T*>(f->B_stag[d]), e.tmp, p.nx, p.ny, p.nz, a0, -1, m, cf, c->stream);
-      center_axis<T>(e.tmp, static_cast<T*>(f->B_nod[d]), p.nx, p.ny, p.nz, a1, -1, m, cf, c->stream);
+  if (center_batch<T>(job, count, p.nx, p.ny, p.nz, shift, m, cf, c->stream)) return;
+  for (int q = 0; q < count; ++q) {
+    const CenterJob<T>& w = job[q];
+    if (!w.then_z) {
+      center_axis<T>(w.in, w.out, p.nx, p.ny, p.nz, w.axis, shift, m, cf, c->stream, w.accumulate != 0);
+    } else if (!center_axis_then_z<T>(w.in, w.out, p.nx, p.ny, p.nz, w.axis, shift, m, cf, c->stream)) {
+      center_axis<T>(w.in, e.tmp, p.nx, p.ny, p.nz, w.axis, shift, m, cf, c->stream);
+      center_axis<T>(e.tmp, w.out, p.nx, p.ny, p.nz, 2, shift, m, cf, c->stream);
     }
-  } else if (dir == PIC_S2N && what == PIC_J) {  // transpose of (N2S, J)
-    for (int d = 0; d < 3; ++d)
-      center_axis<T>(static_cast<const T*>(f->J_stag[d]), static_cast<T*>(f->J_nod[d]), p.nx, p.ny, p.nz, d, -1, m,
-                     cf, c->stream);
-  } else if (dir == PIC_N2S && what == PIC_E) {  // transpose of (S2N, E)
-    for (int d = 0; d < 3; ++d)
-      center_axis<T>(static_cast<const T*>(f->E_nod[d]), static_cast<T*>(f->E_stag[d]), p.nx, p.ny, p.nz, d, 0, m,
-                     cf, c->stream, accumulate);
-  } else if (dir == PIC_N2S && what == PIC_B) {  // transpose of (S2N, B): the same two axes
-    for (int d = 0; d < 3; ++d) {
-      const int a0 = (d == 0) ? 1 : 0;
-      const int a1 = (d == 2) ? 1 : 2;
-      center_axis<T>(static_cast<const T*>(f->B_nod[d]), e.tmp, p.nx, p.ny, p.nz, a1, 0, m, cf, c->stream);
-      center_axis<T>(e.tmp, static_cast<T*>(f->B_stag[d]), p.nx, p.ny, p.nz, a0, 0, m, cf, c->stream, accumulate);
-    }
-  } else {
-    return c->fail(PIC_EINVAL, "unsupported (dir, what) pair for pic_center");
   }
+}
+
+enum { CENTER_J = 1, CENTER_E = 2, CENTER_B = 4 };
+
+// ``what``: CENTER_E and CENTER_B may be taken together.  accumulate: the N2S transposes of E and B add
+// into E_stag / B_stag instead of writing them.
+template <typename T>
+pic_status do_center(pic_ctx c, int dir, int what, pic_fields* f, bool accumulate = false) {
+  Engine<T>& e = static_cast<Engine<T>&>(*c->eng);
+  auto in = [](void* const* a, int d) { return static_cast<const T*>(a[d]); };
+  auto out = [](void* const* a, int d) { return static_cast<T*>(a[d]); };
+  const bool n2s = dir == PIC_N2S;
+  const int shift = n2s ? 0 : -1, acc = accumulate ? 1 : 0;
+  const size_t N = ncells(c->p);
+  const bool batch = (long long)N <= kCenterBatchCells;
+  CenterJob<T> first[kMaxCenterJobs], second[kMaxCenterJobs];
+  int n1 = 0, n2 = 0;
+  auto flush = [&]() {
+    center_all<T>(c, first, n1, shift);
+    if (n2 > 0) center_all<T>(c, second, n2, shift);
+    n1 = n2 = 0;
+  };
+  for (int d = 0; d < 3; ++d) {
+    if (what & CENTER_J)  // J^d along d (S2N: the transpose of N2S)
+      first[n1++] = {in(n2s ? f->J_nod : f->J_stag, d), out(n2s ? f->J_stag : f->J_nod, d), d, 0, 0};
+    if (what & CENTER_E)
+      first[n1++] = {in(n2s ? f->E_nod : f->E_stag, d), out(n2s ? f->E_stag : f->E_nod, d), d, 0, acc};
+    if (what & CENTER_B) {  // B^d along the two other axes
+      const int a0 = (d == 0) ? 1 : 0, a1 = (d == 2) ? 1 : 2;
+      if (!n2s && a1 == 2) {  // B^x, B^y: both axes in one pass
+        first[n1++] = {in(f->B_stag, d), out(f->B_nod, d), a0, 1, 0};
+      } else {  // (N2S: the transpose, the same two axes in the other order)
+        T* t = e.tmp + (batch ? d * N : 0);
+        first[n1++] = {in(n2s ? f->B_nod : f->B_stag, d), t, n2s ? a1 : a0, 0, 0};
+        second[n2++] = {t, out(n2s ? f->B_stag : f->B_nod, d), n2s ? a0 : a1, 0, acc};
+      }
+    }
+    if (!batch) flush();  // one array between the passes: a component at a time
+  }
+  if (n1 > 0) flush();
   return c->check("pic_center");
 }
 
@@ -1117,8 +1133,7 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
           t.E_stag[d] = f->E_avg[d];
           t.B_stag[d] = f->B_avg[d];
         }
-      if ((st = do_center<T>(c, PIC_S2N, PIC_E, &t)) != PIC_OK) return st;
-      if ((st = do_center<T>(c, PIC_S2N, PIC_B, &t)) != PIC_OK) return st;
+      if ((st = do_center<T>(c, PIC_S2N, CENTER_E | CENTER_B, &t)) != PIC_OK) return st;
     }
     SourceSum<T> sum(e, f);
     for (int q = 0; q < nsp; ++q) {
@@ -1205,7 +1220,7 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
     }
     if (!spectral && !nodal && !mid) {
       StageScope sc(c, ST_N2S);
-      if ((st = do_center<T>(c, PIC_N2S, PIC_J, f)) != PIC_OK) return st;
+      if ((st = do_center<T>(c, PIC_N2S, CENTER_J, f)) != PIC_OK) return st;
     }
     {
       StageScope sc(c, ST_FFT_FWD);
@@ -1225,7 +1240,7 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
   if (spectral) {  // the outputs the real-space cycle leaves: the staggered state and J_stag
     state_inverse<T>(c, e, f);
     StageScope sc(c, ST_N2S);
-    if ((st = do_center<T>(c, PIC_N2S, PIC_J, f)) != PIC_OK) return st;
+    if ((st = do_center<T>(c, PIC_N2S, CENTER_J, f)) != PIC_OK) return st;
   }
   // particles left in the scratch arrays go back to the caller's arrays (tile order kept)
   for (int q = 0; q < nsp; ++q)
@@ -1252,8 +1267,7 @@ pic_status do_step_adjoint(pic_ctx c, pic_fields* f, const pic_species* sp, int 
   }
   if (!nodal) {
     StageScope sc(c, ST_S2N);
-    if ((st = do_center<T>(c, PIC_S2N, PIC_E, f)) != PIC_OK) return st;
-    if ((st = do_center<T>(c, PIC_S2N, PIC_B, f)) != PIC_OK) return st;
+    if ((st = do_center<T>(c, PIC_S2N, CENTER_E | CENTER_B, f)) != PIC_OK) return st;
   }
   // field solve: a->E_stag, a->B_stag in place; dL/dJ into J_stag (nodal solver: J_nod),
   // dL/drho^n into rho_old, the field solve's dL/drho^{n+1} into E_nod[0] (then added to
@@ -1268,7 +1282,7 @@ pic_status do_step_adjoint(pic_ctx c, pic_fields* f, const pic_species* sp, int 
   add_into<T>(static_cast<T*>(a->rho_new), static_cast<const T*>(a->E_nod[0]), (int64_t)N, c->stream);
   if (!nodal) {
     StageScope sc(c, ST_N2S);
-    if ((st = do_center<T>(c, PIC_S2N, PIC_J, a)) != PIC_OK) return st;  // J_stag -> J_nod (transpose of N2S)
+    if ((st = do_center<T>(c, PIC_S2N, CENTER_J, a)) != PIC_OK) return st;  // J_stag -> J_nod (transpose of N2S)
   }
   {
     Batch<T*> z{};
@@ -1331,8 +1345,7 @@ pic_status do_step_adjoint(pic_ctx c, pic_fields* f, const pic_species* sp, int 
       t.E_stag[d] = a->E_stag[d];
       t.B_stag[d] = a->B_stag[d];
     }
-    if ((st = do_center<T>(c, PIC_N2S, PIC_E, &t, true)) != PIC_OK) return st;
-    if ((st = do_center<T>(c, PIC_N2S, PIC_B, &t, true)) != PIC_OK) return st;
+    if ((st = do_center<T>(c, PIC_N2S, CENTER_E | CENTER_B, &t, true)) != PIC_OK) return st;
   }
   return c->check("pic_step_adjoint");
 }
@@ -1542,7 +1555,7 @@ pic_status pic_center(pic_ctx ctx, int dir, int what, pic_fields* f) {
   else
     st = check_fields(ctx, f, false, true, false, true, false, false, false, false);
   if (st != PIC_OK) return st;
-  return PIC_DISPATCH(ctx, do_center, dir, what, f);
+  return PIC_DISPATCH(ctx, do_center, dir, what == PIC_J ? CENTER_J : what == PIC_E ? CENTER_E : CENTER_B, f);
 }
 
 pic_status psatd_push_fields(pic_ctx ctx, pic_fields* f) {

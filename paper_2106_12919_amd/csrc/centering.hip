@@ -12,6 +12,8 @@
 // loaded once per window, loads coalesced across the column index).  Contiguous
 // axis (z): a block stages whole z-lines plus the periodic halo in LDS.  Both are
 // specialised on m, so the stencil is unrolled.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace pic {
@@ -23,15 +25,11 @@ struct Coef {
   T c[16];
 };
 
-// Strided axis: grid (column blocks, row blocks, outer) flattened and renumbered
-// XCD-major, row blocks next to each other (which share halo rows) on one XCD.
+// Strided axis: L outputs (row block by) of 256 columns (block bx) at outer index bz.
 template <typename T, int M, int L>
-__global__ void __launch_bounds__(256) k_center_strided(const T* __restrict__ in, T* __restrict__ out, Coef<T> cf,
-                                                        int Na, long long sa, int C, long long outer_stride,
-                                                        int shift, int accumulate) {
-  const int nb = gridDim.x * gridDim.y * gridDim.z;
-  const int lb = xcd_major(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), nb);
-  const int bx = lb % gridDim.x, by = (lb / gridDim.x) % gridDim.y, bz = lb / (gridDim.x * gridDim.y);
+__device__ inline void center_strided(const T* __restrict__ in, T* __restrict__ out, const Coef<T>& cf, int Na,
+                                      long long sa, int C, long long outer_stride, int shift, int accumulate, int bx,
+                                      int by, int bz) {
   const int c = bx * blockDim.x + threadIdx.x;
   if (c >= C) return;
   const int j0 = by * L;
@@ -57,25 +55,34 @@ __global__ void __launch_bounds__(256) k_center_strided(const T* __restrict__ in
   }
 }
 
+// Grid (column blocks, row blocks, outer) flattened and renumbered XCD-major, row blocks next to each
+// other (which share halo rows) on one XCD.
+template <typename T, int M, int L>
+__global__ void __launch_bounds__(256) k_center_strided(const T* __restrict__ in, T* __restrict__ out, Coef<T> cf,
+                                                        int Na, long long sa, int C, long long outer_stride,
+                                                        int shift, int accumulate) {
+  const int nb = gridDim.x * gridDim.y * gridDim.z;
+  const int lb = xcd_major(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), nb);
+  center_strided<T, M, L>(in, out, cf, Na, sa, C, outer_stride, shift, accumulate, lb % gridDim.x,
+                          (lb / gridDim.x) % gridDim.y, lb / (gridDim.x * gridDim.y));
+}
+
 // Two axes in one pass, for the staggered-to-nodal centering of B^x (y, then z) and B^y (x,
 // then z): a block takes L rows along the strided axis (outer index fixed) for every z,
 // centres them along that axis in registers as k_center_strided does, stages the L centred
 // rows with their periodic z halo in LDS (row q at s[q * W + i] holds z = i + 1 - M + shift_z),
 // then centres along z as k_center_z does.  The same sums in the same order as the two passes,
-// without writing and re-reading the intermediate array.  Grid (row blocks, outer), XCD-major.
+// without writing and re-reading the intermediate array.
 template <typename T, int M, int L>
-__global__ void __launch_bounds__(256) k_center_strided_z(const T* __restrict__ in, T* __restrict__ out, Coef<T> cf,
-                                                          int Na, long long sa, long long outer_stride, int nz,
-                                                          int shift_a, int shift_z) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  T* s = reinterpret_cast<T*>(smem);
+__device__ inline void center_strided_z(T* s, const T* __restrict__ in, T* __restrict__ out, const Coef<T>& cf, int Na,
+                                        long long sa, long long outer_stride, int nz, int shift_a, int shift_z,
+                                        int by, int bz) {
   constexpr int H = 2 * M - 1;  // halo elements per row
   constexpr int WIN = L + 2 * M - 1;
   const int W = nz + H;
   const int off = M - 1 - shift_z;  // index of z = 0
-  const int lb = xcd_major(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
-  const int j0 = (lb % gridDim.x) * L;
-  const size_t obase = (size_t)(lb / gridDim.x) * outer_stride;
+  const int j0 = by * L;
+  const size_t obase = (size_t)bz * outer_stride;
   for (int z = threadIdx.x; z < nz; z += blockDim.x) {
     T w[WIN];
 #pragma unroll
@@ -112,6 +119,17 @@ __global__ void __launch_bounds__(256) k_center_strided_z(const T* __restrict__ 
   }
 }
 
+// Grid (row blocks, outer), XCD-major.
+template <typename T, int M, int L>
+__global__ void __launch_bounds__(256) k_center_strided_z(const T* __restrict__ in, T* __restrict__ out, Coef<T> cf,
+                                                          int Na, long long sa, long long outer_stride, int nz,
+                                                          int shift) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lb = xcd_major(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
+  center_strided_z<T, M, L>(reinterpret_cast<T*>(smem), in, out, cf, Na, sa, outer_stride, nz, shift, shift,
+                            lb % gridDim.x, lb / gridDim.x);
+}
+
 // 16-byte vector of T (four floats or two doubles).
 template <typename T>
 struct Vec16;
@@ -136,15 +154,13 @@ struct Vec16<double> {
 // l at s[l * W + i] holds z = i + 1 - M + shift, W = nz + 2M - 1), the line bodies with
 // 16-byte loads, then every thread forms outputs from LDS.
 template <typename T, int M>
-__global__ void __launch_bounds__(256) k_center_z(const T* __restrict__ in, T* __restrict__ out, Coef<T> cf, int nz,
-                                                  int nlines, int lpb, int shift, int accumulate) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  T* s = reinterpret_cast<T*>(smem);
+__device__ inline void center_z(T* s, const T* __restrict__ in, T* __restrict__ out, const Coef<T>& cf, int nz,
+                                int nlines, int lpb, int shift, int accumulate, int bx) {
   constexpr int H = 2 * M - 1;  // halo elements per line
   constexpr int VN = Vec16<T>::n;
   const int W = nz + H;
   const int off = M - 1 - shift;  // index of z = 0
-  const int line0 = blockIdx.x * lpb;
+  const int line0 = bx * lpb;
   const int nl = min(lpb, nlines - line0);
   const T* src = in + (size_t)line0 * nz;
   if (nz % VN == 0) {
@@ -176,6 +192,48 @@ __global__ void __launch_bounds__(256) k_center_z(const T* __restrict__ in, T* _
     T* o = out + (size_t)(line0 + l) * nz + z;
     *o = accumulate ? *o + acc : acc;
   }
+}
+
+template <typename T, int M>
+__global__ void __launch_bounds__(256) k_center_z(const T* __restrict__ in, T* __restrict__ out, Coef<T> cf, int nz,
+                                                  int nlines, int lpb, int shift, int accumulate) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  center_z<T, M>(reinterpret_cast<T*>(smem), in, out, cf, nz, nlines, lpb, shift, accumulate, blockIdx.x);
+}
+
+// Several centerings that do not depend on each other in one launch (center_batch): workgroups of job 0,
+// then of job 1, ...  On small grids one array's centering fills a fraction of the device and takes little
+// longer than its launch; six of them together take about the time of one.
+constexpr int kJobRows = 8;  // outputs per thread along a strided axis
+template <typename T>
+struct Jobs {
+  CenterJob<T> job[kMaxCenterJobs];
+  int blocks[kMaxCenterJobs];
+  int count;
+};
+template <typename T, int M>
+__global__ void __launch_bounds__(256) k_center_jobs(Jobs<T> jobs, Coef<T> cf, int nx, int ny, int nz, int lpb,
+                                                     int shift) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  T* s = reinterpret_cast<T*>(smem);
+  int b = blockIdx.x, q = 0;
+  while (q + 1 < jobs.count && b >= jobs.blocks[q]) b -= jobs.blocks[q++];
+  const CenterJob<T> w = jobs.job[q];
+  const long long plane = (long long)ny * nz;
+  if (w.axis == 2) {
+    center_z<T, M>(s, w.in, w.out, cf, nz, nx * ny, lpb, shift, w.accumulate, b);
+    return;
+  }
+  const int Na = w.axis == 0 ? nx : ny, rows = (Na + kJobRows - 1) / kJobRows;
+  const long long sa = w.axis == 0 ? plane : nz;
+  if (w.then_z) {
+    center_strided_z<T, M, kJobRows>(s, w.in, w.out, cf, Na, sa, w.axis == 0 ? nz : plane, nz, shift, shift, b % rows,
+                                     b / rows);
+    return;
+  }
+  const int C = w.axis == 0 ? ny * nz : nz, cols = (C + 255) / 256;
+  center_strided<T, M, kJobRows>(w.in, w.out, cf, Na, sa, C, w.axis == 0 ? 0 : plane, shift, w.accumulate, b % cols,
+                                 (b / cols) % rows, b / (cols * rows));
 }
 
 // Outputs per thread along the axis: FP32 the longest window of 32, 16 or 8 that still gives
@@ -217,7 +275,7 @@ void launch_strided_z(const T* in, T* out, const Coef<T>& cf, int Na, long long 
                       int shift, hipStream_t s) {
   const size_t lds = (size_t)L * (nz + 2 * M - 1) * sizeof(T);
   hipLaunchKernelGGL((k_center_strided_z<T, M, L>), dim3((Na + L - 1) / L, O), dim3(256), lds, s, in, out, cf, Na,
-                     sa, os, nz, shift, shift);
+                     sa, os, nz, shift);
 }
 
 // Rows per block of the fused pass: the longest of 32, 16, 8 (FP64: 8) whose LDS rows fit the
@@ -247,6 +305,37 @@ bool dispatch_strided_z_m(const T* in, T* out, const Coef<T>& cf, int Na, long l
 }
 
 }  // namespace
+
+template <typename T>
+bool center_batch(const CenterJob<T>* job, int count, int nx, int ny, int nz, int shift, int m, const double* c,
+                  hipStream_t s) {
+  const int lpb = nz >= 1024 ? 1 : 1024 / nz;
+  const size_t lds = (size_t)std::max(lpb, kJobRows) * (nz + 2 * m - 1) * sizeof(T);
+  if ((long long)nx * ny * nz > kCenterBatchCells || count > kMaxCenterJobs || lds > 64 * 1024) return false;
+  Coef<T> cf{};
+  for (int n = 0; n < m && n < 16; ++n) cf.c[n] = (T)c[n];
+  Jobs<T> jobs{};
+  jobs.count = count;
+  int total = 0;
+  for (int q = 0; q < count; ++q) {
+    const CenterJob<T>& w = jobs.job[q] = job[q];
+    const int Na = w.axis == 0 ? nx : ny, rows = (Na + kJobRows - 1) / kJobRows, O = w.axis == 0 ? ny : nx;
+    if (w.axis == 2) jobs.blocks[q] = (nx * ny + lpb - 1) / lpb;
+    else if (w.then_z) jobs.blocks[q] = rows * O;
+    else jobs.blocks[q] = w.axis == 0 ? (ny * nz + 255) / 256 * rows : (nz + 255) / 256 * rows * nx;
+    total += jobs.blocks[q];
+  }
+  switch (m) {
+#define PIC_CASE(MM)                                                                                                \
+  case MM:                                                                                                          \
+    hipLaunchKernelGGL((k_center_jobs<T, MM>), dim3(total), dim3(256), lds, s, jobs, cf, nx, ny, nz, lpb, shift); \
+    return true;
+    PIC_CASE(1) PIC_CASE(2) PIC_CASE(3) PIC_CASE(4) PIC_CASE(5) PIC_CASE(6) PIC_CASE(7) PIC_CASE(8)
+    PIC_CASE(9) PIC_CASE(10) PIC_CASE(11) PIC_CASE(12) PIC_CASE(13) PIC_CASE(14) PIC_CASE(15) PIC_CASE(16)
+#undef PIC_CASE
+    default: return false;
+  }
+}
 
 template <typename T>
 bool center_axis_then_z(const T* in, T* out, int nx, int ny, int nz, int axis, int shift, int m, const double* c,
@@ -297,6 +386,9 @@ template void center_axis<float>(const float*, float*, int, int, int, int, int, 
                                   bool);
 template void center_axis<double>(const double*, double*, int, int, int, int, int, int, const double*, hipStream_t,
                                    bool);
+
+template bool center_batch<float>(const CenterJob<float>*, int, int, int, int, int, int, const double*, hipStream_t);
+template bool center_batch<double>(const CenterJob<double>*, int, int, int, int, int, int, const double*, hipStream_t);
 
 template bool center_axis_then_z<float>(const float*, float*, int, int, int, int, int, int, const double*,
                                          hipStream_t);

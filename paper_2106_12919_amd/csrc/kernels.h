@@ -69,6 +69,25 @@ struct Fft3D {
 template <typename T>
 void center_axis(const T* in, T* out, int nx, int ny, int nz, int axis, int shift, int m, const double* c,
                  hipStream_t s, bool accumulate = false);
+// One centering of a batch: along ``axis``, or (then_z, axis 0 or 1) along it and then along z.
+template <typename T>
+struct CenterJob {
+  const T* in;
+  T* out;
+  int axis, then_z, accumulate;  // (accumulate: not with then_z)
+};
+constexpr int kMaxCenterJobs = 6;
+// Largest grid (cells) the batch is taken on: below, the separate launches leave the device partly idle
+// (one-step call without particles, orders 8 / 32: FP32 32^3 80 -> 61 / 89 -> 64 us, 64 x 64 x 128 131 -> 118 /
+// 140 -> 123, 128 x 128 x 256 515 -> 487 / 532 -> 515); above, their longer register windows win (192^3, order 32:
+// 919 -> 932).
+constexpr long long kCenterBatchCells = 1 << 22;
+// Up to kMaxCenterJobs centerings that do not depend on each other in one launch, the same sums in the same
+// order as center_axis and center_axis_then_z.  Returns false, launching nothing, on larger grids and where
+// the rows do not fit the LDS.
+template <typename T>
+bool center_batch(const CenterJob<T>* job, int count, int nx, int ny, int nz, int shift, int m, const double* c,
+                  hipStream_t s);
 // out = centering of in along ``axis`` (0 or 1), then along z, both with ``shift``, in one pass
 // (the same sums in the same order as two center_axis calls).  Returns false, launching
 // nothing, when no row block fits the LDS.

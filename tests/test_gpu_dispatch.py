@@ -10,7 +10,9 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
+from oracle import centering as ocent  # noqa: E402
 from oracle import step as ostep  # noqa: E402
+from paper_2106_12919_amd import autograd as pag  # noqa: E402
 from paper_2106_12919_amd import inputs  # noqa: E402
 from paper_2106_12919_amd import lib as piclib  # noqa: E402
 
@@ -171,3 +173,23 @@ def test_few_tiles_in_parts(dtype, shape, ppc, order, flags):
     of a tile holding fewer chunks than the others or none; grouped and in the caller's order."""
     banner(f"pic_step 3 steps, few tiles dtype={dtype} shape={shape} ppc={ppc} order={order} flags={flags}")
     steps_against_oracle(shape, ppc, order, 8, dtype, 3, flags=flags)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("shape,order", [((8, 12, 18), 2), ((16, 8, 54), 8), ((24, 36, 32), 16), ((32, 36, 1024), 32)])
+def test_centerings_in_one_launch(dtype, shape, order):
+    """Small grids: the three components in one launch.  Rows and lines that do not fill a workgroup, and lines
+    whose rows are over the batch's LDS (FP64, 1024: separate launches), every direction against the oracle."""
+    banner(f"centerings in one launch dtype={dtype} shape={shape} order={order}")
+    ctx = piclib.Context(shape, (1.0, 1.0, 1.0), 0.5, 1, order, 8, dtype)
+    src = rounded(inputs.random_grid(shape, seed=5, count=3), dtype)
+    x = torch.tensor(np.stack(src), device="cuda", dtype=torch.float32 if dtype == "f32" else torch.float64)
+    tol = 10 * 2 * order * EPS[dtype]  # two axes of a sum of ``order`` terms, margin 10
+    names = {piclib.PIC_J: ostep.J_NAMES, piclib.PIC_E: ostep.E_NAMES, piclib.PIC_B: ostep.B_NAMES}
+    for direction, centre in ((piclib.PIC_S2N, ocent.s2n), (piclib.PIC_N2S, ocent.n2s)):
+        for what in names:
+            got = pag._center(ctx, direction, what, x)
+            for d in range(3):
+                ref = centre(names[what][d], src[d], order // 2)
+                assert max_rel(np64(got[d]), ref) <= tol, (direction, what, d)
+    ctx.close()
