@@ -190,6 +190,7 @@ struct SpeciesView {
 };
 struct TileGeom {
   int ntx, nty, ntz, ntiles;
+  bool distinct;            // whole tiles only, and at least three along every axis
   int* scan_tmp = nullptr;  // device scratch of the bucket scan: (ntiles + 1) / 8192 + 2 ints
 };
 TileGeom make_tiles(const GridGeom& g);  // tiles of kTile^3 cells

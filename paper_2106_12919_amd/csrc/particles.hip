@@ -117,14 +117,12 @@ __device__ inline int advance_offset(T& off, T disp) {
   T f = floor(o);
   o -= f;
   // a finite, in-range offset moves by less than one cell; anything else is clamped
-  int sh = (f > (T)1 || f < (T)-1 || f != f) ? 0 : (int)f;
-  if (f != (T)sh) o = (T)0;
-  if (o >= (T)1) {  // rounding of o - floor(o) for tiny negative o
-    o -= (T)1;
-    sh += 1;
-  }
-  off = o;
-  return sh;
+  const bool ok = fabs(f) <= (T)1;
+  f = ok ? f : (T)0;
+  o = ok ? o : (T)0;
+  const bool up = o >= (T)1;  // rounding of o - floor(o) to 1 for tiny negative o
+  off = up ? (T)0 : o;
+  return (int)(up ? f + (T)1 : f);
 }
 
 // ---------------------------------------------------------------- tiles
@@ -162,9 +160,23 @@ __device__ inline int neighbour_key(int nb, int tx, int ty, int tz, const TileGe
 // box-local index (0 .. B-1) of the first support node of a particle in cell i
 // (0 <= i < n) of a tile starting at cell t0, for boxes whose node 0 is t0 - 1 + BASE
 // (one-cell margin); -1 if the particle is outside the margin.
+// The index modulo n is the smallest of three candidates taken as unsigned numbers.
 __device__ inline int box_index(int i, int t0, int n) {
-  const int l = wrapi(i - t0 + 1, n);
+  const unsigned a = (unsigned)(i - t0 + 1);
+  const int l = (int)min(a, min(a - (unsigned)n, a + (unsigned)n));
   return (l <= kTile + 1) ? l : -1;
+}
+
+// neighbour_of_cell for a cell whose box indices are known (each -1: outside the margin).  On grids of whole
+// tiles, three or more along every axis, they tell the neighbour by themselves.  (With one or two the tiles on
+// both sides are the same one, for which neighbour_of_cell, and the slot runs reserved per neighbour, take one
+// of the two indices.)
+__device__ inline int neighbour_of_box(int lx, int ly, int lz, int i, int j, int k, int tx, int ty, int tz,
+                                       const TileGeom& tg) {
+  if (tg.distinct && (lx | ly | lz) >= 0)
+    return ((lx + kTile - 1) / (unsigned)kTile * 3 + (ly + kTile - 1) / (unsigned)kTile) * 3 +
+           (lz + kTile - 1) / (unsigned)kTile;
+  return neighbour_of_cell(i, j, k, tx, ty, tz, tg);
 }
 
 // Box geometry of one tile for a shape of NW nodes per axis: B = kTile + NW + 1
@@ -244,8 +256,7 @@ template <>
 __device__ inline const double* no_weight<double>() { return g_no_weight_d; }
 
 template <typename T, bool WJ>
-__device__ inline void load_raw(const SpeciesView<T>& sp, int p, Raw<T>& r) {
-  r.cell = sp.cell[p];
+__device__ inline void load_moving(const SpeciesView<T>& sp, int p, Raw<T>& r) {  // all but the cell
 #pragma unroll
   for (int d = 0; d < 3; ++d) r.o[d] = sp.off[d][p];
 #pragma unroll
@@ -253,6 +264,12 @@ __device__ inline void load_raw(const SpeciesView<T>& sp, int p, Raw<T>& r) {
   const bool has_w = sp.w != nullptr;
   const T wv = (has_w ? sp.w : no_weight<T>())[has_w ? p : 0];
   r.w = has_w ? wv : (T)sp.w_const;
+}
+
+template <typename T, bool WJ>
+__device__ inline void load_raw(const SpeciesView<T>& sp, int p, Raw<T>& r) {
+  r.cell = sp.cell[p];
+  load_moving<T, WJ>(sp, p, r);
 }
 
 // What the scale bounds need of a particle: its momentum (when WJ) and weight.
@@ -657,8 +674,9 @@ struct DepositOrder {
 // stays nearly dealt and the deposition's own loads nearly contiguous.  64 x 64 x 128, 4 per cell, FP32:
 // 126 -> 98 us; 128 x 128 x 256, 2 per cell: 333 -> 311; FP64 192 x 192 x 384, 1 per cell: 1915 -> 1786.
 // Linear shapes (8 nodes) are bound by HBM and lose by it (FP32 +1%, FP64 +19% through 129 VGPRs): not used.
+// They are held to four waves per SIMD (FP64: 128 VGPRs; at 129 103 -> 122 us on 108 x 54 x 162, 3 per cell).
 template <typename T, int ORDER>
-__global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_home(GridGeom g, TileGeom tg, Batch<const T*> F,
+__global__ void __launch_bounds__((kGatherBlock<T, ORDER>), ORDER == 1 ? 4 : 1) k_gather_push_home(GridGeom g, TileGeom tg, Batch<const T*> F,
                                                                        SpeciesView<T> in, SpeciesView<T> out,
                                                                        const int* __restrict__ home, int* cursor,
                                                                        const int* __restrict__ nbr_bases,
@@ -700,7 +718,8 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_home(G
     for (int qq = beg + threadIdx.x; qq < end; qq += step) {
       int i, j, k;
       (void)decode_cell(in.cell[at(qq)], g, nullptr, i, j, k);
-      const int nb = neighbour_of_cell(i, j, k, tx, ty, tz, tg);
+      const int nb = neighbour_of_box(box_index(i, t0x, g.nx), box_index(j, t0y, g.ny), box_index(k, t0z, g.nz), i, j,
+                                      k, tx, ty, tz, tg);
       const unsigned long long own = __ballot(nb == 13);
       if (nb == 13) {
         if (__lane_id() == __ffsll(own) - 1) atomicAdd(&cnt[13], __popcll(own));
@@ -730,7 +749,8 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_home(G
     const Raw<T> r = nxt;
     int i, j, k;
     (void)decode_cell(r.cell, g, nullptr, i, j, k);
-    const int nb = neighbour_of_cell(i, j, k, tx, ty, tz, tg);
+    const int lx = box_index(i, t0x, g.nx), ly = box_index(j, t0y, g.ny), lz = box_index(k, t0z, g.nz);
+    const int nb = neighbour_of_box(lx, ly, lz, i, j, k, tx, ty, tz, tg);
     int slot;
     const unsigned long long own = __ballot(nb == 13);
     if (nb == 13) {
@@ -747,7 +767,6 @@ __global__ void __launch_bounds__((kGatherBlock<T, ORDER>)) k_gather_push_home(G
     pn = at(min(qq + 2 * step, end - 1));
     T ox = r.o[0], oy = r.o[1], oz = r.o[2];
     T ux = r.u[0], uy = r.u[1], uz = r.u[2];
-    const int lx = box_index(i, t0x, g.nx), ly = box_index(j, t0y, g.ny), lz = box_index(k, t0z, g.nz);
     gather_push_one<T, ORDER>(box, F, g, lx, ly, lz, i, j, k, ox, oy, oz, ux, uy, uz, qdt2m, dtx, dty, dtz);
     out.u[0][slot] = ux;
     out.u[1][slot] = uy;
@@ -956,28 +975,27 @@ __device__ inline void unpack_xy(unsigned long long w, int& x, int& y) {
   y = (int)((long long)(w - (unsigned long long)(long long)x) >> 32);
 }
 
-// What the deposition needs of one particle: its cell and offsets at x, the velocity,
-// the cell and offsets at x - dt v / 2, and the box indices of the first support
-// node at both positions (-1 outside the box margin).
+// What the deposition needs of one particle: the offsets at x, the velocity, the offsets at x - dt v / 2 and
+// the cells' shift (sx, sy, sz) to it, the box indices (jx, jy, jz) there, and the box indices of the first
+// support node at both positions; outside the margin those are -1 and the cells are set.
 template <typename T>
 struct DepositPoint {
-  int i, j, k, ih, jh, kh, at_rho, at_j;
+  int i, j, k, ih, jh, kh, at_rho, at_j, sx, sy, sz, jx, jy;
   T ox, oy, oz, hx, hy, hz, vx, vy, vz;
 };
 
+// From the box indices at x; false when either position is not within the margin.
 template <typename T, int ORDER, bool WJ>
-__device__ inline bool locate(const Raw<T>& r, const GridGeom& g, int t0x, int t0y, int t0z, T hdtx, T hdty, T hdtz,
-                              int* bad, DepositPoint<T>& d) {
+__device__ inline bool locate(const Raw<T>& r, int lx, int ly, int lz, const GridGeom& g, T hdtx, T hdty, T hdtz,
+                              DepositPoint<T>& d) {
   using X = Box<Shape<T, ORDER>::NW>;
-  if (!decode_cell(r.cell, g, bad, d.i, d.j, d.k)) return false;
+  d.i = d.j = d.k = d.ih = d.jh = d.kh = 0;
   d.ox = r.o[0];
   d.oy = r.o[1];
   d.oz = r.o[2];
-  {
-    const int lx = box_index(d.i, t0x, g.nx), ly = box_index(d.j, t0y, g.ny), lz = box_index(d.k, t0z, g.nz);
-    d.at_rho = (lx >= 0 && ly >= 0 && lz >= 0) ? X::at(lx, ly, lz) : -1;
-  }
+  d.at_rho = X::at(lx, ly, lz);
   d.at_j = -1;
+  bool inside = lx <= kTile + 1;
   if (WJ) {
     const T ig = inv_sqrt((T)1 + r.u[0] * r.u[0] + r.u[1] * r.u[1] + r.u[2] * r.u[2]);
     d.vx = r.u[0] * ig;
@@ -987,11 +1005,33 @@ __device__ inline bool locate(const Raw<T>& r, const GridGeom& g, int t0x, int t
     d.hx = d.ox;
     d.hy = d.oy;
     d.hz = d.oz;
-    d.ih = wrapi(d.i + advance_offset(d.hx, -hdtx * d.vx + (T)0.5 * (T)g.sgx), g.nx);
-    d.jh = wrapi(d.j + advance_offset(d.hy, -hdty * d.vy + (T)0.5 * (T)g.sgy), g.ny);
-    d.kh = wrapi(d.k + advance_offset(d.hz, -hdtz * d.vz + (T)0.5 * (T)g.sgz), g.nz);
-    const int lx = box_index(d.ih, t0x, g.nx), ly = box_index(d.jh, t0y, g.ny), lz = box_index(d.kh, t0z, g.nz);
-    d.at_j = (lx >= 0 && ly >= 0 && lz >= 0) ? X::at(lx, ly, lz) : -1;
+    d.sx = advance_offset(d.hx, -hdtx * d.vx + (T)0.5 * (T)g.sgx);
+    d.sy = advance_offset(d.hy, -hdty * d.vy + (T)0.5 * (T)g.sgy);
+    d.sz = advance_offset(d.hz, -hdtz * d.vz + (T)0.5 * (T)g.sgz);
+    d.jx = lx + d.sx;
+    d.jy = ly + d.sy;
+    const int jz = lz + d.sz;
+    d.at_j = X::at(d.jx, d.jy, jz);
+    inside = inside && max((unsigned)d.jx, max((unsigned)d.jy, (unsigned)jz)) <= (unsigned)(kTile + 1);
+  }
+  return inside;
+}
+
+// The cells and the box indices of such a particle, from its cell; false for an invalid cell.
+template <typename T, int ORDER, bool WJ>
+__device__ inline bool locate_cell(int cell, const GridGeom& g, int t0x, int t0y, int t0z, int* bad, DepositPoint<T>& d) {
+  using X = Box<Shape<T, ORDER>::NW>;
+  if (!decode_cell(cell, g, bad, d.i, d.j, d.k)) return false;
+  auto first = [&](int i, int j, int k) {
+    const int lx = box_index(i, t0x, g.nx), ly = box_index(j, t0y, g.ny), lz = box_index(k, t0z, g.nz);
+    return (lx | ly | lz) >= 0 ? X::at(lx, ly, lz) : -1;
+  };
+  d.at_rho = first(d.i, d.j, d.k);
+  if (WJ) {
+    d.ih = wrapi(d.i + d.sx, g.nx);
+    d.jh = wrapi(d.j + d.sy, g.ny);
+    d.kh = wrapi(d.k + d.sz, g.nz);
+    d.at_j = first(d.ih, d.jh, d.kh);
   }
   return true;
 }
@@ -1059,10 +1099,12 @@ struct DepositLds {
   int next_tile;
   int cross;  // faces of the box holding a nonzero value (see deposit_tile)
   __align__(16) int hist[O::KG];
-  unsigned short order[O::CH];
+  unsigned order[O::CH];  // dealt particles: place in the chunk, then kPlace bits up the three box indices
   unsigned rowmask[O::RMAX];
   int rowstart[O::RMAX];
 };
+constexpr int kPlace = 16;                      // bits of a dealt particle's place; 4 per box index above
+constexpr unsigned kOutside = 15u << kPlace;    // outside the margin, or an invalid cell
 
 // How many of the ``parts`` a tile of len particles is split into hold particles, and the particles
 // per part (whole chunks, so that a part's chunks are the tile's).
@@ -1095,7 +1137,7 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
   int* cnt = L.cnt;
   int* wtot = L.wtot;
   int* hist = L.hist;
-  unsigned short* order = L.order;
+  unsigned* order = L.order;
   unsigned* rowmask = L.rowmask;
   int* rowstart = L.rowstart;
   const int tile = parts == 1 ? item : item / parts;  // (item ntiles * parts: the invalid cells)
@@ -1184,6 +1226,7 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
   }
   if (threadIdx.x < 27) cnt[threadIdx.x] = 0;
   if (threadIdx.x == 0) L.cross = 0;  // read only after the chunk loop's barriers
+  unsigned seen = 0;  // bit l: a particle of this thread at box index l along x, bit 16 + l: along y
   for (int cb = beg; cb < end; cb += O::CH) {
     const int nc = min(O::CH, end - cb);
     if (threadIdx.x < O::KG) hist[threadIdx.x] = 0;
@@ -1194,7 +1237,12 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
     // record, with momentum and weight for the bounds of a single-chunk tile): the first support
     // node of the current shifts from it only when the half step crosses a cell face, and the
     // deal only orders the atomics, it does not change their sums.
-    int kr[O::U];  // (rank, residue) of this thread's particles, until the deal below
+    // The box indices found here go with the deal: the kernel issues vector instructions for 63% (cubic, one
+    // particle per cell) to 82% (linear) of its time, a fifth of them on cells, indices and faces, and the second
+    // pass now decodes no cell, takes the neighbour tile and the faces reached from the indices, and forms the
+    // current's indices from them by the half step's shift.  256^3, 8 per cell, linear, FP32: 2.28 -> 2.03 ms;
+    // cubic FP32 384 x 384 x 768, 1 per cell: 6.80 -> 6.40 ms; FP64 192 x 192 x 384: 1.67 -> 1.57 ms.
+    int kr[O::U];  // box indices and (rank, residue) of this thread's particles, until the deal below
     {
       const int e0 = threadIdx.x;
       int qi[O::U];
@@ -1213,11 +1261,16 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
         kr[u] = 0;
         if (e0 + u * PIC_DEPOSIT_BLOCK < nc) {
           int i, j, k, key = 0;
+          unsigned l = kOutside;
           if (decode_cell(c[u], g, nullptr, i, j, k)) {
             const int lx = box_index(i, t0x, g.nx), ly = box_index(j, t0y, g.ny), lz = box_index(k, t0z, g.nz);
-            if (lx >= 0 && ly >= 0 && lz >= 0) key = X::at(lx, ly, lz) & (O::KG - 1);
+            if ((lx | ly | lz) >= 0) {
+              key = X::at(lx, ly, lz) & (O::KG - 1);
+              l = (unsigned)(lx | ly << 4 | lz << 8) << kPlace;
+            }
           }
-          kr[u] = atomicAdd(&hist[key], 1) * O::KG + key;
+          static_assert(O::CH * O::KG <= 1 << kPlace, "rank and residue fit below the box indices");
+          kr[u] = (int)(l | (unsigned)(atomicAdd(&hist[key], 1) * O::KG + key));
           if (single) bound_add<T, WJ>(r[u], sw, mw);
         }
       }
@@ -1246,35 +1299,52 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
     for (int u = 0; u < O::U; ++u) {
       const int e = threadIdx.x + u * PIC_DEPOSIT_BLOCK;
       if (e < nc) {
-        const int r = kr[u] / O::KG, key = kr[u] % O::KG;
+        constexpr int kLow = (1 << kPlace) - 1;
+        const int r = (kr[u] & kLow) / O::KG, key = kr[u] & (O::KG - 1);
         const int pos = R == 0 ? e : rowstart[r] + __popc(rowmask[r] & ((1u << key) - 1u));
-        order[pos] = (unsigned short)e;
+        order[pos] = (unsigned)((kr[u] & ~kLow) | e);
       }
     }
     __syncthreads();
     if (ORDER == 3 && deal)  // the next gather visits this tile's particles in the same order
-      for (int e = threadIdx.x; e < nc; e += blockDim.x) deal[cb + e] = order[e];
+      for (int e = threadIdx.x; e < nc; e += blockDim.x) deal[cb + e] = (unsigned short)order[e];
     int sh[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) sh[c] = (c < ncomp) ? shs[c] : 0;
     // pass 2: deposit in the dealt order, the next particle's loads in flight meanwhile
-    Raw<T> nxt;
-    if ((int)threadIdx.x < nc) {
-      int q[1] = {cb + order[threadIdx.x]};
+    auto slot_of = [&](unsigned o) {
+      int q[1] = {cb + (int)(o & ((1u << kPlace) - 1u))};
       through_perm(perm, q);
-      load_raw<T, WJ>(sp, q[0], nxt);
+      return q[0];
+    };
+    Raw<T> nxt;
+    unsigned onxt = 0;
+    if ((int)threadIdx.x < nc) {
+      onxt = order[threadIdx.x];
+      load_moving<T, WJ>(sp, slot_of(onxt), nxt);
     }
     for (int pos = threadIdx.x; pos < nc; pos += blockDim.x) {
       const Raw<T> r = nxt;
-      {
-        int q[1] = {cb + order[min(pos + (int)blockDim.x, nc - 1)]};
-        through_perm(perm, q);
-        load_raw<T, WJ>(sp, q[0], nxt);
-      }
+      const unsigned o = onxt;
+      onxt = order[min(pos + (int)blockDim.x, nc - 1)];
+      load_moving<T, WJ>(sp, slot_of(onxt), nxt);
       DepositPoint<T> d;
-      if (!locate<T, ORDER, WJ>(r, g, t0x, t0y, t0z, hdtx, hdty, hdtz, bad, d)) continue;
+      const int lx = (int)(o >> kPlace & 15u), ly = (int)(o >> (kPlace + 4) & 15u), lz = (int)(o >> (kPlace + 8));
+      const bool dealt = lx <= kTile + 1;
+      if (!locate<T, ORDER, WJ>(r, lx, ly, lz, g, hdtx, hdty, hdtz, d)) {
+        // a position outside the margin, or an invalid cell: from the cell itself
+        if (!locate_cell<T, ORDER, WJ>(sp.cell[slot_of(o)], g, t0x, t0y, t0z, bad, d)) continue;
+        seen = ~0u;
+      }
+      seen |= 1u << lx | 0x10000u << ly;
+      if (WJ) seen |= 1u << (d.jx & 15) | 0x10000u << (d.jy & 15);
       if (next_counts) {  // the tile of this position groups the particle in the next step
-        const int nb = neighbour_of_cell(d.i, d.j, d.k, ti, tj, tk, tg);
+        if (dealt && !tg.distinct) {
+          d.i = wrapi(t0x + lx - 1, g.nx);
+          d.j = wrapi(t0y + ly - 1, g.ny);
+          d.k = wrapi(t0z + lz - 1, g.nz);
+        }
+        const int nb = neighbour_of_box(dealt ? lx : -1, ly, lz, d.i, d.j, d.k, ti, tj, tk, tg);
         const unsigned long long own = __ballot(nb == 13);
         if (nb == 13) {
           if (__lane_id() == __ffsll(own) - 1) atomicAdd(&cnt[13], __popcll(own));
@@ -1309,6 +1379,11 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
         }
       }
     }
+    if (box_faces && parts == 1) {  // faces x-, y-, x+, y+ of the mask below, one atomic per wave
+      const int mine = (__any(seen & 1u) ? 1 : 0) | (__any(seen >> 16 & 1u) ? 2 : 0) |
+                       (__any(seen >> (kTile + 1) & 1u) ? 8 : 0) | (__any(seen >> (kTile + 17) & 1u) ? 16 : 0);
+      if ((threadIdx.x & 63) == 0 && mine) atomicOr(&L.cross, mine);
+    }
     __syncthreads();
   }
   if (next_counts && threadIdx.x < 27) {
@@ -1318,31 +1393,12 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
   }
   // Only particles that left the tile since the grouping reach the outermost layers of the
   // box (in-tile particles touch layers 1 .. B - 2), so with box_faces the tile stages only
-  // the x and y layers that hold a nonzero value: bit f of its face mask (faces x-, y-, z- at
-  // layer 0, then at layer B - 1) is set when face f does, and the reduction reads nothing
-  // outside.  z rows are always staged whole (their ends share memory sectors with the rest).
+  // the x and y layers that a particle reached (box index 0 or kTile + 1): bit f of its face mask
+  // (faces x-, y-, z- at layer 0, then at layer B - 1) is set when face f was, and the reduction
+  // reads nothing outside.  z rows are always staged whole (their ends share memory sectors with the rest).
   int faces = 0x3F;
   if (box_faces && parts == 1) {
-    int mine = 4 | 32;  // faces this thread found nonzero, then OR-reduced over the wave: one atomic per wave
-    for (int e = threadIdx.x; e < 4 * X::B2; e += blockDim.x) {
-      const int k = e / X::B2, uv = e - k * X::B2, u = uv / X::B, v = uv - u * X::B;
-      const int f = (k & 1) + 3 * (k >> 1);  // x-, y-, x+, y+
-      const int l = k < 2 ? 0 : X::B - 1;
-      const int n = (k & 1) == 0 ? X::at(l, u, v) : X::at(u, l, v);
-      bool nz = rbox[n] != 0;
-      if (WJ) {
-        if constexpr (PACK)
-          nz = nz || reinterpret_cast<const unsigned long long*>(box)[n] != 0ull || box[2 * X::B3 + n] != 0;
-        else
-          nz = nz || box[X::B3 + n] != 0 || box[2 * X::B3 + n] != 0 || box[3 * X::B3 + n] != 0;
-      }
-      if (nz) mine |= 1 << f;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mine |= __shfl_xor(mine, o, 64);
-    if ((threadIdx.x & 63) == 0 && mine) atomicOr(&L.cross, mine);
-    __syncthreads();
-    faces = L.cross;
+    faces = L.cross | 4 | 32;
     if (threadIdx.x == 0) box_faces[tile] = faces;
   }
   const int lo[3] = {(faces & 1) ? 0 : 1, (faces & 2) ? 0 : 1, (faces & 4) ? 0 : 1};

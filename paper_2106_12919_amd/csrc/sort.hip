@@ -334,6 +334,7 @@ TileGeom make_tiles(const GridGeom& g) {
   t.nty = (g.ny + kTile - 1) / kTile;
   t.ntz = (g.nz + kTile - 1) / kTile;
   t.ntiles = t.ntx * t.nty * t.ntz;
+  t.distinct = g.nx % kTile == 0 && g.ny % kTile == 0 && g.nz % kTile == 0 && t.ntx > 2 && t.nty > 2 && t.ntz > 2;
   return t;
 }
 

@@ -193,3 +193,13 @@ def test_centerings_in_one_launch(dtype, shape, order):
                 ref = centre(names[what][d], src[d], order // 2)
                 assert max_rel(np64(got[d]), ref) <= tol, (direction, what, d)
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("shape,order", [((24, 24, 24), 1), ((24, 32, 24), 3), ((16, 24, 32), 3), ((8, 24, 24), 1),
+                                         ((36, 24, 54), 3)])
+def test_particles_leaving_tiles(dtype, shape, order):
+    """The neighbour tile and the faces of a tile's box from the box indices (three or more whole tiles along
+    every axis), on one and two tiles along an axis and on ragged ones, where it comes from the cells."""
+    banner(f"pic_step 4 steps, particles leaving tiles dtype={dtype} shape={shape} order={order}")
+    steps_against_oracle(shape, 2, order, 8, dtype, 4)
