@@ -259,12 +259,12 @@ void deposit_tiled(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& s
 // Parts each tile of a species of n particles is best deposited in (1 on all but small grids).  With parts > 1
 // deposit_tiled stages each part's integers in a slot of its own (room for ntiles * parts), writes the tiles'
 // scales (4 ntiles ints) to box_faces and takes no nbr_counts; ReduceArgs::parts says so to deposit_reduce.
-constexpr int kMaxParts = 8;
+constexpr int kMaxParts = 8, kDepositFill = 256;
 template <typename T>
 int deposit_parts(const TileGeom& t, int64_t n);
 // Slots of the staging buffer a grid of t.ntiles tiles may use.
 inline size_t stage_slots(const TileGeom& t) {
-  const int fill = 512 / t.ntiles;
+  const int fill = kDepositFill / t.ntiles;
   return (size_t)t.ntiles * (size_t)(fill < 1 ? 1 : fill > kMaxParts ? kMaxParts : fill);
 }
 // How deposit_reduce starts each node and what else it folds in.  By default it adds to the

@@ -2589,17 +2589,19 @@ void allow_lds(const void* kernel, size_t bytes) {
 
 int deposit_box(int shape_order) { return kTile + (shape_order == 1 ? 2 : 4) + 1; }
 int deposit_stage_slot(int shape_order) { return shape_order == 1 ? StageRows<1>::SLOT : StageRows<3>::SLOT; }
-// Workgroups per tile on grids of few tiles: as many as fill the device twice, as long as each has
+// Workgroups per tile on grids of few tiles: as many as fill the device (``blocks``), as long as each has
 // ``least`` particles on average, at most kMaxParts.  One workgroup per tile leaves most compute units idle
-// there: 32^3 (64 tiles), 8 per cell, linear, FP64: deposition 110 -> 29 us, gather 42 -> 16 (reduction 9 ->
-// 24: it sums the parts); the whole call of one step 208 -> 166; cubic FP32, 5 steps 1414 -> 663.
-int tile_parts_for(const TileGeom& t, int64_t n, int least) {
-  const int64_t fill = 512 / t.ntiles, have = n / ((int64_t)t.ntiles * least);
+// there: 32^3 (64 tiles), 8 per cell, linear, FP64: deposition 110 -> 43 us, gather 42 -> 16 (reduction 9 ->
+// 23: it sums the parts); the whole call of one step 208 -> 157; cubic FP32, 5 steps 1414 -> 649.
+// The gather fills the device twice, the deposition once: each part stages a slot and reads the tile's bounds,
+// and with twice the parts the reduction took 32 us (cubic FP64, 5 steps 823 -> 899; 48^3, linear 287 -> 313).
+int tile_parts_for(const TileGeom& t, int64_t n, int least, int blocks) {
+  const int64_t fill = blocks / t.ntiles, have = n / ((int64_t)t.ntiles * least);
   return (int)std::max<int64_t>(1, std::min<int64_t>(std::min(fill, have), kMaxParts));
 }
 template <typename T>
 int deposit_parts(const TileGeom& t, int64_t n) {
-  return tile_parts_for(t, n, DepositOrder<T>::CH);
+  return tile_parts_for(t, n, DepositOrder<T>::CH, kDepositFill);
 }
 template <typename T>
 void gather_push_tiled(const GridGeom& g, const TileGeom& t, const T* const E[3], const T* const B[3],
@@ -2619,7 +2621,7 @@ void gather_push_tiled(const GridGeom& g, const TileGeom& t, const T* const E[3]
   const dim3 block(g.shape_order == 1 ? kGatherBlock<T, 1> : kGatherBlock<T, 3>);
   // few tiles: several workgroups per tile, each with the tile's field box (not with nbr_bases, whose runs
   // one workgroup fills)
-  const int parts = nbr_bases ? 1 : tile_parts_for(t, in.n, (int)block.x);
+  const int parts = nbr_bases ? 1 : tile_parts_for(t, in.n, (int)block.x, 512);
   const dim3 grid(t.ntiles + 1, parts);
   if (home_cursor) {
     if (g.shape_order == 1) {
