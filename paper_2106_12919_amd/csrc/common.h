@@ -107,7 +107,7 @@ constexpr FftPlan plan_of(int n, bool z) {
   p.twcount = off;
   return p;
 }
-inline FftPlan make_fft_plan(int n, bool z) { return plan_of(n, z); }
+inline FftPlan make_fft_plan(int n, bool z = false) { return plan_of(n, z); }
 // FP64 twiddles of a plan, 2*twcount doubles (re, im) of exp(-2 pi i k r/(ns R)).
 void fft_twiddles(const FftPlan& p, double* out);
 
