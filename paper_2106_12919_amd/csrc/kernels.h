@@ -248,7 +248,7 @@ void permute_species(const SpeciesView<T>& in, const SpeciesView<T>& out, const 
 // deposit_reduce zeroes it again (ReduceArgs::work).
 // ``spill_flag`` (optional) is set to 1 whenever a particle goes to rho/J directly.  With
 // ``box_faces`` (ntiles ints, optional; used on grids of whole tiles) each tile stages only
-// the layers of its box that hold a nonzero value and records which outer faces it staged,
+// the layers of its box that its particles reached and records which outer faces it staged,
 // for a deposit_reduce with the same array in ReduceArgs::box_faces.  ``deal`` (optional, one per slot;
 // cubic shapes) receives the order in which each tile's particles were visited, chunk by chunk.
 template <typename T>
