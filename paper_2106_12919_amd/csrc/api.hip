@@ -188,6 +188,13 @@ struct Engine : EngineBase {
   cplx<T>* Ah[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};  // averaged <E>, <B> spectra
   T* tmp = nullptr;
   std::vector<void*> allocs;
+  // Memory that its last launch leaves at zero for the next one, also from one call to the next: the tile
+  // counts (by the scan), the deposition's tile counter and the spill arrays with their flags (by the
+  // reduction).  A call that returns an error may have counted without the scan that follows, and a scan of
+  // two steps' counts gives slots past the particles' arrays: such a call zeroes all of it (settled()).
+  // ``unsettled``: that is still to be done.
+  bool unsettled = false;
+  bool grown = false;  // ensure_species has launched the clearing of new counts
 
   ~Engine() override {
     for (void* a : allocs) (void)hipFree(a);
@@ -210,8 +217,29 @@ struct Engine : EngineBase {
       }
     return hipSuccess;
   }
+  // zeroes the tile counts of ``x`` on ``st`` (a kernel, so that a captured call may do it)
+  void zero_counts(const SpeciesScratch<T>& x, hipStream_t st) {
+    Batch<float*> z{};  // (ints: the same bits)
+    for (int b = 0; b < 2; ++b) z.p[b] = reinterpret_cast<float*>(x.counts[b]);
+    zero_arrays<float>(z, 2, (int64_t)tiles.ntiles + 1, st);
+  }
+  // zeroes what every finished call leaves at zero
+  void settle(size_t cells, hipStream_t st) {
+    for (const SpeciesScratch<T>& x : sps)
+      if (x.cap > 0) zero_counts(x, st);
+    Batch<float*> z{};
+    z.p[0] = reinterpret_cast<float*>(t_counts);
+    zero_arrays<float>(z, 1, (int64_t)tiles.ntiles + 1, st);
+    z.p[0] = reinterpret_cast<float*>(work);
+    zero_arrays<float>(z, 1, 1, st);
+    z.p[0] = reinterpret_cast<float*>(spill_flag);
+    zero_arrays<float>(z, 1, 2, st);
+    Batch<T*> sp{};
+    for (int q = 0; q < 4; ++q) sp.p[q] = spill[q];
+    zero_arrays<T>(sp, 4, (int64_t)cells, st);
+  }
   // grows the scratch of species s to n particles
-  hipError_t ensure_species(size_t s, int64_t n) {
+  hipError_t ensure_species(size_t s, int64_t n, hipStream_t st) {
     if (sps.size() <= s) sps.resize(s + 1);
     SpeciesScratch<T>& x = sps[s];
     if (x.cap >= n) return hipSuccess;
@@ -225,7 +253,6 @@ struct Engine : EngineBase {
     const size_t nt = (size_t)tiles.ntiles;
     for (int b = 0; b < 2; ++b) {
       if ((e = alloc(&x.counts[b], nt + 1)) != hipSuccess) return e;
-      if ((e = hipMemset(x.counts[b], 0, sizeof(int) * (nt + 1))) != hipSuccess) return e;
       if ((e = alloc(&x.starts[b], nt + 2)) != hipSuccess) return e;
     }
     if ((e = alloc(&x.cursor, nt + 1)) != hipSuccess) return e;
@@ -239,7 +266,8 @@ struct Engine : EngineBase {
     if ((e = alloc(&x.w, m)) != hipSuccess) return e;
     if ((e = alloc(&x.perm, m)) != hipSuccess) return e;
     if ((e = alloc(&x.deal, m)) != hipSuccess) return e;
-    if ((e = hipStreamSynchronize(nullptr)) != hipSuccess) return e;  // the cleared counts, before any stream's use
+    zero_counts(x, st);
+    grown = true;
     x.cap = n;
     return hipSuccess;
   }
@@ -674,7 +702,7 @@ pic_status deposit_yee_all(pic_ctx c, const pic_species* sp, int nsp, pic_fields
     if (sp[s].n == 0) continue;
     const SpeciesView<T> v = view<T>(sp[s]);
     const bool wj = with_j && std::isfinite(sp[s].m);
-    if (e.ensure_species((size_t)s, sp[s].n) != hipSuccess) {  // no scratch: the untiled path
+    if (e.ensure_species((size_t)s, sp[s].n, c->stream) != hipSuccess) {  // no scratch: the untiled path
       (void)hipGetLastError();
       // its float atomics add in an order that varies between runs
       if (g.det) return c->fail(PIC_ENOMEM, "pic_deposit: no scratch for the deterministic tiled deposition");
@@ -707,7 +735,7 @@ pic_status do_deposit(pic_ctx c, const pic_species* sp, int nsp, pic_fields* f, 
     if (sp[s].n == 0) continue;
     int* perm = sort_idx;
     if (!sort_idx) {
-      hipError_t he = e.ensure_species((size_t)s, sp[s].n);
+      hipError_t he = e.ensure_species((size_t)s, sp[s].n, c->stream);
       if (he != hipSuccess) return c->fail(PIC_ENOMEM, std::string("pic_deposit: ") + hipGetErrorString(he));
       perm = e.sps[s].perm;
     }
@@ -750,7 +778,7 @@ pic_status do_gather_push(pic_ctx c, const pic_fields* f, pic_species* sp, int n
   }
   for (int s = 0; s < nsp; ++s)
     if (std::isfinite(sp[s].m) && sp[s].n > 0) {
-      hipError_t he = e.ensure_species((size_t)s, sp[s].n);
+      hipError_t he = e.ensure_species((size_t)s, sp[s].n, c->stream);
       if (he != hipSuccess) return c->fail(PIC_ENOMEM, std::string("pic_gather_push: ") + hipGetErrorString(he));
       SpeciesScratch<T>& x = e.sps[s];
       const SpeciesView<T> v = view<T>(sp[s]);
@@ -1026,7 +1054,7 @@ pic_status do_step_yee(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int n
   }
   pic_status st;
   for (int q = 0; q < nsp; ++q) {
-    hipError_t he = e.ensure_species((size_t)q, sp[q].n);
+    hipError_t he = e.ensure_species((size_t)q, sp[q].n, c->stream);
     if (he != hipSuccess) return c->fail(PIC_ENOMEM, std::string("pic_step: ") + hipGetErrorString(he));
   }
   const size_t N = ncells(p);
@@ -1109,7 +1137,7 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
   std::vector<char> in_scratch(nsp, 0);
   std::vector<int> layout(nsp, 0);  // which of the species' two groupings describes its current arrays
   for (int q = 0; q < nsp; ++q) {
-    hipError_t he = e.ensure_species((size_t)q, sp[q].n);
+    hipError_t he = e.ensure_species((size_t)q, sp[q].n, c->stream);
     if (he != hipSuccess) return c->fail(PIC_ENOMEM, std::string("pic_step: ") + hipGetErrorString(he));
   }
   pic_status st;
@@ -1301,7 +1329,7 @@ pic_status do_step_adjoint(pic_ctx c, pic_fields* f, const pic_species* sp, int 
   }
   for (int q = 0; q < nsp; ++q) {
     if (sp[q].n == 0) continue;
-    hipError_t he = e.ensure_species((size_t)q, sp[q].n);
+    hipError_t he = e.ensure_species((size_t)q, sp[q].n, c->stream);
     if (he == hipSuccess && !e.astage) {
       const size_t B = (size_t)deposit_box(p.shape_order);
       he = e.alloc(&e.astage, (size_t)e.tiles.ntiles * 6 * B * B * B);
@@ -1439,10 +1467,48 @@ pic_status device_ok(pic_ctx c) {
   return PIC_OK;
 }
 
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return cs != hipStreamCaptureStatusNone;
+}
+
+// Runs ``call`` between two states in which the memory of Engine::unsettled is zero: zeroes it after a call
+// that fails, and before one where that could not be launched.  While the stream is being captured nothing
+// runs until the graph does, so whatever comes next zeroes it again.
+template <typename T, typename Call>
+pic_status settled(pic_ctx c, Call call) {
+  Engine<T>& e = static_cast<Engine<T>&>(*c->eng);
+  const size_t cells = ncells(c->p);
+  bool later = false;  // zeroed only with the graph, or not at all
+  if (e.unsettled) {
+    e.settle(cells, c->stream);
+    later = capturing(c->stream);
+  }
+  e.unsettled = true;
+  e.grown = false;
+  const pic_status st = call();
+  if (st != PIC_OK) {
+    e.settle(cells, c->stream);
+    later = hipGetLastError() != hipSuccess || capturing(c->stream);
+  } else if (e.grown) {
+    later = later || capturing(c->stream);
+  }
+  e.unsettled = later;
+  return st;
+}
+
 }  // namespace
 
 #define PIC_DISPATCH(ctx, fn, ...) \
   ((ctx)->p.dtype == PIC_F32 ? fn<float>(ctx, __VA_ARGS__) : fn<double>(ctx, __VA_ARGS__))
+// the calls that sort or deposit particles
+#define PIC_DISPATCH_SETTLED(ctx, fn, ...)                                                          \
+  ((ctx)->p.dtype == PIC_F32 ? settled<float>(ctx, [&]() { return fn<float>(ctx, __VA_ARGS__); })  \
+                             : settled<double>(ctx, [&]() { return fn<double>(ctx, __VA_ARGS__); }))
 
 extern "C" {
 
@@ -1522,7 +1588,7 @@ pic_status pic_deposit(pic_ctx ctx, const pic_species* sp, int nsp, pic_fields* 
   const bool wj = mode == PIC_DEP_RHO_AND_J, yee = yee_cycle(ctx->p);  // staggered cycle: J into J_stag
   if ((st = check_fields(ctx, f, false, false, false, false, wj && !yee, wj && yee, false, true)) != PIC_OK)
     return st;
-  return PIC_DISPATCH(ctx, do_deposit, sp, nsp, f, mode);
+  return PIC_DISPATCH_SETTLED(ctx, do_deposit, sp, nsp, f, mode);
 }
 
 pic_status pic_deposit_noalloc(pic_ctx ctx, const pic_species* sp, int nsp, pic_fields* f, int mode) {
@@ -1539,7 +1605,7 @@ pic_status pic_deposit_noalloc(pic_ctx ctx, const pic_species* sp, int nsp, pic_
   if (!ctx->noalloc) return ctx->fail(PIC_EHIP, "pic_deposit_noalloc: " + ctx->noalloc_err);
   const bool wj = mode == PIC_DEP_RHO_AND_J;
   if ((st = check_fields(ctx, f, false, false, false, false, wj, false, false, true)) != PIC_OK) return st;
-  return PIC_DISPATCH(ctx, do_deposit, sp, nsp, f, mode, static_cast<int*>(ctx->noalloc));
+  return PIC_DISPATCH_SETTLED(ctx, do_deposit, sp, nsp, f, mode, static_cast<int*>(ctx->noalloc));
 }
 
 pic_status pic_center(pic_ctx ctx, int dir, int what, pic_fields* f) {
@@ -1580,7 +1646,7 @@ pic_status pic_gather_push(pic_ctx ctx, const pic_fields* f, pic_species* sp, in
   if ((st = check_species(ctx, sp, nsp)) != PIC_OK) return st;
   const bool yee = yee_cycle(ctx->p);  // the staggered cycle gathers from the Yee-grid arrays
   if ((st = check_fields(ctx, f, yee, yee, !yee, !yee, false, false, false, false)) != PIC_OK) return st;
-  return PIC_DISPATCH(ctx, do_gather_push, f, sp, nsp);
+  return PIC_DISPATCH_SETTLED(ctx, do_gather_push, f, sp, nsp);
 }
 
 pic_status pic_step(pic_ctx ctx, pic_fields* f, pic_species* sp, int nsp, int nsteps) {
@@ -1590,7 +1656,7 @@ pic_status pic_step(pic_ctx ctx, pic_fields* f, pic_species* sp, int nsp, int ns
   if ((st = check_species(ctx, sp, nsp)) != PIC_OK) return st;
   if ((st = check_fields(ctx, f, true, true, true, true, true, true, true, true)) != PIC_OK) return st;
   if ((st = check_avg(ctx, f)) != PIC_OK) return st;
-  return PIC_DISPATCH(ctx, do_step, f, sp, nsp, nsteps);
+  return PIC_DISPATCH_SETTLED(ctx, do_step, f, sp, nsp, nsteps);
 }
 
 pic_status pic_step_adjoint(pic_ctx ctx, pic_fields* f, const pic_species* sp, int nsp, pic_fields* adj,
@@ -1611,7 +1677,7 @@ pic_status pic_step_adjoint(pic_ctx ctx, pic_fields* f, const pic_species* sp, i
       if ((st = check_ptr(ctx, asp[q].u[d], "adjoint u")) != PIC_OK) return st;
     }
   }
-  return PIC_DISPATCH(ctx, do_step_adjoint, f, sp, nsp, adj, asp);
+  return PIC_DISPATCH_SETTLED(ctx, do_step_adjoint, f, sp, nsp, adj, asp);
 }
 
 pic_status pic_sync(pic_ctx ctx) {
