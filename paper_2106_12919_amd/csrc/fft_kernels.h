@@ -536,8 +536,9 @@ constexpr SolveShape<T> solve_shape(int n) {
 // in the same LDS tile, adds each one's part of the update to the six updated fields, which stay in
 // registers, and transforms those back.  As three kernels (x pass, update, inverse x pass) they move 54
 // spectra between HBM and the chip, here 18 (the tables are even in kx, so lines read them for
-// kx <= N / 2 only).  216 x 216 x 288 FP64: 532 + 450 + 268 us -> 865; the whole solve at 256^3: FP32 1890 ->
-// 1507 us, FP64 3563 -> 2702.  Bound by its chain of 17 transforms (2 barriers per stage) at two
+// kx <= N / 2 only).  The whole solve at 256^3: FP32 1890 -> 1485 us, FP64 3563 -> 2650.  Every sum is
+// formed in the order of k_psatd_update, so the results are as accurate: terms that wait for a later
+// source are kept in LDS (in registers they spilled, 96 x 96 x 192 FP64 267 -> 319 us).  Bound by its chain of 17 transforms (2 barriers per stage) at two
 // workgroups per CU.  The same fusion of pic_step's resident state (40 arrays against 25) was no faster
 // than the separate kernels (384 x 384 x 768 FP32 4.1 ms either way, 128 x 128 x 256 142 against 128 us).
 template <typename T, int N>
@@ -546,7 +547,8 @@ __global__ void __launch_bounds__(solve_shape<T>(N).block, sizeof(T) == 4 ? 4 : 
   constexpr int TOTAL = N * TL, PER = (TOTAL + BLOCK - 1) / BLOCK, ROWS = BLOCK / TL;
   extern __shared__ __align__(16) unsigned char smem[];
   cplx<T>* tile = reinterpret_cast<cplx<T>*>(smem);
-  cplx<T>* twl = tile + TOTAL;
+  cplx<T>* kept = tile + TOTAL;  // two values per element, read by the thread that wrote them
+  cplx<T>* twl = kept + 2 * TOTAL;
   for (int e = threadIdx.x; e < N - 1; e += BLOCK) twl[e] = tw[e];
   const int col0 = xcd_major(blockIdx.x, gridDim.x) * TL;
   const int i = (int)threadIdx.x % TL, j0 = (int)threadIdx.x / TL;
@@ -618,43 +620,53 @@ __global__ void __launch_bounds__(solve_shape<T>(N).block, sizeof(T) == 4 ? 4 : 
     F[5][u] = csub(cscale(bz, C), cscale(csub(cmul(px, ey), cmul(py, ex)), Sw));
     settle(u);
   }
+  // J^d: -Sw J to E^d and X1 (D+ x J) to B, each component of the curl formed before it is added, as
+  // k_psatd_update does: the earlier of its two terms waits in the thread's own places of LDS
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {  // J^d: -Sw J to E^d, X1 D+ x J to the two other components of B
+  for (int d = 0; d < 3; ++d) {
     put(v);
     load(a.src[7 + d], v);
     fft_lds_static_inplace<T, -1, N, TL, true, BLOCK>(tile, twl, tid());
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      const T Sw = table(a.Sw, u), X1 = table(a.X1, u);
-      const cplx<T> j = own(u), xj = cscale(j, X1);
-      F[d][u] = csub(F[d][u], cscale(j, Sw));
-      const cplx<T> px = dx(a.Dp[0], u);
+      if (!has(u)) continue;
+      cplx<T>* const k0 = kept + tid() + u * BLOCK;
+      cplx<T>* const k1 = k0 + TOTAL;
+      const T X1 = table(a.X1, u);
+      const cplx<T> j = own(u), px = dx(a.Dp[0], u);
+      F[d][u] = csub(F[d][u], cscale(j, table(a.Sw, u)));
       if (d == 0) {
-        F[4][u] = cadd(F[4][u], cmul(pz, xj));
-        F[5][u] = csub(F[5][u], cmul(py, xj));
+        *k0 = cmul(pz, j);
+        *k1 = cmul(py, j);
       } else if (d == 1) {
-        F[5][u] = cadd(F[5][u], cmul(px, xj));
-        F[3][u] = csub(F[3][u], cmul(pz, xj));
+        F[5][u] = cadd(F[5][u], cscale(csub(cmul(px, j), *k1), X1));
+        *k1 = cmul(pz, j);
       } else {
-        F[3][u] = cadd(F[3][u], cmul(py, xj));
-        F[4][u] = csub(F[4][u], cmul(px, xj));
+        F[3][u] = cadd(F[3][u], cscale(csub(cmul(py, j), *k1), X1));
+        F[4][u] = cadd(F[4][u], cscale(csub(*k0, cmul(px, j)), X1));
       }
       settle(u);
     }
   }
-  // rho^{n+1}, then rho^n: (X3 rho^n - X2 rho^{n+1}) D+ to E
+  // (X3 rho^n - X2 rho^{n+1}) D+ to E, the difference first
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
     put(v);
-    load(a.src[10], v);  // rho^n (the second time a reload that nothing uses)
+    if (r == 0) load(a.src[10], v);  // rho^n
     fft_lds_static_inplace<T, -1, N, TL, true, BLOCK>(tile, twl, tid());
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      const cplx<T> rr = cscale(own(u), r == 0 ? -table(a.X2, u) : table(a.X3, u));
-      F[0][u] = cadd(F[0][u], cmul(rr, dx(a.Dp[0], u)));
-      F[1][u] = cadd(F[1][u], cmul(rr, py));
-      F[2][u] = cadd(F[2][u], cmul(rr, pz));
-      settle(u);
+      if (!has(u)) continue;
+      cplx<T>* const k0 = kept + tid() + u * BLOCK;
+      if (r == 0) {
+        *k0 = cscale(own(u), table(a.X2, u));
+      } else {
+        const cplx<T> rr = csub(cscale(own(u), table(a.X3, u)), *k0);
+        F[0][u] = cadd(F[0][u], cmul(rr, dx(a.Dp[0], u)));
+        F[1][u] = cadd(F[1][u], cmul(rr, py));
+        F[2][u] = cadd(F[2][u], cmul(rr, pz));
+        settle(u);
+      }
     }
   }
 #pragma unroll
@@ -706,7 +718,8 @@ struct FftLength {
   static void solve_x(const SolveX<T>& a, const cplx<T>* tw, hipStream_t s) {
     constexpr SolveShape<T> S = solve_shape<T>(N);
     if constexpr (S.lines > 0) {
-      constexpr size_t lds = fft_lds_bytes<T>((size_t)S.lines * N, N);
+      constexpr size_t lds = fft_lds_bytes<T>(3 * (size_t)S.lines * N, N);
+      static_assert(lds <= 160 * 1024, "fits the LDS");
       allow_lds((const void*)k_solve_x<T, N>, lds);
       hipLaunchKernelGGL((k_solve_x<T, N>), dim3((unsigned)(a.ny * a.pz / S.lines)), dim3(S.block), lds, s, a, tw);
     }
