@@ -27,7 +27,6 @@
 
 #include "fft_kernels.h"
 
-
 namespace pic {
 
 namespace {
@@ -110,12 +109,10 @@ void Fft3D<T>::forward(const Batch<const T*>& in, const Batch<cplx<T>*>& out, in
   if (x_pass) ops[0]->strided[0](cin, out, count, tw[0], 1, ny * pz, 0, (long long)ny * pz, lc, 0, s);
 }
 
-// From 3 MB per array on: below, the kernel's chain of 17 transforms in one workgroup takes longer than
-// three launches (FP32 32^3 31.6 against 27.8 us, 64 x 64 x 128 69.7 against 69.1, 96^3 102 against 105, 96 x 96 x 192
-// 146 against 168; FP64 32^3 33.5 against 31.7, 64^3 66.6 against 66.9, 64 x 64 x 128 91 against 102).
+// (the rule and its measurements: solve_from_kib)
 template <typename T>
 bool Fft3D<T>::solves_along_x() const {
-  return ops[0]->solve_x != nullptr && (size_t)nx * ny * nz * sizeof(T) >= (size_t)3 << 20;
+  return ops[0]->solve_x != nullptr && (size_t)nx * ny * nz * sizeof(T) >= ops[0]->solve_from;
 }
 
 template <typename T>

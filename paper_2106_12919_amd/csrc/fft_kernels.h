@@ -18,8 +18,10 @@ struct FftOps {
   void (*strided[2])(const Batch<const cplx<T>*>& in, const Batch<cplx<T>*>& out, int count, const cplx<T>* tw,
                      int outer_count, int inner_count, long long outer_stride, long long elem_stride,
                      const LineCenter<T>& lc, int axis, hipStream_t s);  // forward, inverse
-  // x pass, standard update and inverse x pass in one kernel (null where it is not built)
+  // x pass, standard update and inverse x pass in one kernel (null where it is not built), and the bytes
+  // per array from which it is the faster form
   void (*solve_x)(const SolveX<T>& a, const cplx<T>* tw, hipStream_t s);
+  size_t solve_from;
 };
 // The axis lengths pic_init accepts: every even 2^a 3^b in [8, 1024].  fft_len.hip is compiled once per
 // unit u = 0 .. kFftUnits - 1 (in parallel) with the lengths at u, u + kFftUnits, ...
@@ -521,9 +523,35 @@ template <typename T>
 struct SolveShape {
   int lines, block;
 };
+
+// KiB per array from which the fused pass is the faster one along x lines of n points (0: on no grid, so it is
+// not built).  psatd_push_fields timed with it and with the separate kernels at 3 to 100 MiB per array, all
+// lengths (fused / separate): mostly 0.85 to 0.95 from 3 MiB on, 0.75 to 0.8 from 50.  Below, its chain of 17
+// transforms in one workgroup takes longer than three launches (FP32 32^3 31.6 against 27.8 us, FP64 33.5
+// against 31.7); lengths with few workgroups per array need some more (FP32, 3 MiB: 108 points 1.02 to 1.04, 192
+// 1.10, 512 1.04, 768 1.11).  With more registers than the workgroup has (FP32 162 1.05 at 5 MiB and 0.95 at 6;
+// 486 1.06 at 17 and 0.93 at 34; 648 1.06 at 16 and 0.99 at 100; FP64 144 1.10 at 23 and 0.95 at 30; 486 1.01 at
+// 173) or one workgroup per CU (FP64 108 1.14 at 10 MiB, 1.02 at 29, 0.94 at 51; 162 and 324 1.05 at 16, 0.93 at
+// 29) only large grids gain, or none.  FP64 lines of 8 and 12 points occupy 64 and 96 of a workgroup's 256 threads: 1.14 and
+// 1.08 at 16 MiB.
+template <typename T>
+constexpr int solve_from_kib(int n) {
+  switch (sizeof(T) == 4 ? n : -n) {
+    case 108: case 144: case -72: case -512: return 3584;
+    case 192: case 512: case 768: return 4096;
+    case 162: return 6 << 10;
+    case -162: case -324: return 24 << 10;
+    case -144: return 28 << 10;
+    case 486: return 32 << 10;
+    case -108: return 48 << 10;
+    case 648: case -8: case -12: case -486: return 0;
+    default: return 3 << 10;
+  }
+}
 template <typename T>
 constexpr SolveShape<T> solve_shape(int n) {
   const int per = sizeof(T) == 4 ? 6 : 3, wide = sizeof(T) == 4 ? 16 : 8;
+  if (solve_from_kib<T>(n) == 0) return {0, 0};
   if (n * wide <= 256 * per) return {wide, 256};
   if (n * wide <= 512 * per) return {wide, 512};
   if (n * wide / 2 <= 512 * per) return {wide / 2, 512};
@@ -725,7 +753,8 @@ struct FftLength {
     }
   }
   static constexpr FftOps<T> ops = {&r2c, &c2r, {&strided<-1>, &strided<+1>},
-                                    solve_shape<T>(N).lines > 0 ? &solve_x : nullptr};
+                                    solve_shape<T>(N).lines > 0 ? &solve_x : nullptr,
+                                    (size_t)solve_from_kib<T>(N) << 10};
 };
 
 }  // namespace

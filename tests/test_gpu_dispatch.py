@@ -231,3 +231,16 @@ def test_field_solve_fused_along_x_rounds_as_the_separate_kernels():
     fused, separate = err.values()
     assert fused[0] <= 1.002 * separate[0], ("E", fused, separate)
     assert fused[1] <= 1.002 * separate[1], ("B", fused, separate)
+
+
+# both sides of the sizes from which the fused x pass is taken, per group of lengths, and lengths without it
+FUSED_FROM = [("f32", (192, 36, 128)), ("f32", (192, 48, 128)), ("f32", (768, 24, 64)), ("f32", (162, 54, 144)),
+              ("f32", (162, 64, 162)), ("f32", (486, 128, 144)), ("f32", (648, 64, 96)), ("f64", (16, 128, 216)),
+              ("f64", (72, 48, 144)), ("f64", (128, 64, 72)), ("f64", (162, 108, 192)), ("f64", (144, 162, 162)),
+              ("f64", (108, 216, 288)), ("f64", (12, 192, 256)), ("f64", (486, 32, 48))]
+
+
+@pytest.mark.parametrize("dtype,shape", FUSED_FROM)
+def test_field_solve_around_the_fused_sizes(dtype, shape):
+    """psatd_push_fields on both sides of the rule that chooses the fused x pass."""
+    test_field_solve_fused_along_x(dtype, shape, False)
