@@ -197,9 +197,9 @@ pic_status pic_deposit(pic_ctx ctx, const pic_species* sp, int nsp, pic_fields* 
 
 /* pic_deposit for callers that cannot allocate device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and kernels as
- * pic_deposit (hybrid cycle), but the per-call tile sort of each species (two int32 per
+ * pic_deposit (hybrid cycle), but the per-call tile sort of each species (one int32 per
  * particle), which pic_deposit keeps in context scratch allocated on a species' first use, lives
- * in a static device array of 32 MiB that the library holds on each GPU until the process ends;
+ * in a static device array of 16 MiB that the library holds on each GPU until the process ends;
  * the call itself allocates and frees nothing (pic_init, which allocates, must have run).
  * Limits and errors: at most 4,194,304 particles per species per call (PIC_EUNSUPPORTED beyond);
  * PIC_EUNSUPPORTED with PIC_STAGGERED_CYCLE; PIC_EHIP if the array's device address could not be

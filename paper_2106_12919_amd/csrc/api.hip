@@ -13,12 +13,13 @@
 
 using namespace pic;
 
-// Scratch of pic_deposit_noalloc: the per-call tile sort of each species (at most two int32 per
-// particle) for callers that cannot allocate device memory.  A file-scope device array: each GPU the library runs on holds its own copy until the
-// process ends, and every call on that GPU shares it.  Host code reaches it only through the
-// per-device address hipGetSymbolAddress returns (scratch_address below), never by its name.
-constexpr size_t kNoAllocScratchBytes = size_t(32) << 20;
-constexpr int64_t kNoAllocMaxParticles = (int64_t)(kNoAllocScratchBytes / (2 * sizeof(int)));
+// Scratch of pic_deposit_noalloc: the per-call tile sort of each species (the particle of each slot, one
+// int32 per particle) for callers that cannot allocate device memory.  A file-scope device array: each GPU
+// the library runs on holds its own copy until the process ends, and every call on that GPU shares it.  Host
+// code reaches it only through the per-device address hipGetSymbolAddress returns (scratch_address below),
+// never by its name.
+constexpr int64_t kNoAllocMaxParticles = (int64_t)1 << 22;
+constexpr size_t kNoAllocScratchBytes = (size_t)kNoAllocMaxParticles * sizeof(int);
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
 namespace {
@@ -717,7 +718,7 @@ pic_status deposit_yee_all(pic_ctx c, const pic_species* sp, int nsp, pic_fields
 }
 
 // sort_idx: null = each species' sort indices in the context's species scratch (allocated on
-// first use); else 2 n int32 of caller-provided device memory (pic_deposit_noalloc).
+// first use); else n int32 of caller-provided device memory (pic_deposit_noalloc).
 template <typename T>
 pic_status do_deposit(pic_ctx c, const pic_species* sp, int nsp, pic_fields* f, int mode, int* sort_idx = nullptr) {
   Engine<T>& e = static_cast<Engine<T>&>(*c->eng);

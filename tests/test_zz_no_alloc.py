@@ -78,3 +78,25 @@ def test_noalloc_deposit_rejects_oversized_species():
     with pytest.raises(RuntimeError, match="particles in one species"):
         piclib.pic_deposit_noalloc(ctx.ctx, [sp], f)
     ctx.close()
+
+
+def test_noalloc_deposit_at_the_size_limit():
+    """The most particles the static array has places for."""
+    banner("pic_deposit_noalloc at its size limit")
+    shape, n = (64, 64, 64), 4194304
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    cell = torch.randint(0, 64 ** 3, (n,), generator=gen, device="cuda", dtype=torch.int32)
+    off = [torch.rand(n, generator=gen, device="cuda").clamp_(max=1 - 2.0 ** -24) for _ in range(3)]
+    u = [0.1 * torch.randn(n, generator=gen, device="cuda") for _ in range(3)]
+    ctx = piclib.Context(shape, (1.0, 1.0, 1.0), 0.5, 1, 4, 16, "f32")
+    sp = piclib.Species(cell, off, u, None, -1.0, 1.0, w_const=0.01)
+    fa, fb = piclib.Fields(shape, "f32"), piclib.Fields(shape, "f32")
+    piclib.pic_deposit_noalloc(ctx.ctx, [sp], fa)
+    piclib.pic_deposit(ctx.ctx, [sp], fb)
+    piclib.pic_sync(ctx.ctx)
+    tol = 1024 * EPS["f32"]  # the deposition's FP32 bound
+    assert max_rel(np64(fa.rho_new), np64(fb.rho_new)) <= tol
+    for d in range(3):
+        assert max_rel(np64(fa.J_nod[d]), np64(fb.J_nod[d])) <= tol, d
+    ctx.close()
