@@ -244,3 +244,24 @@ FUSED_FROM = [("f32", (192, 36, 128)), ("f32", (192, 48, 128)), ("f32", (768, 24
 def test_field_solve_around_the_fused_sizes(dtype, shape):
     """psatd_push_fields on both sides of the rule that chooses the fused x pass."""
     test_field_solve_fused_along_x(dtype, shape, False)
+
+
+@pytest.mark.parametrize("order", [3, 1])
+@pytest.mark.parametrize("dtype,ppc", [("f32", 3), ("f64", 1)])
+def test_several_chunks_in_whole_unsplit_tiles(monkeypatch, dtype, ppc, order):
+    """Whole tiles, three along every axis, each by one workgroup, some of them of several dealing chunks and
+    some empty: neighbour bases, faces gathered over the chunks, neighbours from the box indices and (cubic)
+    the published order together, as in the dense tiles of a beam.  The particles of the middle third of x
+    move to the first third, so that the average tile stays under two chunks (not split)."""
+    shape = (24, 24, 24)
+    banner(f"pic_step 4 steps, several chunks in whole tiles dtype={dtype} ppc={ppc} order={order}")
+    small = inputs.small
+
+    def crowded(*args, **kw):
+        wl = small(*args, **kw)
+        wl.electrons.cell = wl.electrons.cell.copy()
+        wl.electrons.cell[:, 0] -= 8 * (wl.electrons.cell[:, 0] // 8 == 1)
+        return wl
+
+    monkeypatch.setattr(inputs, "small", crowded)
+    steps_against_oracle(shape, ppc, order, 8, dtype, 4)
