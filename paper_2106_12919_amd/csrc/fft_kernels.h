@@ -203,8 +203,8 @@ __device__ inline void butterfly(const cplx<T>* __restrict__ src, cplx<T>* __res
 
 // The transform of lines whose length N and count NL per block are compile-time constants:
 // every stage's radix, stride and twiddle offset is a constant of plan_of(N), so butterfly
-// indices need no runtime division and LDS offsets become instruction immediates.  Same
-// butterflies, in the same order, as fft_lds.  Returns the buffer holding the result.
+// indices need no runtime division and LDS offsets become instruction immediates.  Returns the
+// buffer holding the result.
 template <typename T, int SIGN, int N, int NL, bool LINE_FASTEST, int S = 0>
 __device__ inline cplx<T>* fft_lds_static(cplx<T>* a, cplx<T>* b, const cplx<T>* __restrict__ tw) {
   constexpr FftPlan P = plan_of(N, !LINE_FASTEST);

@@ -378,8 +378,7 @@ static_assert((size_t)1024 * 1024 * 1024 * sizeof(float) - 1 <= 0xffffffffu, "fl
 // write nodes 4 apart and rows are B = 13 (odd) apart, so the 16-byte LDS stores of a wave spread over
 // the banks.  Gather + push: 384 x 384 x 768 FP32 6.21 -> 5.96 ms, 192 x 192 x 384 FP64 1786 -> 1734 us,
 // reverse mode's particle kernel 278 -> 273 us.  Cubic boxes only: a linear box (11 of 16 values used)
-// got slower (256^3, 8 per cell, FP32: 2.23 -> 2.39 ms).  FP32 rows not a multiple of 4 take one load per
-// node.
+// got slower (256^3, 8 per cell, FP32: 2.23 -> 2.39 ms).
 template <typename T, int ORDER, int NA, int BLOCK, typename PUT>
 __device__ inline void load_box_rows(const T* const* A, const GridGeom& g, int t0x, int t0y, int t0z, PUT put) {
   using S = Shape<T, ORDER>;
@@ -421,11 +420,17 @@ __device__ inline void load_box_rows(const T* const* A, const GridGeom& g, int t
   }
 }
 
+// Whether a box is loaded by load_box_rows: cubic ones whose rows are whole vectors, in FP64 all (nz is even).
+template <typename T, int ORDER>
+__device__ inline bool box_by_rows(const GridGeom& g) {
+  return ORDER == 3 && (sizeof(T) == 8 || g.nz % Vec16<T>::n == 0);
+}
+
 // Stages the six nodal components over the box of tile (t0x, t0y, t0z), in the
-// FieldSlots layout or (GATHER) the GatherBox one.  Thread t takes box elements
-// e = t + u * BLOCK; their coordinates (lx, ly, lz) advance by the block size
-// written in base B (no division per node).  Boxes inside the grid (all but the tiles on
-// its faces) skip the periodic wrap.  Each thread issues the loads of all its nodes before
+// FieldSlots layout or (GATHER) the GatherBox one.  Boxes that load_box_rows does not take go node by
+// node: thread t takes box elements e = t + u * BLOCK; their coordinates (lx, ly, lz) advance by the
+// block size written in base B (no division per node), boxes inside the grid (all but the tiles on
+// its faces) skip the periodic wrap, and each thread issues the loads of all its nodes before
 // storing any, so they are in flight together.
 template <typename T, int ORDER, bool GATHER = false, int BLOCK = PIC_GATHER_BLOCK>
 __device__ inline void load_field_box(T* box, const Batch<const T*>& F, const GridGeom& g, int t0x, int t0y, int t0z) {
@@ -434,7 +439,7 @@ __device__ inline void load_field_box(T* box, const Batch<const T*>& F, const Gr
   using Off = typename BoxOffset<T>::type;
   constexpr int B = X::B;
   constexpr int FS = FieldSlots<T>::FS;
-  if (ORDER == 3 && g.nz % Vec16<T>::n == 0) {
+  if (box_by_rows<T, ORDER>(g)) {
     load_box_rows<T, ORDER, 6, BLOCK>(F.p, g, t0x, t0y, t0z, [&](int n, const T* x) {
       if (GATHER) {
         GatherBox<T, X::B3>::store(box, n, x);
@@ -2051,7 +2056,7 @@ __global__ void __launch_bounds__(PIC_GATHER_BLOCK) k_particle_adjoint_tiled(
 #pragma unroll
       for (int c = 0; c < 3; ++c) ljbox[e * 4 + c] = x[1 + c];
     };
-    if (ORDER == 3 && g.nz % Vec16<T>::n == 0) {
+    if (box_by_rows<T, ORDER>(g)) {
       load_box_rows<T, ORDER, 4, PIC_GATHER_BLOCK>(L.p, g, t0x, t0y, t0z, put);
     } else {
       constexpr int PER = (X::B3 + PIC_GATHER_BLOCK - 1) / PIC_GATHER_BLOCK;
