@@ -319,7 +319,9 @@ pic_status pic_continuity_residual(pic_ctx ctx, const pic_fields* f, double* out
 /* Per-stage timing with HIP events on the context stream.  When enabled, each
  * stage launch of pic_step is bracketed by events; pic_stage_times returns, for
  * stage s < nstage, the accumulated milliseconds and the number of launches since
- * the last reset.  Stage names: pic_stage_name(s). */
+ * the last reset.  Stage names: pic_stage_name(s).  (psatd_push_fields counts its transforms and
+ * update as fft_forward, psatd_update and fft_inverse; where it takes the x transforms and the
+ * update in one kernel, that kernel is psatd_update.) */
 pic_status pic_profile(pic_ctx ctx, int enable);
 pic_status pic_stage_times(pic_ctx ctx, double* ms, int64_t* count, int nstage);
 const char* pic_stage_name(int s);

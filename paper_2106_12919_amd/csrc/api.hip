@@ -1147,7 +1147,9 @@ pic_status do_step(pic_ctx c, pic_fields* f, pic_species* sp, int nsp, int nstep
   // Real-space cycle: on every step but the last of the call the centering runs inside the
   // transforms (J_nod -> spectra of J on the Yee grid; updated spectra -> E_nod, B_nod of the
   // next step).  The last step takes the separate passes, so that at return E_stag, B_stag,
-  // J_stag and E_nod, B_nod hold what the documented cycle leaves.
+  // J_stag and E_nod, B_nod hold what the documented cycle leaves.  Steps without particles, 28 grids from
+  // 32^3 to 288 x 288 x 324 at orders 2 to 32, with the centering inside / in separate passes: 0.76 to 0.98,
+  // the most at low orders; 48^3 FP32 1.00 at order 32, 32^3 and 48^3 FP64 1.01 to 1.10 (5 us of a step).
   const bool fused = !spectral && !nodal && !avg;
   const LineCenter<T> lc_j = fused ? transform_centering<T>(c, false) : LineCenter<T>();
   const LineCenter<T> lc_eb = fused ? transform_centering<T>(c, true) : LineCenter<T>();

@@ -524,16 +524,16 @@ struct SolveShape {
   int lines, block;
 };
 
-// KiB per array from which the fused pass is the faster one along x lines of n points (0: on no grid, so it is
-// not built).  psatd_push_fields timed with it and with the separate kernels at 3 to 100 MiB per array, all
-// lengths (fused / separate): mostly 0.85 to 0.95 from 3 MiB on, 0.75 to 0.8 from 50.  Below, its chain of 17
-// transforms in one workgroup takes longer than three launches (FP32 32^3 31.6 against 27.8 us, FP64 33.5
-// against 31.7); lengths with few workgroups per array need some more (FP32, 3 MiB: 108 points 1.02 to 1.04, 192
-// 1.10, 512 1.04, 768 1.11).  With more registers than the workgroup has (FP32 162 1.05 at 5 MiB and 0.95 at 6;
-// 486 1.06 at 17 and 0.93 at 34; 648 1.06 at 16 and 0.99 at 100; FP64 144 1.10 at 23 and 0.95 at 30; 486 1.01 at
-// 173) or one workgroup per CU (FP64 108 1.14 at 10 MiB, 1.02 at 29, 0.94 at 51; 162 and 324 1.05 at 16, 0.93 at
-// 29) only large grids gain, or none.  FP64 lines of 8 and 12 points occupy 64 and 96 of a workgroup's 256 threads: 1.14 and
-// 1.08 at 16 MiB.
+// KiB per array from which the fused pass is the faster one along x lines of n points (0: on no grid, so it
+// is not built).  psatd_push_fields timed with it and with the separate kernels at 3 to 100 MiB per array,
+// all lengths (fused / separate): mostly 0.85 to 0.95 from 3 MiB on, 0.75 to 0.8 from 50.  Below, its chain
+// of 17 transforms in one workgroup takes longer than three launches (FP32 32^3 31.6 against 27.8 us, FP64
+// 33.5 against 31.7); lengths with few workgroups per array need some more (FP32, 3 MiB: 108 points 1.02 to
+// 1.04, 192 1.10, 512 1.04, 768 1.11).  With more registers than the workgroup has (FP32 162 1.05 at 5 MiB
+// and 0.95 at 6; 486 1.06 at 17 and 0.93 at 34; 648 1.06 at 16 and 0.99 at 100; FP64 144 1.10 at 23 and 0.95
+// at 30; 486 1.01 at 173) or one workgroup per CU (FP64 108 1.14 at 10 MiB, 1.02 at 29, 0.94 at 51; 162 and
+// 324 1.05 at 16, 0.93 at 29) only large grids gain, or none.  FP64 lines of 8 and 12 points occupy 64 and
+// 96 of a workgroup's 256 threads: 1.14 and 1.08 at 16 MiB.
 template <typename T>
 constexpr int solve_from_kib(int n) {
   switch (sizeof(T) == 4 ? n : -n) {
@@ -566,9 +566,10 @@ constexpr SolveShape<T> solve_shape(int n) {
 // spectra between HBM and the chip, here 18 (the tables are even in kx, so lines read them for
 // kx <= N / 2 only).  The whole solve at 256^3: FP32 1890 -> 1485 us, FP64 3563 -> 2650.  Every sum is
 // formed in the order of k_psatd_update, so the results are as accurate: terms that wait for a later
-// source are kept in LDS (in registers they spilled, 96 x 96 x 192 FP64 267 -> 319 us).  Bound by its chain of 17 transforms (2 barriers per stage) at two
-// workgroups per CU.  The same fusion of pic_step's resident state (40 arrays against 25) was no faster
-// than the separate kernels (384 x 384 x 768 FP32 4.1 ms either way, 128 x 128 x 256 142 against 128 us).
+// source are kept in LDS (in registers they spilled, 96 x 96 x 192 FP64 267 -> 319 us).  Bound by its chain
+// of 17 transforms (2 barriers per stage) at two workgroups per CU.  The same fusion of pic_step's resident
+// state (40 arrays against 25) was no faster than the separate kernels (384 x 384 x 768 FP32 4.1 ms either
+// way, 128 x 128 x 256 142 against 128 us).
 template <typename T, int N>
 __global__ void __launch_bounds__(solve_shape<T>(N).block, sizeof(T) == 4 ? 4 : 3) k_solve_x(SolveX<T> a, const cplx<T>* __restrict__ tw) {
   constexpr int TL = solve_shape<T>(N).lines, BLOCK = solve_shape<T>(N).block;

@@ -673,7 +673,7 @@ struct DepositOrder {
 //
 // The cubic gather was bound by its LDS reads: 64 nodes of 16 + 8 bytes per particle, each pair 9.4 clocks
 // per wave when the lanes' first nodes are distinct modulo 32, 20.6 in cell order and 26 in random order
-// (measured; LDS-active 71% of the beam wake's gather, 56% of that conflicts).  ``deal`` is the order in
+// (measured; LDS-active 71% of the beam wake's gather, 56% of that conflicts; now 48% and 33%).  ``deal`` is the order in
 // which the previous deposition visited the same particles (dealt round-robin over those residues, per
 // chunk of DepositOrder<T>::CH); the gather takes it over, and as it writes in the order it visits, memory
 // stays nearly dealt and the deposition's own loads nearly contiguous.  64 x 64 x 128, 4 per cell, FP32:
@@ -1242,10 +1242,12 @@ __device__ inline void deposit_tile(int item, int parts, const GridGeom& g, cons
     // record, with momentum and weight for the bounds of a single-chunk tile): the first support
     // node of the current shifts from it only when the half step crosses a cell face, and the
     // deal only orders the atomics, it does not change their sums.
-    // The box indices found here go with the deal: the kernel issues vector instructions for 63% (cubic, one
-    // particle per cell) to 82% (linear) of its time, a fifth of them on cells, indices and faces, and the second
-    // pass now decodes no cell, takes the neighbour tile and the faces reached from the indices, and forms the
-    // current's indices from them by the half step's shift.  256^3, 8 per cell, linear, FP32: 2.28 -> 2.03 ms;
+    // The box indices found here go with the deal, so the second pass decodes no cell, takes the neighbour tile
+    // and the faces reached from the indices, and forms the current's indices from them by the half step's
+    // shift.  The kernel issued vector instructions for 63% (cubic, one particle per cell) to 82% (linear) of its
+    // time, a fifth of them on these; now it is 59% and 73%, and its LDS is active for 58% and 38% (38% and 43% of
+    // that conflicts), the waves waiting at barriers and for loads half of their time.
+    // 256^3, 8 per cell, linear, FP32: 2.28 -> 2.03 ms;
     // cubic FP32 384 x 384 x 768, 1 per cell: 6.80 -> 6.40 ms; FP64 192 x 192 x 384: 1.67 -> 1.57 ms.
     int kr[O::U];  // box indices and (rank, residue) of this thread's particles, until the deal below
     {
