@@ -434,7 +434,10 @@ hipError_t build_engine(const pic_params& p, Engine<T>& e) {
   // the row layout of deposit_tiled (B x B x 16 per component) holds the node-major boxes
   // (B^3) of the staggered cycle's deposition too
   const size_t slot = (size_t)deposit_stage_slot(p.shape_order);
-  if ((err = e.alloc(&e.stage, stage_slots(e.tiles) * 4 * slot)) != hipSuccess) return err;
+  const size_t staged = stage_slots(e.tiles) * 4 * slot;
+  if ((err = e.alloc(&e.stage, staged)) != hipSuccess) return err;
+  e.tiles.spare = reinterpret_cast<int*>(e.stage);
+  e.tiles.spare_ints = staged * (sizeof(T) / sizeof(int));
   return hipStreamSynchronize(nullptr);  // everything cleared above, before any stream's use
 }
 

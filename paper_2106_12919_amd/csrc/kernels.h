@@ -192,6 +192,9 @@ struct TileGeom {
   int ntx, nty, ntz, ntiles;
   bool distinct;            // whole tiles only, and at least three along every axis
   int* scan_tmp = nullptr;  // device scratch of the bucket scan: (ntiles + 1) / 8192 + 2 ints
+  // device memory that is free while a sort runs (the deposition's staging boxes), and its ints; optional
+  int* spare = nullptr;
+  size_t spare_ints = 0;
 };
 TileGeom make_tiles(const GridGeom& g);  // tiles of kTile^3 cells
 // Edge length (nodes) of the LDS boxes of one tile: the tile, the shape support and a

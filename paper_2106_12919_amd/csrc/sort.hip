@@ -5,6 +5,8 @@
 // the sorted order has no holes (they are counted and never deposited).  Three
 // launches: count per tile, exclusive scan of the counts, rank (each particle's
 // slot in tile order, kept as the permutation slot -> particle).
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace pic {
@@ -32,13 +34,14 @@ __device__ inline int tile_key(int c, const GridGeom& g, const TileGeom& t) {
 // 26 us for 2.1 M grouped particles, 407 against 341 for 9 M scattered ones).
 constexpr int kSortPer = 8;
 constexpr int kSortBuckets = 32768;
-constexpr int kSortTable = 1024;  // entries of the hashed table
+constexpr int kSortTable = 2048;  // entries of the hashed table
 constexpr int kSortProbes = 16;
 
 template <bool HASH>
 __device__ inline int table_place(volatile int* keys, int key) {
   if (!HASH) return key;
-  const unsigned h = ((unsigned)key * 2654435761u) >> 22;  // 10 bits: kSortTable entries
+  const unsigned h = ((unsigned)key * 2654435761u) >> 21;  // 11 bits: kSortTable entries
+#pragma unroll 1
   for (int p = 0; p < kSortProbes; ++p) {
     const int e = (int)((h + p) & (kSortTable - 1));
     int k = keys[e];
@@ -91,7 +94,8 @@ __device__ inline void table_clear(int* keys, int* cnt, int nbk) {
   __syncthreads();
 }
 
-// Dynamic LDS of both: the counts (the table's entries, or one per bucket), then with HASH the keys.
+// Dynamic LDS of both: the counts (the table's entries, or one per bucket), then with HASH the keys and one
+// more int.
 template <bool HASH, int BLOCK>
 __global__ void __launch_bounds__(BLOCK) k_tile_count(GridGeom g, TileGeom t, const int32_t* __restrict__ cell,
                                                            long long n, int* counts) {
@@ -114,13 +118,20 @@ __global__ void __launch_bounds__(BLOCK) k_tile_count(GridGeom g, TileGeom t, co
   }
 }
 
-// Each workgroup reserves one run per tile on ``cursor`` and places its particles in it by rank.
+// Each workgroup reserves one run per tile on ``cursor`` and places its particles in it by rank.  With ``slots``
+// (HASH), a workgroup that fills seven eighths of its table (an unordered species)
+// writes the slots of its particles in order and says so in scattered[block], for k_tile_place: in one kernel
+// with that many global atomics the scattered writes of perm are slow (134 M unordered particles in 32769
+// buckets: count, rank and place 12.5 ms, with one rank kernel 17.6).
 template <bool HASH, int BLOCK>
 __global__ void __launch_bounds__(BLOCK) k_tile_rank(GridGeom g, TileGeom t, const int32_t* __restrict__ cell,
-                                                          long long n, int* cursor, int* perm, int* bad) {
+                                                          long long n, int* cursor, int* perm, int* bad, int* slots,
+                                                          int* scattered) {
   extern __shared__ int cnt[];
   int* const keys = cnt + kSortTable;
+  int* const used = keys + kSortTable;  // (HASH) entries of the table in use
   const int nbk = t.ntiles + 1;
+  if (HASH && threadIdx.x == 0) *used = 0;
   table_clear<HASH, BLOCK>(keys, cnt, nbk);
   const long long p0 = (long long)blockIdx.x * BLOCK * kSortPer + threadIdx.x;
   int place[kSortPer], rank[kSortPer];
@@ -132,15 +143,42 @@ __global__ void __launch_bounds__(BLOCK) k_tile_rank(GridGeom g, TileGeom t, con
     if (p < n && key == t.ntiles && bad) atomicAdd(bad, 1);
   }
   __syncthreads();
+  if (HASH) {
+    int mine = 0;
+#pragma unroll
+    for (int e = threadIdx.x; e < kSortTable; e += BLOCK) mine += __popcll(__ballot(cnt[e] != 0));
+    if (mine && __lane_id() == 0) atomicAdd(used, mine);
+  }
   for (int e = threadIdx.x; e < (HASH ? kSortTable : nbk); e += BLOCK) {
     const int c = cnt[e];
     if (c) cnt[e] = atomicAdd(&cursor[HASH ? keys[e] : e], c);  // this workgroup's run of the tile
   }
   __syncthreads();
+  const bool split = HASH && slots && __builtin_amdgcn_readfirstlane(*used) > kSortTable / 8 * 7;
+  if (HASH && slots && threadIdx.x == 0) scattered[blockIdx.x] = split;
+  int* const out = split ? slots : perm;
 #pragma unroll
   for (int u = 0; u < kSortPer; ++u) {
     const long long p = p0 + (long long)u * BLOCK;
-    if (p < n) perm[(place[u] >= 0 ? cnt[place[u]] : 0) + rank[u]] = (int)p;
+    const int slot = (place[u] >= 0 ? cnt[place[u]] : 0) + rank[u];
+    if (p < n) out[split ? (int)p : slot] = split ? slot : (int)p;
+  }
+}
+
+// The particles of the workgroups that k_tile_rank found scattered, to their slots.  The resident workgroups
+// walk the particles side by side, BLOCK at a time (64 flags a look), so that what they write at one time
+// is a short run in each tile.
+template <int BLOCK>
+__global__ void __launch_bounds__(BLOCK) k_tile_place(long long n, const int* __restrict__ slots,
+                                                      const int* __restrict__ scattered, int* perm) {
+  const long long chunks = (n + BLOCK - 1) / BLOCK, step = gridDim.x;
+  for (long long c0 = blockIdx.x; c0 < chunks; c0 += 64 * step) {
+    const long long c = c0 + __lane_id() * step;
+    unsigned long long todo = __ballot(c < chunks && scattered[c / kSortPer] != 0);
+    for (; todo; todo &= todo - 1) {
+      const long long p = (c0 + (__ffsll(todo) - 1) * step) * BLOCK + threadIdx.x;
+      if (p < n) perm[slots[p]] = (int)p;
+    }
   }
 }
 
@@ -359,14 +397,20 @@ template <bool HASH, int BLOCK>
 void sort_with(const GridGeom& g, const TileGeom& t, const int32_t* cell, int64_t n, int* counts, int* starts,
                int* cursor, int* perm, int* bad, hipStream_t s) {
   const dim3 grid((unsigned)((n + BLOCK * kSortPer - 1) / (BLOCK * kSortPer))), block(BLOCK);
-  const size_t lds = sizeof(int) * (size_t)(HASH ? 2 * kSortTable : t.ntiles + 1);
+  const size_t lds = sizeof(int) * (size_t)(HASH ? 2 * kSortTable + 1 : t.ntiles + 1);
   allow_lds((const void*)k_tile_count<HASH, BLOCK>, lds);
   allow_lds((const void*)k_tile_rank<HASH, BLOCK>, lds);
   if (n > 0)
     hipLaunchKernelGGL((k_tile_count<HASH, BLOCK>), grid, block, lds, s, g, t, cell, (long long)n, counts);
   scan_counts(t, counts, starts, cursor, s);
-  if (n > 0)
-    hipLaunchKernelGGL((k_tile_rank<HASH, BLOCK>), grid, block, lds, s, g, t, cell, (long long)n, cursor, perm, bad);
+  if (n <= 0) return;
+  int* const slots = HASH && t.spare && (size_t)n + grid.x <= t.spare_ints ? t.spare : nullptr;
+  int* const scattered = slots ? slots + n : nullptr;
+  hipLaunchKernelGGL((k_tile_rank<HASH, BLOCK>), grid, block, lds, s, g, t, cell, (long long)n, cursor, perm, bad, slots,
+                     scattered);
+  if (slots)
+    hipLaunchKernelGGL(k_tile_place<BLOCK>, dim3(std::min(grid.x * kSortPer, 1024u)), block, 0, s, (long long)n,
+                       (const int*)slots, (const int*)scattered, perm);  // 4 workgroups per CU
 }
 
 }  // namespace
@@ -375,7 +419,7 @@ void tile_sort(const GridGeom& g, const TileGeom& t, const int32_t* cell, int64_
                int* cursor, int* perm, int* bad, hipStream_t s) {
   // buckets 0..ntiles-1 are tiles, bucket ntiles collects invalid cells; small tables (and the hashed
   // one) take small workgroups, large ones as many particles per table as a workgroup can hold
-  if (t.ntiles + 1 > kSortBuckets) sort_with<true, 256>(g, t, cell, n, counts, starts, cursor, perm, bad, s);
+  if (t.ntiles + 1 > kSortBuckets) sort_with<true, 512>(g, t, cell, n, counts, starts, cursor, perm, bad, s);
   else if (t.ntiles + 1 > 1024) sort_with<false, 1024>(g, t, cell, n, counts, starts, cursor, perm, bad, s);
   else sort_with<false, 256>(g, t, cell, n, counts, starts, cursor, perm, bad, s);
 }

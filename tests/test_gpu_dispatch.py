@@ -133,6 +133,36 @@ def test_tile_sort_tables(shape, order):
     ctx.close()
 
 
+@pytest.mark.parametrize("n", [4095, 4096 * 3 + 1, 1300000])
+def test_tile_sort_hashed_in_stretches(n):
+    """The hashed table with stretches of grouped and of scattered particles in turn: workgroups that place
+    their particles themselves beside ones that leave it to the kernel after them, more particles than that
+    kernel takes in one walk."""
+    shape = (256, 256, 288)
+    banner(f"pic_deposit, particles in stretches of either order n={n}")
+    N = int(np.prod(shape))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    cell = torch.randint(0, N, (n,), generator=gen, device="cuda", dtype=torch.int32)
+    stretch = torch.arange(n, device="cuda") // 5000
+    cell = torch.where(stretch % 2 == 0, cell.sort().values, cell)
+    half = torch.full((n,), 0.5, device="cuda", dtype=torch.float64)
+    ctx = piclib.Context(shape, (1.0, 1.0, 1.0), 0.5, 1, 4, 16, "f64")
+    f = piclib.Fields(shape, "f64")
+    sp = piclib.Species(cell, [half] * 3, [torch.zeros_like(half)] * 3, None, 1.0, 1.0, w_const=8.0)
+    c = cell.long()
+    i, j, k = c // (shape[1] * shape[2]), (c // shape[2]) % shape[1], c % shape[2]
+    ref = torch.zeros(N, device="cuda", dtype=torch.float64)
+    one = torch.ones(n, device="cuda", dtype=torch.float64)
+    for a in range(8):
+        q = (((i + a // 4) % shape[0]) * shape[1] + (j + a // 2 % 2) % shape[1]) * shape[2] + (k + a % 2) % shape[2]
+        ref.index_add_(0, q, one)
+    for _ in range(2):
+        piclib.pic_deposit(ctx.ctx, [sp], f, piclib.PIC_DEP_RHO_ONLY)
+        assert torch.equal(f.rho_new.reshape(-1), ref)
+    ctx.close()
+
+
 # every workgroup and tile shape of the fused x pass, and the first lengths past its last one
 FUSED = [("f32", (8, 288, 384)), ("f32", (96, 96, 96)), ("f32", (108, 96, 96)), ("f32", (216, 64, 64)),
          ("f32", (432, 48, 48)), ("f32", (768, 36, 36)), ("f32", (864, 32, 36)),
