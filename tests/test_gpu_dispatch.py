@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 from oracle import centering as ocent  # noqa: E402
+from oracle import particles as opart  # noqa: E402
 from oracle import step as ostep  # noqa: E402
 from paper_2106_12919_amd import autograd as pag  # noqa: E402
 from paper_2106_12919_amd import inputs  # noqa: E402
@@ -88,6 +89,46 @@ def test_several_chunks_per_tile(dtype, shape, ppc):
     the gather follows the order the deposition published, chunk by chunk."""
     banner(f"pic_step 4 steps, several chunks per tile dtype={dtype} shape={shape} ppc={ppc}")
     steps_against_oracle(shape, ppc, 3, 8, dtype, 4)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("shape", [(48, 48, 64), (16, 16, 16)])
+def test_chunks_spread_over_heavy_tiles(dtype, shape):
+    """pic_deposit of particles in cell order, cubic: tiles just below, at and above the size from which a chunk
+    takes particles from all over its tile, as whole tiles and split in parts."""
+    banner(f"pic_deposit heavy tiles dtype={dtype} shape={shape}")
+    rng = np.random.default_rng(17)
+    sizes = {(0, 0, 0): 16383, (1, 0, 1): 16384, (1, 1, 1): 20001, (0, 1, 1): 17 * 1024}
+    cells = []
+    for t, n in sizes.items():
+        l = rng.integers(0, 8, (n, 3)) + 8 * np.array(t)
+        cells.append((l[:, 0] * shape[1] + l[:, 1]) * shape[2] + l[:, 2])
+    cell = np.sort(np.concatenate(cells)).astype(np.int32)
+    n, td = cell.size, torch.float32 if dtype == "f32" else torch.float64
+    dev = lambda a: torch.tensor(a, dtype=td, device="cuda")  # noqa: E731
+    off = [dev(rng.random(n) * 0.999) for _ in range(3)]
+    u = [dev(m + 0.1 * rng.standard_normal(n)) for m in (0.5, -0.4, 0.3)]
+    sp = piclib.Species(torch.tensor(cell, device="cuda"), off, u, None, -1.0, 1.0, w_const=0.5)
+    ctx = piclib.Context(shape, (1.0, 1.0, 1.0), 0.5, 3, 8, 16, dtype)
+    f = piclib.Fields(shape, dtype)
+    piclib.pic_deposit(ctx.ctx, [sp], f, piclib.PIC_DEP_RHO_AND_J)
+    piclib.pic_sync(ctx.ctx)
+    p = ostep.Params(shape, (1.0, 1.0, 1.0), 0.5, 3, 8, 16)
+    ijk = np.stack(np.unravel_index(cell, shape), axis=1)
+    pos = ijk + np.stack([np64(x) for x in off], axis=1)
+    uu = np.stack([np64(x) for x in u])
+    v = uu / np.sqrt(1.0 + np.sum(uu * uu, axis=0))
+    rho = opart.deposit([np.full(n, -0.5)], pos, shape, (1.0, 1.0, 1.0), 3)[0]
+    half = opart.wrap(pos - 0.5 * 0.5 * v.T, p.lengths)
+    J = opart.deposit(list(-0.5 * v), half, shape, (1.0, 1.0, 1.0), 3)
+    # A node sums at most 64 cells of about 40 particles (2600 contributions), each rounded to half a unit.  FP32:
+    # a unit is at most 2^-29 of 0.3 times the tile's 20001 charges, 1.1e-5 charges; a full node holds about 32.
+    # FP64: at most 2^-46 charges.  The contributions themselves are good to about 64 eps.
+    tol = {"f32": 2600 / 2 * 1.1e-5 / 32, "f64": 2600 / 2 * 2.0 ** -46 / 32}[dtype] + 64 * EPS[dtype]
+    assert max_rel(np64(f.rho_new), rho) <= tol
+    for d in range(3):
+        assert max_rel(np64(f.J_nod[d]), J[d]) <= tol
+    ctx.close()
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
