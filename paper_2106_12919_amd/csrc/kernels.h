@@ -303,7 +303,7 @@ struct ReduceArgs {
   }
 };
 template <typename T>
-void deposit_reduce(const GridGeom& g, const TileGeom& t, const int* starts, const T* stage, bool with_j, T* rho,
+void deposit_reduce(const GridGeom& g, const TileGeom& t, const int* starts, T* stage, bool with_j, T* rho,
                     T* const J[3], hipStream_t s, const ReduceArgs<T>& ra = ReduceArgs<T>());
 
 // Reverse mode of gather + push + move + deposition of one species, particles at time n

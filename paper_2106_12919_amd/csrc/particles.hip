@@ -1740,11 +1740,39 @@ __global__ void __launch_bounds__(256) k_deposit_reduce_rows(GridGeom g, TileGeo
   }
 }
 
+// The parts' integers of split tiles summed and converted with the tile's scale, into the tile's first slot, for
+// k_deposit_reduce.  Summed there instead, one thread walked the parts of up to 27 boxes (the images around a
+// short last tile) and the few nodes of such a grid filled a few compute units only: pic_deposit of 18^3, 8 per
+// cell, linear FP64 141 -> 87 us, cubic FP64 198 -> 135; 36^3, 16 per cell, cubic FP64 326 -> 290.
+template <typename T>
+__global__ void __launch_bounds__(256) k_fold_parts(const int* __restrict__ starts, T* stage, int ncomp, int slot,
+                                                    int parts, const int* __restrict__ scales) {
+  const int tile = blockIdx.x, len = starts[tile + 1] - starts[tile];
+  const int at = (int)(blockIdx.y * blockDim.x + threadIdx.x) * 4;
+  if (len == 0 || at >= ncomp * slot) return;
+  int per;
+  const int np = tile_parts<T>(len, parts, per);
+  T* const first = stage + (size_t)tile * parts * ncomp * slot + at;
+  typename Fixed<T>::acc_t sum[4] = {0, 0, 0, 0};
+#pragma unroll 4
+  for (int p = 0; p < np; ++p) {
+    T v[4];
+    load4(first + (size_t)p * ncomp * slot, v);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sum[i] += Fixed<T>::value(v[i]);
+  }
+  const int sh = -scales[4 * tile + at / slot];
+  T v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = ldexp((T)sum[i], sh);
+  store4(first, v);
+}
+
 // The same for any grid (partial tiles at the upper ends): candidate (tile, box index)
 // pairs per axis over the periodic images x - n, x, x + n, box node l of tile t being
-// grid node (t * kTile - 1 + BASE + l) mod n.  PARTS: split tiles (the sum over the parts in the one kernel
-// for both took 81 instead of 70 VGPRs, FP64 106 instead of 84: 162 x 288 x 486 FP32 832 -> 1051 us).
-template <typename T, int ORDER, bool PARTS>
+// grid node (t * kTile - 1 + BASE + l) mod n.  Of split tiles it reads the first slot, with what k_fold_parts
+// left there.
+template <typename T, int ORDER>
 __global__ void __launch_bounds__(256) k_deposit_reduce(GridGeom g, TileGeom tg, const int* __restrict__ starts,
                                                         const T* __restrict__ stage, Batch<T*> out, int ncomp,
                                                         ReduceArgs<T> ra) {
@@ -1793,18 +1821,8 @@ __global__ void __launch_bounds__(256) k_deposit_reduce(GridGeom g, TileGeom tg,
           if (starts[tile] == starts[tile + 1]) continue;
           const int slot = ra.rows ? StageRows<ORDER>::SLOT : X::B3;
           const int at = ra.rows ? StageRows<ORDER>::at(clx[a], cly[b], clz[c]) : X::at(clx[a], cly[b], clz[c]);
-          const T* sb = stage + (size_t)tile * (PARTS ? ra.parts : 1) * ncomp * slot + at;
-          if (PARTS) {  // the parts' integers summed, then converted with the tile's scale
-            int per;
-            const int np = tile_parts<T>(starts[tile + 1] - starts[tile], ra.parts, per);
-            for (int q = 0; q < ncomp; ++q) {
-              typename Fixed<T>::acc_t sum = 0;
-              for (int p = 0; p < np; ++p) sum += Fixed<T>::value(sb[(size_t)(p * ncomp + q) * slot]);
-              acc[q] += ldexp((T)sum, -ra.box_faces[4 * tile + q]);
-            }
-          } else {
-            for (int q = 0; q < ncomp; ++q) acc[q] += sb[(size_t)q * slot];
-          }
+          const T* sb = stage + (size_t)tile * ra.parts * ncomp * slot + at;
+          for (int q = 0; q < ncomp; ++q) acc[q] += sb[(size_t)q * slot];
         }
     for (int q = 0; q < ncomp; ++q) out.p[q][idx] = ra.start(q, out.p[q], idx) + acc[q] + (spilled ? ra.take_spill(q, idx) : (T)0);
   }
@@ -2723,7 +2741,7 @@ void deposit_tiled(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& s
 }
 
 template <typename T>
-void deposit_reduce(const GridGeom& g, const TileGeom& t, const int* starts, const T* stage, bool with_j, T* rho,
+void deposit_reduce(const GridGeom& g, const TileGeom& t, const int* starts, T* stage, bool with_j, T* rho,
                     T* const J[3], hipStream_t s, const ReduceArgs<T>& ra) {
   Batch<T*> out{};
   out.p[0] = rho;
@@ -2762,15 +2780,15 @@ void deposit_reduce(const GridGeom& g, const TileGeom& t, const int* starts, con
   }
   const long long N = (long long)g.nx * g.ny * g.nz;
   const unsigned nr = (unsigned)std::min<long long>((N + 255) / 256, 65536);
-  auto launch = [&](auto parts) {
-    constexpr bool P = decltype(parts)::value;
-    if (g.shape_order == 1)
-      hipLaunchKernelGGL((k_deposit_reduce<T, 1, P>), dim3(nr), dim3(256), 0, s, g, t, starts, stage, out, ncomp, ra);
-    else
-      hipLaunchKernelGGL((k_deposit_reduce<T, 3, P>), dim3(nr), dim3(256), 0, s, g, t, starts, stage, out, ncomp, ra);
-  };
-  if (ra.parts > 1) launch(std::true_type{});
-  else launch(std::false_type{});
+  if (ra.parts > 1) {
+    const int slot = deposit_stage_slot(g.shape_order);
+    hipLaunchKernelGGL((k_fold_parts<T>), dim3(t.ntiles, (ncomp * slot / 4 + 255) / 256), dim3(256), 0, s, starts,
+                       stage, ncomp, slot, ra.parts, ra.box_faces);
+  }
+  if (g.shape_order == 1)
+    hipLaunchKernelGGL((k_deposit_reduce<T, 1>), dim3(nr), dim3(256), 0, s, g, t, starts, (const T*)stage, out, ncomp, ra);
+  else
+    hipLaunchKernelGGL((k_deposit_reduce<T, 3>), dim3(nr), dim3(256), 0, s, g, t, starts, (const T*)stage, out, ncomp, ra);
 }
 
 template <typename T>
@@ -2844,9 +2862,9 @@ void scatter_tiled(const GridGeom& g, const TileGeom& t, const SpeciesView<T>& s
   const long long N = (long long)g.nx * g.ny * g.nz;
   const unsigned nr = (unsigned)std::min<long long>((N + 255) / 256, 65536);
   if (g.shape_order == 1)
-    hipLaunchKernelGGL((k_deposit_reduce<T, 1, false>), dim3(nr), dim3(256), 0, s, g, t, starts, stage, o, 6, ReduceArgs<T>());
+    hipLaunchKernelGGL((k_deposit_reduce<T, 1>), dim3(nr), dim3(256), 0, s, g, t, starts, stage, o, 6, ReduceArgs<T>());
   else
-    hipLaunchKernelGGL((k_deposit_reduce<T, 3, false>), dim3(nr), dim3(256), 0, s, g, t, starts, stage, o, 6, ReduceArgs<T>());
+    hipLaunchKernelGGL((k_deposit_reduce<T, 3>), dim3(nr), dim3(256), 0, s, g, t, starts, stage, o, 6, ReduceArgs<T>());
 }
 
 template <typename T>
@@ -2937,7 +2955,7 @@ void deposit_yee(const GridGeom& g, const SpeciesView<T>& sp, bool with_j, T* rh
   template void deposit_tiled<T>(const GridGeom&, const TileGeom&, const SpeciesView<T>&, const int*, const int*, \
                                  bool, T*, int*, int*, int*, int*, T*, T* const*, hipStream_t, int*, int*,       \
                                  unsigned short*, int);                                                          \
-  template void deposit_reduce<T>(const GridGeom&, const TileGeom&, const int*, const T*, bool, T*, T* const*,   \
+  template void deposit_reduce<T>(const GridGeom&, const TileGeom&, const int*, T*, bool, T*, T* const*,         \
                                   hipStream_t, const ReduceArgs<T>&);                                            \
   template void gather_push_tiled<T>(const GridGeom&, const TileGeom&, const T* const*, const T* const*,         \
                                      const SpeciesView<T>&, const SpeciesView<T>&, const int*, const int*, bool,  \

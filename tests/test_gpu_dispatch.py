@@ -92,6 +92,14 @@ def test_several_chunks_per_tile(dtype, shape, ppc):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("shape,ppc,order", [((12, 12, 12), 24, 1), ((18, 18, 18), 12, 3), ((12, 8, 18), 16, 3)])
+def test_split_ragged_tiles(dtype, shape, ppc, order):
+    """Tiles in several parts on grids with partial tiles, with tiles of fewer particles than one part among them."""
+    banner(f"pic_step 3 steps, split ragged tiles dtype={dtype} shape={shape} ppc={ppc} order={order}")
+    steps_against_oracle(shape, ppc, order, 8, dtype, 3)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("shape", [(48, 48, 64), (16, 16, 16)])
 def test_chunks_spread_over_heavy_tiles(dtype, shape):
     """pic_deposit of particles in cell order, cubic: tiles just below, at and above the size from which a chunk
