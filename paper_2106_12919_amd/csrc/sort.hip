@@ -28,10 +28,11 @@ __device__ inline int tile_key(int c, const GridGeom& g, const TileGeom& t) {
 // counter once per tile it holds.  Up to kSortBuckets buckets (128 KiB of LDS) the table is indexed by
 // the tile; beyond, by a hash with linear probing (HASH): particles are nearly grouped by tile (the
 // previous call's order), so a workgroup holds few distinct tiles.  A key that finds no place in the
-// table goes to the global counter by itself.  32769 buckets, 134 M particles of the 256^3 thermal
-// plasma: count and rank 334 + 453 us, against 701 + 1325 (and 308 to invert the slots) with one global
-// atomic per wave and tile.  At 1025 and 6157 buckets the hash was slower than the indexed table (33 against
-// 26 us for 2.1 M grouped particles, 407 against 341 for 9 M scattered ones).
+// table goes to the global counter by itself.  32769 buckets, 134 M particles (256^3, 8 per cell) in cell order:
+// count and rank 368 + 523 us, against 512 + 656 (and 318 to invert the slots) with one global atomic per wave
+// and tile; moved by up to 8 cells 793 + 1042, against 1926 + 2228 (and 481).
+// At 1025 and 6157 buckets the hash was slower than the indexed table (33 against 26 us for 2.1 M grouped
+// particles, 407 against 341 for 9 M scattered ones).
 constexpr int kSortPer = 8;
 constexpr int kSortBuckets = 32768;
 constexpr int kSortTable = 2048;  // entries of the hashed table
